@@ -175,6 +175,15 @@ __device__ __forceinline__ void store_nt(P ptr, T v) {
     __builtin_nontemporal_store(v, ptr);
 }
 
+// The 16-bit word that store_moment writes for a moment of a 16-bit plane.
+template <int ST> __device__ __forceinline__ uint16_t half_bits(float v, int p, const Scales &sc) {
+    const float s = v * ((ST != ST_FP16Q && p >= 1 && p < 4) ? sc.inv_s1 : sc.inv_s2);
+    if constexpr (ST == ST_BF16)
+        return bf16_bits(s);
+    else
+        return __builtin_bit_cast(uint16_t, f16_of(s));
+}
+
 template <int ST, bool G = false>
 __device__ __forceinline__ void store_moment(void *mom, long long ld, int p, long long id, float v, const Scales &sc) {
     if constexpr (ST == ST_FP32) {
@@ -269,42 +278,46 @@ __device__ __forceinline__ int boundary_face(const Geo &g, int x, int y, int z) 
     return -1;
 }
 
-// Raw moments m[10] (rho', ubar, Q) and phase of boundary node (x, y) on `face`
-// at step `step`, given those of its nearest interior node on input: the rule
-// imposes density and/or velocity and keeps the copied non-equilibrium part.
+// Raw moments m[10] (rho', ubar, Q) of a boundary node on a face of `axis` under
+// `rule`, given those of its nearest interior node: the rule imposes density and/or
+// velocity and keeps the copied non-equilibrium part.  Written as selections, so
+// that lanes under different rules do not diverge; the inlet is apply_inlet.
+__device__ __forceinline__ void apply_rule(uint32_t rule, int axis, float m[10]) {
+    const bool slip = rule == 1u, still = rule == 4u;  // free slip, no slip
+    const bool sx = slip && axis == 0, sy = slip && axis == 1, sz = slip && axis == 2;
+    m[0] = rule == 3u ? 0.f : m[0];  // outflow: unit density
+    m[1] = sx || still ? 0.f : m[1];  // free slip: no normal velocity, no normal-tangential stress
+    m[2] = sy || still ? 0.f : m[2];
+    m[3] = sz || still ? 0.f : m[3];
+    m[7] = sx || sy ? 0.f : m[7];
+    m[8] = sx || sz ? 0.f : m[8];
+    m[9] = sy || sz ? 0.f : m[9];
+}
+
+// The inlet disc on -z: u = U s(r)(1 + a xi) e_z, phi = s(r).
+template <class P>
+__device__ __forceinline__ void apply_inlet(const P &ph, const Geo &g, int x, int y, unsigned long long step,
+                                            float m[10], int32_t &phi) {
+    const float dx = x - 0.5f * (g.nx - 1), dy = y - 0.5f * (g.ny - 1);
+    const float r = sqrtf(dx * dx + dy * dy);
+    const float s = 0.5f * (1.0f - tanhf(2.0f * (r - 0.5f * ph.inlet_d) / ph.width));
+    const float xi = noise_xi(ph.noise_key, 1ull, step, (unsigned long long)(x + (long long)g.nx * y), 2ull);
+    m[1] = 0.f;
+    m[2] = 0.f;
+    m[3] = ph.inlet_u * s * (1.0f + ph.inlet_noise * xi);
+    phi = phi_from_float(s);
+}
+
+// A boundary node on `face` (0..5) at step `step`.
 __device__ __forceinline__ void apply_boundary_rule(const Phys &ph, const Geo &g, int face, int x, int y,
                                                     unsigned long long step, float m[10], int32_t &phi) {
-    const int axis = face >> 1;
     // constant indices keep the rule table in scalar registers
     const int rule = face == 0 ? ph.bc[0] : face == 1 ? ph.bc[1] : face == 2 ? ph.bc[2]
                    : face == 3 ? ph.bc[3] : face == 4 ? ph.bc[4] : ph.bc[5];
-    switch (rule) {
-    case 1:  // free slip: no normal velocity, no normal-tangential stress
-        m[1 + axis] = 0.f;
-        if (axis == 0) { m[7] = 0.f; m[8] = 0.f; }
-        if (axis == 1) { m[7] = 0.f; m[9] = 0.f; }
-        if (axis == 2) { m[8] = 0.f; m[9] = 0.f; }
-        break;
-    case 4:  // no slip
-        m[1] = m[2] = m[3] = 0.f;
-        break;
-    case 3:  // outflow: unit density
-        m[0] = 0.f;
-        break;
-    case 2: {  // inlet disc on -z: u = U s(r)(1 + a xi) e_z, phi = s(r)
-        const float dx = x - 0.5f * (g.nx - 1), dy = y - 0.5f * (g.ny - 1);
-        const float r = sqrtf(dx * dx + dy * dy);
-        const float s = 0.5f * (1.0f - tanhf(2.0f * (r - 0.5f * ph.inlet_d) / ph.width));
-        const float xi = noise_xi(ph.noise_key, 1ull, step, (unsigned long long)(x + (long long)g.nx * y), 2ull);
-        m[1] = 0.f;
-        m[2] = 0.f;
-        m[3] = ph.inlet_u * s * (1.0f + ph.inlet_noise * xi);
-        phi = phi_from_float(s);
-        break;
-    }
-    default:
-        break;
-    }
+    if (rule == 2)
+        apply_inlet(ph, g, x, y, step, m, phi);
+    else
+        apply_rule((uint32_t)rule, face >> 1, m);
 }
 
 }  // namespace tslb

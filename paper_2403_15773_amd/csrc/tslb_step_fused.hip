@@ -1,30 +1,45 @@
 // Fused thread-safe LB step for gfx950: one kernel reads the raw moments and
 // phase field of step t once from HBM and writes those of step t+1 once.
+// (binary32 storage; tslb_step_half.hip is the step for 16-bit stored moments)
 //
-// Work decomposition.  A workgroup owns a 32 x 16 tile of (x, y) destination
-// columns and marches through a chunk of z planes.  Its 640 threads are
-//   t <  512 : destination column (t % 32, t / 32), also the source of that column,
-//   t <  612 : one of the 100 columns of the one-node halo ring (sources only),
-//   t >= 612 : idle in the source stages.
-// For every z plane the workgroup
-//   S1  stages the fixed-point phase field of plane p (3-node halo) in LDS,
-//   S2  computes G = grad(phi) and n = G/(|G| + eps) of plane p-1 (2-node halo),
-//   S3  computes kappa = div n and F = -sigma kappa G of plane p-2 (1-node halo),
-//   S4  rebuilds at every source of plane p-2 the 27 post-collision populations
-//       (as brackets t_i = f_i/w_i - 1) and the 7 phase populations,
-//   S5  moves them: x and y through LDS, z through registers (the populations of
-//       velocity c_z = -1, 0, +1 belong to destination planes p-3, p-2, p-1),
-//   S6  finishes destination plane p-3 and stores it.
+// Work decomposition.  A workgroup owns a 32 x 16 (or 32 x 20) tile of (x, y)
+// destination columns and marches through a chunk of z planes; its threads are
+// destination columns (each also the source of that column), columns of the
+// one-node halo ring (sources only) and, for the interface geometry, columns of a
+// two-node halo.  For every z plane the workgroup
+//   S1  stages the fixed-point phase field of a plane (3-node halo) in LDS,
+//   S2  computes G = grad(phi) and n = G/(|G| + eps) (2-node halo) from the plane's
+//       nine values around a column and sums kept of the planes before it,
+//   S3  computes kappa = div n and F = -sigma kappa G (1-node halo),
+//   S4  expands at every source the post-collision populations (as brackets
+//       t_i = f_i/w_i - 1) in c_z: t(c) = T0 + c_z T1 + (c_z^2 - 1/3) T2, each T on the
+//       nine (c_x, c_y), and the 7 phase populations,
+//   S5  moves them across columns through LDS,
+//   S6  sums the three T over (c_x, c_y) at the destination, forms from the sums what
+//       c_z = -1, 0, +1 carry to the planes below, at and above (kept in registers),
+//       finishes the plane below and stores it.
 // Each destination node is written by exactly one thread and every read is of
 // step t, so the update is race-free (the thread-safe property of the method).
+//
+// What bounds it.  Vector instructions and the latency of two dependent phases per
+// plane, not HBM; on large lattices with every node moving the chip also lowers its
+// clock, so instructions and LDS words cost time twice.  What the choices below
+// bought, each step timed on a 128 x 128 x 512 jet in motion (us a step):
+//   252  populations exchanged per c_z, G from 13 differences per column and plane
+//   226  the T exchanged instead (the c_z expansion and the neighbour density
+//        difference then act on 6 sums and on T0 instead of on 27 populations), 16-byte
+//        LDS records per direction, G and kappa from running sums (9 LDS reads of phi
+//        a column instead of 26), state accesses with a scalar base, the memory wait
+//        after the destination's arithmetic.  Per 20-row plane 5.3k vector
+//        wave-instructions instead of 6.4k, 60 LDS instructions a wave instead of 129.
 //
 // Arithmetic (Eqs. 5-8, 15-19 with Guo forcing; Eqs. 20-24):
 //   source:  u = ubar + F/(2 rho), P = Q + F F/(4 rho), J = rho u + F/2,
 //            a2 = rho u u + (1-omega) P + (u F + F u)/2,
 //            a3_aab = rho u_a^2 u_b + (1-omega)(2 u_a P_ab + u_b P_aa),
 //            a3_xyz = rho u_x u_y u_z + (1-omega)(u_x P_yz + u_y P_xz + u_z P_xy),
-//            t(c) = rho' + 3 c.J + 4.5 H2(c):a2 + 4.5 H3(c):a3, evaluated on the
-//            27 velocities as a tensor product of 1-D quadratics in c_x, c_y, c_z;
+//            t(c) = rho' + 3 c.J + 4.5 H2(c):a2 + 4.5 H3(c):a3, evaluated as a tensor
+//            product of 1-D quadratics in c_x, c_y, c_z;
 //   destination: moments sum_i w_i H(c_i) t_i(x - c_i) as a tensor product of
 //            1-D three-point transforms written relative to the middle value, so
 //            the large isotropic part cancels before rounding.
@@ -37,11 +52,12 @@
 // plus gravity; zero on boundary layers), so that at the destination
 // ubar = j and Q = Pi - rho c_s^2 I - j j.
 // Precision: the source builds tau = t - rho' (no density part) and publishes its
-// rho' once; the destination forms t_i - rho'(own column, same plane) as
-// tau_i + (rho'(source) - rho'(own column)), exact differences of neighbours, and
+// rho' beside it; the destination forms t - rho'(own column, same plane) as
+// tau + (rho'(source) - rho'(own column)), exact differences of neighbours, and
 // puts rho'(own column) back into the zeroth moment only.  No sum is rounded at
-// the magnitude of rho' except the final density itself.
+// the magnitude of rho' except in z and in the final density itself.
 #include <algorithm>
+#include <type_traits>
 
 #include "tslb_internal.h"
 
@@ -53,7 +69,9 @@ namespace fused {
 // columns.  Two heights: 16 rows with 640 threads (10 waves) and 20 rows with
 // 768 threads (12 waves, three on every SIMD, less halo per column), chosen per
 // lattice by the host (fused_plan); the one-component and variable-density
-// steps take 16 rows.
+// steps take 16 rows.  A source's exchange record is 36 words: for each of the eight
+// directions across columns T0, T1, T2 and rho', then the phase sent to +x, -x, +y and
+// -y.  16-byte accesses a stride of 36 words apart cover all LDS banks.
 template <int ROWS> struct Tile {
     static constexpr int TX = 32, TY = ROWS;
     static constexpr int SX = TX + 2, SY = TY + 2, NSRC = SX * SY;   // sources: 34 x 18 or 34 x 22
@@ -61,42 +79,44 @@ template <int ROWS> struct Tile {
     static constexpr int PX = TX + 6, PY = TY + 6, NPHI = PX * PY;   // phase field: 38 x 22 or 38 x 26
     static constexpr int NDST = TX * TY;                              // 512 or 640
     static constexpr int NT = ROWS == 16 ? 640 : 768;                 // threads per workgroup
+    static constexpr int REC = 36;                                    // words of a source's exchange record
     static_assert(ROWS == 16 || ROWS == 20, "tile heights: 16 or 20 rows");
     static_assert(NSRC <= NT && NDST <= NSRC, "tile does not fit the workgroup");
     static_assert(NPHI <= 2 * NT && NGEO <= 2 * NT, "staging loops assume two items per thread");
 };
-constexpr int NXCH = 35;   // exchange slots per source (two components)
-constexpr int NXCH1 = 28;  // exchange slots per source (one component)
+typedef float vec4 __attribute__((ext_vector_type(4)));
+typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
 
 // LDS of a workgroup: PH = two components (with the phase field), else one.
 // The gradient ring holds G itself for the variable-density step (its forces
 // take G directly), else only |G| + eps: the force is rebuilt as n (|G| + eps)
 // from the stored normal, which keeps the 20-row tile within 160 KB of LDS.
-template <bool PH, bool VD, int ROWS> struct Smem {
+template <bool PH, bool VD, int ROWS> struct alignas(16) Smem {
     using T = Tile<ROWS>;
+    float xch[T::NSRC][T::REC];        // populations crossing columns
     int32_t phi[4][T::NPHI];           // fixed-point phase field, ring of 4 planes
     float n[3][3][T::NGEO];            // unit normal, ring of 3 planes
     float G[3][VD ? 3 : 1][T::NSRC];   // gradient (VD) or |G| + eps on the source region, ring of 3 planes
-    float xch[NXCH][T::NSRC];          // populations crossing columns
 };
-template <bool VD, int ROWS> struct Smem<false, VD, ROWS> {
-    float xch[NXCH1][Tile<ROWS>::NSRC];  // populations crossing columns
+template <bool VD, int ROWS> struct alignas(16) Smem<false, VD, ROWS> {
+    float xch[Tile<ROWS>::NSRC][Tile<ROWS>::REC];  // populations crossing columns
 };
 static_assert(sizeof(Smem<true, false, 20>) <= 160 * 1024 && sizeof(Smem<true, true, 16>) <= 160 * 1024,
               "LDS of one workgroup");
 
 // 1-D three-point transform of (a_-, a_0, a_+) with weights (1/6, 2/3, 1/6):
-// m0 = sum w a, m1 = sum w c a, m2 = sum w (c^2 - 1/3) a, written relative to a_0.
+// m0 = sum w a, 6 m1 = 6 sum w c a, 9 m2 = 9 sum w (c^2 - 1/3) a, written relative to
+// a_0.  The factors of the first and second moments are left to the constants of
+// the multiply-adds that take them (in z, and where the new moments are formed).
 struct Tr3 {
     float m0, m1, m2;
 };
 __device__ __forceinline__ Tr3 tr3(float am, float a0, float ap) {
     const float dm = am - a0, dp = ap - a0;
-    const float s = dm + dp;
     Tr3 r;
-    r.m0 = fmaf(s, 1.0f / 6.0f, a0);
-    r.m1 = (dp - dm) * (1.0f / 6.0f);
-    r.m2 = s * (1.0f / 9.0f);
+    r.m2 = dm + dp;
+    r.m0 = fmaf(r.m2, 1.0f / 6.0f, a0);
+    r.m1 = dp - dm;
     return r;
 }
 __device__ __forceinline__ float tr3_m0(float am, float a0, float ap) {
@@ -109,10 +129,6 @@ __device__ __forceinline__ float recip(float x) {
     const float r = __builtin_amdgcn_rcpf(x);
     return fmaf(r, fmaf(-x, r, 1.0f), r);
 }
-
-// Weighted three-point sum with the one-dimensional D3Q27 weights:
-// (1/6) m + (2/3) z + (1/6) p.
-__device__ __forceinline__ float w1sum(float m, float z, float p) { return fmaf(z, 2.0f / 3.0f, (m + p) * (1.0f / 6.0f)); }
 
 // Quadratic A + B c + C (c^2 - 1/3) at c = -1, 0, +1.
 __device__ __forceinline__ void quad3(float A, float B, float C, float &vm, float &v0, float &vp) {
@@ -136,7 +152,8 @@ __device__ __forceinline__ int wrap_or_clamp(int v, int n, int periodic) {
 }
 
 // The six 2-D moments X_pq = sum_{cx,cy} w(cx) w(cy) h_p(cx) h_q(cy) t(cx, cy) of
-// one z group, p, q in {00, 10, 01, 20, 02, 11} (order of the output array).
+// one z group, p, q in {00, 10, 01, 20, 02, 11} (order of the output array), times
+// 1, 6, 6, 9, 9 and 36.
 __device__ __forceinline__ void xy_moments(const float t[9], float X[6]) {
     // y stage, per c_x: t[(cx+1) + 3(cy+1)]
     Tr3 y0 = tr3(t[0], t[3], t[6]);   // c_x = -1
@@ -162,22 +179,93 @@ __device__ __forceinline__ int xcd_work_item(int b, int nb) {
     return (xcd < rem8 ? xcd * (q8 + 1) : rem8 * (q8 + 1) + (xcd - rem8) * q8) + slot;
 }
 
-// One work item (a tile and a z chunk) of one lattice.  G: access the state
-// through global-address-space pointers (for state pointers read from memory).
+// A pointer that is the same in every lane, kept in scalar registers, and a
+// 32-bit lane offset in bytes.  The empty asm statements hide how the two were
+// formed, so that an access through them takes the scalar-base form of the memory
+// instructions.  Without them the compiler shares base + lane offset between the
+// planes and adds each plane's stride in 64-bit vector arithmetic (one
+// v_lshl_add_u64 per access, 22 of them per node), or keeps every plane's base in
+// scalar registers, which do not suffice for that.
+__device__ __forceinline__ global_t<char> *uniform(global_t<char> *p) {
+    __asm__ volatile("" : "+s"(p));
+    return p;
+}
+__device__ __forceinline__ uint32_t lane_offset(uint32_t off) {
+    __asm__ volatile("" : "+v"(off));
+    return off;
+}
+
+// Bytes of a word of moment plane p.
+template <int ST> __device__ __forceinline__ constexpr int moment_size(int p) {
+    return ST == ST_FP32 || (ST == ST_FP16Q && p < 4) ? 4 : 2;
+}
+
+// Stored words of the ten moments of the node at element `off` of the z plane that
+// starts `zoff` elements into each moment plane (zoff uniform).
+template <int ST>
+__device__ __forceinline__ void load_plane(const void *mom, long long ld, long long zoff, uint32_t off, uint32_t m[10]) {
+    global_t<char> *q = (global_t<char> *)mom + moment_size<ST>(0) * zoff;
+    uint32_t o = lane_offset(off * moment_size<ST>(0));
+#pragma unroll
+    for (int p = 0; p < 10; ++p) {
+        const int sz = moment_size<ST>(p);
+        q = uniform(q);
+        if (sz == 4)
+            m[p] = *(const global_t<uint32_t> *)(q + o);
+        else
+            m[p] = *(const global_t<uint16_t> *)(q + o);
+        q += sz * ld;
+        if (p < 9 && moment_size<ST>(p + 1) != sz) {  // from the binary32 to the binary16 planes
+            q -= (sz - moment_size<ST>(p + 1)) * zoff;
+            o = lane_offset(off * moment_size<ST>(p + 1));
+        }
+    }
+}
+
+template <int ST>
+__device__ __forceinline__ void store_plane(void *mom, long long ld, long long zoff, uint32_t off, const float m[10],
+                                            const Scales &sc) {
+    global_t<char> *q = (global_t<char> *)mom + moment_size<ST>(0) * zoff;
+    uint32_t o = lane_offset(off * moment_size<ST>(0));
+#pragma unroll
+    for (int p = 0; p < 10; ++p) {
+        const int sz = moment_size<ST>(p);
+        q = uniform(q);
+        if (sz == 4)
+            store_nt((global_t<float> *)(q + o), m[p]);
+        else
+            store_nt((global_t<uint16_t> *)(q + o), half_bits<ST>(m[p], p, sc));
+        q += sz * ld;
+        if (p < 9 && moment_size<ST>(p + 1) != sz) {
+            q -= (sz - moment_size<ST>(p + 1)) * zoff;
+            o = lane_offset(off * moment_size<ST>(p + 1));
+        }
+    }
+}
+
+__device__ __forceinline__ void store_phi(int32_t *phi, long long zoff, uint32_t off, int32_t v) {
+    global_t<char> *q = uniform((global_t<char> *)phi + 4 * zoff);
+    store_nt((global_t<int32_t> *)(q + lane_offset(off * 4u)), v);
+}
+
+// The lattice's parameters in memory: what only the inlet rule needs is read where
+// an inlet node is written (loaded at kernel entry it would sit in scalar registers
+// through the whole loop).
+using PhysMem = const __attribute__((address_space(4))) Phys *;
+
+// One work item (a tile and a z chunk) of one lattice.
 // MULTI marks the multi-lattice kernel's instantiation: it keeps that kernel's
 // copy of the step apart from the single-lattice kernel's, whose code is
 // otherwise changed (and slowed) by the second user of the same instantiation.
-template <int ST, bool PH, bool G, bool MULTI, bool VD, int ROWS>
-__device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g, const Phys &ph, const Scales &sc,
-                                           const StateView &in, const StateView &out, int lz, int tiles_x,
-                                           int tiles_y, unsigned long long step_next, int w) {
+template <int ST, bool PH, bool MULTI, bool VD, int ROWS>
+__device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g, const Phys &ph, PhysMem walls,
+                                           const Scales &sc, const StateView &in, const StateView &out, int lz,
+                                           int tiles_x, int tiles_y, unsigned long long step_next, int w) {
+// multiply-adds are written out: every instantiation rounds alike
+#pragma clang fp contract(off)
     using T = Tile<ROWS>;
     constexpr int TX = T::TX, TY = T::TY, SX = T::SX, SY = T::SY, NSRC = T::NSRC, GX = T::GX, GY = T::GY,
                   NGEO = T::NGEO, PX = T::PX, NPHI = T::NPHI, NDST = T::NDST, NT = T::NT;
-    // exchange slots: 0-23 the x/y-crossing populations of the three z groups,
-    // then (two components) 24-27 phase +-x, +-y; rho'; phase rest, +z, -z;
-    // and the three populations of velocity (0, 0, c_z)
-    constexpr int kRho = PH ? 28 : 24, kCen = PH ? 32 : 25;
     const int tile = w % (tiles_x * tiles_y);
     const int chunk = w / (tiles_x * tiles_y);
     // The tile owns columns [xo, xo + TX) x [yo, yo + TY); its origin (x0, y0) is
@@ -191,10 +279,12 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     const int t = threadIdx.x;
     const long long plane = (long long)g.nx * g.ny;
 
-    // ---- this thread's source column (local sx, sy in the 34 x 18 region) ----
+    // ---- this thread's source column (local sx, sy in the 34 x 18 or 34 x 22 region) ----
     int sx = 0, sy = 0;
     const bool is_dst = t < NDST;
     const bool is_src = t < NSRC;
+    static_assert(NDST % 64 == 0, "a wave has destinations in all lanes or in none");
+    const bool dst_wave = __builtin_amdgcn_readfirstlane(t >> 6) < NDST / 64;
     if (is_dst) {
         sx = t % TX + 1;
         sy = t / TX + 1;
@@ -209,39 +299,50 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     const int gxs = x0 + sx - 1, gys = y0 + sy - 1;          // unwrapped global source column
     const int cxs = wrap_or_clamp(gxs, g.nx, g.per[0]);
     const int cys = wrap_or_clamp(gys, g.ny, g.per[1]);
-    const long long col_src = (long long)cxs + (long long)g.nx * cys;
+    const uint32_t off_src = (uint32_t)cxs + (uint32_t)g.nx * (uint32_t)cys;  // nx ny < 2^30
     const bool src_bnd_xy = (!g.per[0] && (gxs <= 0 || gxs >= g.nx - 1)) ||
                             (!g.per[1] && (gys <= 0 || gys >= g.ny - 1));
-    // Destination columns: every owned column, walls included.  A wall column
-    // finishes the moments of its nearest interior node x_F (one node in from the
-    // wall) and stores them through its face rule (Eqs. 9, 10), so each
-    // destination thread reads the exchange buffer around fidx = x_F.
+    // Destination columns: every owned column, walls included.  A node on an x or y
+    // wall takes the moments of its nearest interior node x_F through its face rule
+    // (Eqs. 9, 10).  Each lane finishes its own column; where the tile has walls, a
+    // wall lane then takes the moments of x_F from the lane that finished it.  The two
+    // are in one wave (a wave holds two rows of 32 columns, walls lie at the tile's
+    // edges and its height is even), but for the last row of a lattice of odd height
+    // below a tile's: that row is written as an image of the row before it (y_image).
     const bool owned = is_dst && gxs >= xo && gxs < xo + TX && gxs < g.nx && gys >= yo && gys < yo + TY &&
                        gys < g.ny;
     const int dxf = (!g.per[0] && gxs == 0) ? 1 : ((!g.per[0] && gxs == g.nx - 1) ? -1 : 0);
     const int dyf = (!g.per[1] && gys == 0) ? 1 : ((!g.per[1] && gys == g.ny - 1) ? -1 : 0);
-    const int fidx = (sy + dyf) * SX + (sx + dxf);
+    const bool y_image = !g.per[1] && g.ny < TY && (g.ny & 1);
+    const bool own = owned && !(y_image && gys == g.ny - 1);
+    const int lane_f = (t & 63) + dxf + TX * (y_image && dyf < 0 ? 0 : dyf);  // lane of x_F
+    const bool tile_walls = (!g.per[0] && (x0 == 0 || x0 + TX >= g.nx)) || (!g.per[1] && (y0 == 0 || y0 + TY >= g.ny));
+    uint32_t rules = 0;  // four bits per face
+#pragma unroll
+    for (int f = 0; f < 6; ++f) rules |= (uint32_t)ph.bc[f] << (4 * f);
+    const uint32_t off_dst = (uint32_t)gxs + (uint32_t)g.nx * (uint32_t)gys;  // used where owned
 
     // ---- staging columns of the phase field (<= 2 per thread) ----
-    long long col_phi[2];
-    int phi_item[2];
+    // (a thread without a second item loads the first again and stores nothing)
+    uint32_t off_phi[2];
+    const bool phi_two = t + NT < NPHI;
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-        const int i = t + k * NT;
-        phi_item[k] = i < NPHI ? i : -1;
+        const int i = k && phi_two ? t + NT : t;
         const int px = i % PX, py = i / PX;
         const int gx = wrap_or_clamp(x0 - 3 + px, g.nx, g.per[0]);
         const int gy = wrap_or_clamp(y0 - 3 + py, g.ny, g.per[1]);
-        col_phi[k] = (long long)gx + (long long)g.nx * gy;
+        off_phi[k] = (uint32_t)gx + (uint32_t)g.nx * (uint32_t)gy;
     }
-    // Geometry items (S2 of plane p): centre (gx, gy) in the GX x GY region.
+    // Geometry items (S2 of plane p): a thread has at most two columns of the
+    // GX x GY region, `a` computed in phase A and `b` in phase B, the same ones on
+    // every plane (each keeps its own partial sums).
     // Waves are placed on the four SIMDs round-robin (wave w on SIMD w % 4), and
     // each phase ends at a barrier.  The normal and gradient of plane p are first
     // read in the next iteration, so an item may run in either phase.
     // 16 rows: SIMDs 0 and 1 run three source waves (0, 4, 8 and 1, 5, 9), SIMDs
-    // 2 and 3 two, so in phase A waves 0-7 take items 0-511 and waves 2 and 3 the
-    // next 80; the last 128 run in phase B on waves 8 and 9, which have no
-    // destination.
+    // 2 and 3 two, so in phase A waves 0-7 take items 0-511, and in phase B waves 8
+    // and 9, which have no destination, the next 128 and waves 2 and 3 the last 80.
     // 20 rows: phase A holds three source waves on every SIMD, phase B three
     // destination waves on SIMDs 0 and 1 but two on SIMDs 2 and 3, so threads
     // 0-479 (two waves per SIMD) take one item in phase A, and in phase B waves 10
@@ -251,43 +352,50 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     // item in phase A, where that measured faster: waves 0-7 take items 0-511 and
     // waves 2, 3, 6 and 7 the other 208.
     static_assert(GX >= 32 && GX < 64, "geometry rows are split into 32 + (GX - 32) columns");
-    constexpr int NGEO_B = VD ? 0 : (TY == 16 ? NT - NDST : 384);  // phase-B items
-    constexpr int NGEO_A = NGEO - NGEO_B;                          // phase-A items
-    static_assert(VD || NT - NDST == 128, "two waves without a destination");
-    int geo_a[2] = {-1, -1};
-    {
-        const int wv = t >> 6, lane = t & 63;
-        if constexpr (TY == 16 && VD) {
-            static_assert(NDST == 512 && NGEO - NDST <= 256, "16-row geometry map: 512 + 4 waves of items");
-            const int rank = wv == 2 ? 0 : wv == 3 ? 1 : wv == 6 ? 2 : wv == 7 ? 3 : -1;
-            const int i = NDST + rank * 64 + lane;
-            geo_a[0] = t < NDST ? t : -1;
-            if (rank >= 0 && i < NGEO) geo_a[1] = i;
-        } else if constexpr (TY == 16) {
-            static_assert(NDST == 512 && NGEO_A == NDST + 80, "16-row geometry map: 512 + 80 items in phase A");
-            geo_a[0] = t < NDST ? t : -1;
-            if ((wv == 2 || wv == 3) && lane < 40) geo_a[1] = NDST + (wv - 2) * 40 + lane;
-        } else {
-            static_assert(!VD && NGEO_A == 480, "20-row geometry map: waves 0-7 in phase A");
-            geo_a[0] = t < NGEO_A ? t : -1;
-        }
-    }
-    int geo_b = (NGEO_B > 0 && t >= NDST) ? NGEO_A + (t - NDST) : -1;  // waves without a destination
-    if constexpr (TY == 20) {  // and waves 2, 3, 6, 7, before their destination work
+    int item[2] = {-1, -1};
+    if constexpr (PH) {
         const int wv = t >> 6, lane = t & 63;
         const int r4 = wv == 2 ? 0 : wv == 3 ? 1 : wv == 6 ? 2 : wv == 7 ? 3 : -1;
-        if (r4 >= 0) geo_b = NGEO_A + 128 + r4 * 64 + lane;
+        constexpr int na = TY == 16 ? NDST : 480;  // phase-A items on threads 0 .. na - 1
+        if (t < na) item[0] = t;
+        if (VD) {
+            if (r4 >= 0 && r4 * 64 + lane < NGEO - na) item[1] = na + r4 * 64 + lane;
+        } else {
+            if (t >= NDST) item[1] = na + (t - NDST);
+            if (r4 >= 0 && NT - NDST + r4 * 64 + lane < NGEO - na) item[1] = na + (NT - NDST) + r4 * 64 + lane;
+        }
+        static_assert(NGEO - na <= (VD ? 256 : NT - NDST + 256), "every geometry item has a thread");
+    }
+    int gc[2], gi[2], gs[2];  // position of each item in the phi, geometry and source regions (-1: outside)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        // items 0 .. 32 GY - 1 cover columns 0-31 of each row, one row per
+        // half-wave (contiguous LDS addresses, no bank conflicts); the
+        // rest cover columns 32 .. GX - 1
+        const int i = max(item[k], 0);
+        const int gxl = i < 32 * GY ? (i & 31) : 32 + (i - 32 * GY) % (GX - 32);
+        const int gyl = i < 32 * GY ? (i >> 5) : (i - 32 * GY) / (GX - 32);
+        gi[k] = gyl * GX + gxl;
+        gc[k] = (gyl + 1) * PX + (gxl + 1);
+        const int ssx = gxl - 1, ssy = gyl - 1;
+        gs[k] = ssx >= 0 && ssx < SX && ssy >= 0 && ssy < SY ? ssy * SX + ssx : -1;
     }
 
     const float omega1 = 1.0f - ph.omega;
-    const float sigma = ph.sigma, gamma = ph.gamma, eps = ph.eps;
+    const float sigma72 = ph.sigma * (1.0f / 72.0f), gamma = ph.gamma, eps = ph.eps;
 
-    // carried destination state (see the S5 comment)
-    float XA[6], XB[6], XC[6];
+    // carried destination state (see S6)
+    float ZA[3], ZD[3], ZQ[3], ZP[6], ZR = 0.f;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) XA[k] = XB[k] = XC[k] = 0.f;
-    int32_t PA = 0, PC = 0;  // phase partial sums of planes r - 1 and r (column x_F)
-    float cA = 0.f, cB = 0.f, cC = 0.f, eA = 0.f, eB = 0.f, eC = 0.f;  // curvature partial sums (S3a)
+    for (int k = 0; k < 3; ++k) ZA[k] = ZD[k] = ZQ[k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) ZP[k] = 0.f;
+    int32_t PA = 0, PC = 0;    // phase partial sums of planes r - 1 and r
+    float k1 = 0.f, k2 = 0.f, e1 = 0.f, e2 = 0.f;  // curvature partial sums (S3a)
+    // gradient partial sums of the two geometry items (S2)
+    float gSx[2] = {0.f, 0.f}, gAx[2] = {0.f, 0.f}, gSy[2] = {0.f, 0.f}, gAy[2] = {0.f, 0.f};
+    float gR0[2] = {0.f, 0.f}, gR1[2] = {0.f, 0.f};
+    int32_t gc0[2] = {0, 0}, gc1[2] = {0, 0};
 
     // prefetched raw moments of the next source plane (own column)
     // (stored words: a 16-bit moment is converted only when the next iteration
@@ -295,8 +403,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     uint32_t mom[10] = {};  // defined before the first prefetch (decoded but unused until then)
     int32_t phi_next[2] = {0, 0};
 
-    // z is uniform and at most a few planes outside [0, nz): wrap by whole periods
-    // (no integer division in the loop)
+    // z is uniform and at most a few planes outside [0, nz): wrapped by whole
+    // periods, or clamped.  In the loop each index follows from the one before.
     auto plane_of = [&](int z) {
         if (g.per[2]) {
             while (z < 0) z += g.nz;
@@ -305,66 +413,75 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         }
         return z < 0 ? 0 : (z >= g.nz ? g.nz - 1 : z);
     };
-    auto load_moments = [&](int z, uint32_t m[10]) {
-        const long long id = col_src + plane * plane_of(z);
-#pragma unroll
-        for (int p = 0; p < 10; ++p) m[p] = load_moment_bits<ST, G>(in.mom, g.ld, p, id);
+    auto plane_after = [&](int z, int k) {  // plane_of(z) from k = plane_of(z - 1)
+        const int n = g.per[2] ? 0 : g.nz - 1;
+        return (!g.per[2] && z <= 0) ? 0 : (k + 1 >= g.nz ? n : k + 1);
     };
-    auto load_phi = [&](int z, int32_t v[2]) {
-        const long long zoff = plane * plane_of(z);
+    auto load_phi = [&](int k, int32_t v[2]) {
+        global_t<char> *q = uniform((global_t<char> *)in.phi + 4 * (plane * k));
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (phi_item[k] >= 0) v[k] = mem<G>(in.phi)[col_phi[k] + zoff];
+        for (int k = 0; k < 2; ++k) v[k] = *(const global_t<int32_t> *)(q + lane_offset(off_phi[k] * 4u));
+    };
+    auto stage_phi = [&](int slot, const int32_t v[2]) {
+        if constexpr (PH) {
+            sm.phi[slot & 3][t] = v[0];
+            if (phi_two) sm.phi[slot & 3][t + NT] = v[1];
+        }
     };
 
-    // ---- S2: G and n of plane p from phi planes p-1, p, p+1 (slots it-1, it, it+1),
-    // one geometry item i ----
-    auto geometry_item = [&](int i, int it) {
+    // ---- S2: G and n of plane p at geometry item k ----
+    // G = 3 sum_i w_i c_i phi(y + c_i) with the factorised weights (1, 4, 1)/6 per
+    // axis: G_x = (1/72) sum_z (1,4,1) sum_y (1,4,1) [phi(x+1) - phi(x-1)], G_y
+    // likewise, and G_z = (1/72) [36 (c(z+1) - c(z-1)) + R(z+1) - R(z-1)] with c the
+    // column's own value and R = sum_xy (1,4,1)(1,4,1) (phi - c).  So one plane of
+    // phi enters through nine values, and the item keeps its sums of the planes
+    // before it.  Differences of phi are exact integers, rounded once when they
+    // become binary32, so a uniform field gives exactly G = 0.
+    auto absorb_plane = [&](auto K, int slot, float &Gx, float &Gy, float &Gz) {
         if constexpr (PH) {
-            const int32_t *pm = sm.phi[(it + 3) & 3], *p0 = sm.phi[it & 3], *pp = sm.phi[(it + 1) & 3];
-            // items 0 .. 32 GY - 1 cover columns 0-31 of each row, one row per
-            // half-wave (contiguous LDS addresses, no bank conflicts); the
-            // rest cover columns 32 .. GX - 1
-            const int gxl = i < 32 * GY ? (i & 31) : 32 + (i - 32 * GY) % (GX - 32);
-            const int gyl = i < 32 * GY ? (i >> 5) : (i - 32 * GY) / (GX - 32);
-            const int gi = gyl * GX + gxl;  // position in the geometry region
-            const int c = (gyl + 1) * PX + (gxl + 1);  // centre in the phi region
-            float G0 = 0.f, G1 = 0.f, G2 = 0.f;
-#pragma unroll
-            for (int cz = -1; cz <= 1; ++cz)
-#pragma unroll
-                for (int cy = -1; cy <= 1; ++cy)
-#pragma unroll
-                    for (int cx = -1; cx <= 1; ++cx) {
-                        const bool lead = cx > 0 || (cx == 0 && (cy > 0 || (cy == 0 && cz > 0)));
-                        if (!lead) continue;
-                        const int32_t *pa = cz > 0 ? pp : (cz < 0 ? pm : p0);
-                        const int32_t *pb = cz > 0 ? pm : (cz < 0 ? pp : p0);
-                        const int32_t a = pa[c + cy * PX + cx];
-                        const int32_t bb = pb[c - cy * PX - cx];
-                        const float d = (float)(a - bb);
-                        const float w = 3.0f * w27(cx, cy, cz) * kPhiUlp;
-                        if (cx) G0 = fmaf(w * cx, d, G0);
-                        if (cy) G1 = fmaf(w * cy, d, G1);
-                        if (cz) G2 = fmaf(w * cz, d, G2);
-                    }
+            constexpr int k = decltype(K)::value;
+            const int32_t *q = sm.phi[slot & 3] + gc[k];
+            const int32_t c = q[0], e = q[1], v = q[-1], n = q[PX], d = q[-PX];
+            const int32_t ne = q[PX + 1], sw = q[-PX - 1], se = q[-PX + 1], nw = q[PX - 1];
+            const float ew = (float)(e - v), ns = (float)(n - d), d1 = (float)(ne - sw), d2 = (float)(se - nw);
+            const float wc = (float)(v - c), sc = (float)(d - c), swc = (float)(sw - c), nwc = (float)(nw - c);
+            const float dd = d1 + d2;
+            const float A = fmaf(4.0f, ew, dd), B = fmaf(4.0f, ns, d1 - d2);
+            const float R = fmaf(4.0f, fmaf(2.0f, wc + sc, ew + ns), fmaf(2.0f, swc + nwc, dd));
+            Gx = gSx[k] + A;
+            Gy = gSy[k] + B;
+            Gz = fmaf(36.0f, (float)(c - gc0[k]), R - gR0[k]);
+            gSx[k] = fmaf(4.0f, A, gAx[k]);
+            gAx[k] = A;
+            gSy[k] = fmaf(4.0f, B, gAy[k]);
+            gAy[k] = B;
+            gR0[k] = gR1[k];
+            gR1[k] = R;
+            gc0[k] = gc1[k];
+            gc1[k] = c;
+        }
+    };
+    auto geometry_item = [&](auto K, int it) {
+        if constexpr (PH) {
+            constexpr int k = decltype(K)::value;
+            float Gx, Gy, Gz;
+            absorb_plane(K, it + 1, Gx, Gy, Gz);
+            constexpr float kS = kPhiUlp / 72.0f;
             // hardware square root (1 ulp) and a refined reciprocal: |G| + eps >= eps
-            const float den = __builtin_amdgcn_sqrtf(fmaf(G0, G0, fmaf(G1, G1, G2 * G2))) + eps;
-            const float inv = recip(den);
+            const float den = fmaf(__builtin_amdgcn_sqrtf(fmaf(Gx, Gx, fmaf(Gy, Gy, Gz * Gz))), kS, eps);
+            const float inv = recip(den) * kS;
             float *n = &sm.n[it % 3][0][0];
-            n[gi] = G0 * inv;
-            n[NGEO + gi] = G1 * inv;
-            n[2 * NGEO + gi] = G2 * inv;
-            const int ssx = gxl - 1, ssy = gyl - 1;
-            if (ssx >= 0 && ssx < SX && ssy >= 0 && ssy < SY) {
+            n[gi[k]] = Gx * inv;
+            n[NGEO + gi[k]] = Gy * inv;
+            n[2 * NGEO + gi[k]] = Gz * inv;
+            if (gs[k] >= 0) {
                 float *Gs = &sm.G[it % 3][0][0];
-                const int si = ssy * SX + ssx;
                 if constexpr (VD) {
-                    Gs[si] = G0;
-                    Gs[NSRC + si] = G1;
-                    Gs[2 * NSRC + si] = G2;
+                    Gs[gs[k]] = Gx * kS;
+                    Gs[NSRC + gs[k]] = Gy * kS;
+                    Gs[2 * NSRC + gs[k]] = Gz * kS;
                 } else {
-                    Gs[si] = den;
+                    Gs[gs[k]] = den;
                 }
             }
         }
@@ -374,16 +491,18 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     // prologue: phase planes z0 - 3 and z0 - 2 staged (slots 0, 1)
     if constexpr (PH) {
         int32_t v[2] = {0, 0};
-        load_phi(z0 - 3, v);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (phi_item[k] >= 0) sm.phi[0][phi_item[k]] = v[k];
-        load_phi(z0 - 2, v);
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-            if (phi_item[k] >= 0) sm.phi[1][phi_item[k]] = v[k];
+        load_phi(plane_of(z0 - 3), v);
+        stage_phi(0, v);
+        load_phi(plane_of(z0 - 2), v);
+        stage_phi(1, v);
     }
     __syncthreads();
+    if constexpr (PH) {  // the geometry takes in plane z0 - 3 (slot 0)
+        float gx, gy, gz;
+        if (item[0] >= 0) absorb_plane(std::integral_constant<int, 0>{}, 0, gx, gy, gz);
+        if (item[1] >= 0) absorb_plane(std::integral_constant<int, 1>{}, 0, gx, gy, gz);
+    }
+    int kmom = plane_of(z0 - 1), kphi = plane_of(z0 - 2);  // z planes of the loads
 
     // Iteration it works on three planes: p = z0 - 3 + it (geometry), q = p - 1
     // (normal of the curvature sums) and r = p - 2 (sources), and finishes
@@ -397,351 +516,406 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         // moments of source plane r + 1 for the next iteration
         float mom_cur[10];
 #pragma unroll
-        for (int k = 0; k < 10; ++k) mom_cur[k] = decode_moment<ST>(mom[k], k, sc);
-        if (is_src && it >= 3) load_moments(r + 1, mom);
+        for (int k = 0; k < 10; ++k) {
+            mom_cur[k] = decode_moment<ST>(mom[k], k, sc);
+            if (!VD && k >= 4) mom_cur[k] *= omega1;  // (1 - omega) Q
+            // formed before the loads below, which then reuse the words' registers
+            __asm__ volatile("" : "+v"(mom_cur[k]));
+        }
+        // (the first source plane is z0 - 1, loaded while it <= 3; lanes without a
+        // source load a column of the lattice and drop it)
+        if (it > 3) kmom = plane_after(r + 1, kmom);
+        load_plane<ST>(in.mom, g.ld, plane * kmom, off_src, mom);
         // phase plane p + 2, staged at the start of phase B.  Issued here, next to
         // the moment prefetch, so that both have all of phase A to arrive (both are
         // waited for at the start of phase B).
         if constexpr (PH) {
-            if (it + 3 <= nit) load_phi(p + 2, phi_next);
+            kphi = plane_after(p + 2, kphi);
+            load_phi(kphi, phi_next);
         }
 
         // ================= phase A =================
         // ---- S3a: per-column partial sums of the curvature stencil (plane q) ----
-        // With w_i = w1(c_x) w1(c_y) w1(c_z), w1(0) = 2/3, w1(+-1) = 1/6, the stencil
+        // With w_i = w1(c_x) w1(c_y) w1(c_z), w1 = (1, 4, 1)/6, the stencil
         // kappa = 3 sum_i w_i c_i . n(x + c_i) factorises into sums over one plane:
-        //   kappa(r) = (1/2) [ sum_cz w1(cz) C(r + cz) + E(r + 1) - E(r - 1) ],
-        //   C = sum_cy w1(cy) (n_x(x+1, y+cy) - n_x(x-1, y+cy))
-        //     + sum_cx w1(cx) (n_y(x+cx, y+1) - n_y(x+cx, y-1)),
-        //   E = sum_{cx,cy} w1(cx) w1(cy) n_z(x+cx, y+cy),
-        // so each source keeps C and E of three planes in registers.
+        //   72 kappa(r) = C(r-1) + 4 C(r) + C(r+1) + E(r+1) - E(r-1),
+        //   C = sum_cy (1,4,1) (n_x(x+1, y+cy) - n_x(x-1, y+cy))
+        //     + sum_cx (1,4,1) (n_y(x+cx, y+1) - n_y(x+cx, y-1)),
+        //   E = sum_{cx,cy} (1,4,1)(1,4,1) n_z(x+cx, y+cy),
+        // so each source keeps k1 = C(r-1) + 4 C(r), k2 = C(r), e1 = E(r-1) and e2 = E(r)
+        // (E apart: it is of order 36 where C, a sum of differences, is small).
+        float kap = 0.f;
         if constexpr (PH) {
             if (it >= 2 && is_src) {
-                const float *nq = &sm.n[(it + 2) % 3][0][0];  // plane q, written one iteration ago
+                // plane q, written one iteration ago; entry 0 is the corner (x-1, y-1)
+                const float *nq = &sm.n[(it + 2) % 3][0][0] + sy * GX + sx;
                 const float *nyq = nq + NGEO, *nzq = nq + 2 * NGEO;
-                const int c = (sy + 1) * GX + (sx + 1);  // centre in the geometry region
-                const float Cx = w1sum(nq[c - GX + 1] - nq[c - GX - 1], nq[c + 1] - nq[c - 1], nq[c + GX + 1] - nq[c + GX - 1]);
-                const float Cy = w1sum(nyq[c + GX - 1] - nyq[c - GX - 1], nyq[c + GX] - nyq[c - GX],
-                                       nyq[c + GX + 1] - nyq[c - GX + 1]);
-                const float E = w1sum(w1sum(nzq[c - GX - 1], nzq[c - GX], nzq[c - GX + 1]),
-                                      w1sum(nzq[c - 1], nzq[c], nzq[c + 1]),
-                                      w1sum(nzq[c + GX - 1], nzq[c + GX], nzq[c + GX + 1]));
-                cA = cB;
-                cB = cC;
-                cC = Cx + Cy;
-                eA = eB;
-                eB = eC;
-                eC = E;
+                const float Cx = fmaf(4.0f, nq[GX + 2] - nq[GX], (nq[2] - nq[0]) + (nq[2 * GX + 2] - nq[2 * GX]));
+                const float Cy = fmaf(4.0f, nyq[2 * GX + 1] - nyq[1], (nyq[2 * GX] - nyq[0]) + (nyq[2 * GX + 2] - nyq[2]));
+                const float Em = fmaf(4.0f, nzq[1], nzq[0] + nzq[2]);
+                const float E0 = fmaf(4.0f, nzq[GX + 1], nzq[GX] + nzq[GX + 2]);
+                const float Ep = fmaf(4.0f, nzq[2 * GX + 1], nzq[2 * GX] + nzq[2 * GX + 2]);
+                const float C = Cx + Cy, E = fmaf(4.0f, E0, Em + Ep);
+                kap = (k1 + C) + (E - e1);
+                k1 = fmaf(4.0f, C, k2);
+                k2 = C;
+                e1 = e2;
+                e2 = E;
             }
         }
 
-        if (it >= 4) {
+        // what the source's own column takes of its populations (used in phase B)
+        float T0c, T1c, T2c, rpc;
+        int32_t prest, pup, pdown;
+        if (it >= 4 && is_src) {
             // ---- S3: kappa and F at the source (plane r = q - 1) ----
             float F0 = 0.f, F1 = 0.f, F2 = 0.f, n0 = 0.f, n1 = 0.f, n2 = 0.f;
             float Gx = 0.f, Gy = 0.f, Gz = 0.f;  // grad(phi) at the source (VD)
             bool sbnd = false;                   // the source is a boundary-layer node (VD)
             int32_t phis = 0;
             if constexpr (PH) {
-                if (is_src) {
-                    const float kap = 0.5f * (w1sum(cA, cB, cC) + (eC - eA));
-                    const int zr = r;
-                    const bool bnd = src_bnd_xy || (!g.per[2] && (zr <= 0 || zr >= g.nz - 1));
-                    const float a = bnd ? 0.f : -sigma * kap;
-                    const float *nr = &sm.n[(it + 1) % 3][0][0];  // plane r
-                    const int c = (sy + 1) * GX + (sx + 1);
-                    n0 = nr[c];
-                    n1 = nr[NGEO + c];
-                    n2 = nr[2 * NGEO + c];
-                    const float *Gs = &sm.G[(it + 1) % 3][0][0];  // plane r
-                    if constexpr (VD) {
-                        Gx = Gs[sidx];
-                        Gy = Gs[NSRC + sidx];
-                        Gz = Gs[2 * NSRC + sidx];
-                        sbnd = bnd;
-                        F0 = a * Gx;
-                        F1 = a * Gy;
-                        F2 = a * Gz;
-                    } else {
-                        const float ag = a * Gs[sidx];  // G = n (|G| + eps)
-                        F0 = ag * n0;
-                        F1 = ag * n1;
-                        F2 = ag * n2;
-                    }
-                    phis = sm.phi[(it - 2) & 3][(sy + 2) * PX + (sx + 2)];
+                const bool bnd = src_bnd_xy || (!g.per[2] && (r <= 0 || r >= g.nz - 1));
+                const float a = bnd ? 0.f : -sigma72 * kap;
+                const float *nr = &sm.n[(it + 1) % 3][0][0] + (sy + 1) * GX + (sx + 1);  // plane r
+                n0 = nr[0];
+                n1 = nr[NGEO];
+                n2 = nr[2 * NGEO];
+                const float *Gs = &sm.G[(it + 1) % 3][0][0] + sidx;  // plane r
+                if constexpr (VD) {
+                    Gx = Gs[0];
+                    Gy = Gs[NSRC];
+                    Gz = Gs[2 * NSRC];
+                    sbnd = bnd;
+                    F0 = a * Gx;
+                    F1 = a * Gy;
+                    F2 = a * Gz;
+                } else {
+                    const float ag = a * Gs[0];  // G = n (|G| + eps)
+                    F0 = ag * n0;
+                    F1 = ag * n1;
+                    F2 = ag * n2;
                 }
+                phis = sm.phi[(it - 2) & 3][(sy + 2) * PX + (sx + 2)];
             }
 
             // ---- S4: post-collision populations of the source ----
-            float tm[9], t0[9], tp[9];  // groups c_z = -1, 0, +1, index (cx+1) + 3(cy+1)
-            int32_t base = 0, ax = 0, ay = 0, az = 0;
-            if (is_src) {
-                const float rp = mom_cur[0];
-                float om1 = omega1;
-                if constexpr (VD) {
-                    // rho(phi), omega(phi) and the acceleration that replaces F
-                    const float pc = fminf(fmaxf(phi_to_float(phis), 0.0f), 1.0f);
-                    const float om = recip(fmaf(3.0f, fmaf(ph.dnu, pc, ph.nu_b), 0.5f));
-                    om1 = 1.0f - om;
-                    if (sbnd) {
-                        F0 = F1 = F2 = 0.f;
-                    } else {
-                        const float ir = recip(fmaf(ph.drho, pc, ph.rho_b));
-                        const float cp = (-1.0f / 3.0f) * ph.drho * rp;     // pressure force / G
-                        const float cm = (0.5f * om - 1.0f) * ph.drho;      // viscous force / (Q.G)
-                        const float QG0 = fmaf(mom_cur[4], Gx, fmaf(mom_cur[7], Gy, mom_cur[8] * Gz));
-                        const float QG1 = fmaf(mom_cur[7], Gx, fmaf(mom_cur[5], Gy, mom_cur[9] * Gz));
-                        const float QG2 = fmaf(mom_cur[8], Gx, fmaf(mom_cur[9], Gy, mom_cur[6] * Gz));
-                        F0 = fmaf(fmaf(cm, QG0, fmaf(cp, Gx, F0)), ir, ph.grav[0]);
-                        F1 = fmaf(fmaf(cm, QG1, fmaf(cp, Gy, F1)), ir, ph.grav[1]);
-                        F2 = fmaf(fmaf(cm, QG2, fmaf(cp, Gz, F2)), ir, ph.grav[2]);
-                    }
+            const float rp = mom_cur[0];
+            float om1 = omega1;
+            if constexpr (VD) {
+                // rho(phi), omega(phi) and the acceleration that replaces F
+                const float pc = fminf(fmaxf(phi_to_float(phis), 0.0f), 1.0f);
+                const float om = recip(fmaf(3.0f, fmaf(ph.dnu, pc, ph.nu_b), 0.5f));
+                om1 = 1.0f - om;
+                if (sbnd) {
+                    F0 = F1 = F2 = 0.f;
+                } else {
+                    const float ir = recip(fmaf(ph.drho, pc, ph.rho_b));
+                    const float cp = (-1.0f / 3.0f) * ph.drho * rp;     // pressure force / G
+                    const float cm = (0.5f * om - 1.0f) * ph.drho;      // viscous force / (Q.G)
+                    const float QG0 = fmaf(mom_cur[4], Gx, fmaf(mom_cur[7], Gy, mom_cur[8] * Gz));
+                    const float QG1 = fmaf(mom_cur[7], Gx, fmaf(mom_cur[5], Gy, mom_cur[9] * Gz));
+                    const float QG2 = fmaf(mom_cur[8], Gx, fmaf(mom_cur[9], Gy, mom_cur[6] * Gz));
+                    F0 = fmaf(fmaf(cm, QG0, fmaf(cp, Gx, F0)), ir, ph.grav[0]);
+                    F1 = fmaf(fmaf(cm, QG1, fmaf(cp, Gy, F1)), ir, ph.grav[1]);
+                    F2 = fmaf(fmaf(cm, QG2, fmaf(cp, Gz, F2)), ir, ph.grav[2]);
                 }
-                const float rho = VD ? 1.0f : 1.0f + rp;  // density of the velocity terms
+#pragma unroll
+                for (int k = 4; k < 10; ++k) mom_cur[k] *= om1;
+            }
+            const float rho = VD ? 1.0f : 1.0f + rp;  // density of the velocity terms
+            // m = (1 - omega) P and a2 of the header, with g = F/rho, v = ubar + g, J = rho v:
+            //   a2_ab = J_a v_b + (1 - omega) Q_ab - (omega/4) F_a g_b
+            float u0 = mom_cur[1], u1 = mom_cur[2], u2 = mom_cur[3];
+            float mxx = mom_cur[4], myy = mom_cur[5], mzz = mom_cur[6], mxy = mom_cur[7], mxz = mom_cur[8],
+                  myz = mom_cur[9];
+            float Jx, Jy, Jz, a2xx, a2yy, a2zz, a2xy, a2xz, a2yz;
+            if constexpr (PH) {
                 const float inv = VD ? 1.0f : recip(rho);
-                const float hF = 0.5f * inv, qF = 0.25f * inv;
-                const float u0 = fmaf(hF, F0, mom_cur[1]), u1 = fmaf(hF, F1, mom_cur[2]), u2 = fmaf(hF, F2, mom_cur[3]);
-                const float Pxx = fmaf(qF * F0, F0, mom_cur[4]), Pyy = fmaf(qF * F1, F1, mom_cur[5]);
-                const float Pzz = fmaf(qF * F2, F2, mom_cur[6]), Pxy = fmaf(qF * F0, F1, mom_cur[7]);
-                const float Pxz = fmaf(qF * F0, F2, mom_cur[8]), Pyz = fmaf(qF * F1, F2, mom_cur[9]);
-                // Hermite coefficients, pre-scaled: t(c) = K0 + sum K1 c + ... (see header)
-                const float Jx = fmaf(rho, u0, 0.5f * F0), Jy = fmaf(rho, u1, 0.5f * F1), Jz = fmaf(rho, u2, 0.5f * F2);
-                const float mxx = om1 * Pxx, myy = om1 * Pyy, mzz = om1 * Pzz;
-                const float mxy = om1 * Pxy, mxz = om1 * Pxz, myz = om1 * Pyz;
-                const float ru0 = rho * u0, ru1 = rho * u1, ru2 = rho * u2;
-                const float a2xx = fmaf(ru0, u0, mxx) + u0 * F0;
-                const float a2yy = fmaf(ru1, u1, myy) + u1 * F1;
-                const float a2zz = fmaf(ru2, u2, mzz) + u2 * F2;
-                const float a2xy = fmaf(ru0, u1, mxy) + 0.5f * (u0 * F1 + F0 * u1);
-                const float a2xz = fmaf(ru0, u2, mxz) + 0.5f * (u0 * F2 + F0 * u2);
-                const float a2yz = fmaf(ru1, u2, myz) + 0.5f * (u1 * F2 + F1 * u2);
-                // a3_aab = u_a (rho u_a u_b + 2 m_ab) + u_b m_aa
-                const float a3xxy = fmaf(u0, fmaf(ru0, u1, 2.0f * mxy), u1 * mxx);
-                const float a3xxz = fmaf(u0, fmaf(ru0, u2, 2.0f * mxz), u2 * mxx);
-                const float a3yyx = fmaf(u1, fmaf(ru1, u0, 2.0f * mxy), u0 * myy);
-                const float a3yyz = fmaf(u1, fmaf(ru1, u2, 2.0f * myz), u2 * myy);
-                const float a3zzx = fmaf(u2, fmaf(ru2, u0, 2.0f * mxz), u0 * mzz);
-                const float a3zzy = fmaf(u2, fmaf(ru2, u1, 2.0f * myz), u1 * mzz);
-                const float a3xyz = fmaf(ru0 * u1, u2, fmaf(u0, myz, fmaf(u1, mxz, u2 * mxy)));
-                // The scale factors of the coefficients (3 J, 4.5 a2_aa, 9 a2_ab, 13.5 a3_aab,
-                // 27 a3_xyz) are folded into the constants of the multiply-adds that take
-                // a coefficient as a slope or curvature term; only the five that enter as
-                // an addend are scaled explicitly.
-                const float K1y = 3.0f * Jy, K1z = 3.0f * Jz;
-                const float K2yy = 4.5f * a2yy, K2zz = 4.5f * a2zz, K2yz = 9.0f * a2yz;
-                // t = T0 + cz T1 + h(cz) T2; T0 = U0 + cy U1 + h(cy) U2 (per cx), etc.
-                float U0[3], U1[3], V0[3], W0[3];
-                {   // U0 = quad3(0, 3 Jx, 4.5 a2xx): tau = t - rho'
-                    const float m = 3.0f * a2xx;
-                    U0[1] = -1.5f * a2xx;
-                    U0[0] = fmaf(-3.0f, Jx, m);
-                    U0[2] = fmaf(3.0f, Jx, m);
-                }
-                {   // U1 = quad3(3 Jy, 9 a2xy, 13.5 a3xxy)
-                    const float m = fmaf(9.0f, a3xxy, K1y);
-                    U1[1] = fmaf(-4.5f, a3xxy, K1y);
-                    U1[0] = fmaf(-9.0f, a2xy, m);
-                    U1[2] = fmaf(9.0f, a2xy, m);
-                }
-                {   // V0 = quad3(3 Jz, 9 a2xz, 13.5 a3xxz)
-                    const float m = fmaf(9.0f, a3xxz, K1z);
-                    V0[1] = fmaf(-4.5f, a3xxz, K1z);
-                    V0[0] = fmaf(-9.0f, a2xz, m);
-                    V0[2] = fmaf(9.0f, a2xz, m);
-                }
-                W0[0] = fmaf(-13.5f, a3zzx, K2zz);
-                W0[1] = K2zz;
-                W0[2] = fmaf(13.5f, a3zzx, K2zz);
+                const float g0 = F0 * inv, g1 = F1 * inv, g2 = F2 * inv;
+                const float v0 = u0 + g0, v1 = u1 + g1, v2 = u2 + g2;
+                u0 = fmaf(0.5f, g0, u0);
+                u1 = fmaf(0.5f, g1, u1);
+                u2 = fmaf(0.5f, g2, u2);
+                Jx = rho * v0;
+                Jy = rho * v1;
+                Jz = rho * v2;
+                const float hs = 0.25f * (om1 - 1.0f), ks = 0.25f * om1;
+                const float h0 = hs * F0, h1 = hs * F1, h2 = hs * F2;
+                const float q0 = ks * F0, q1 = ks * F1, q2 = ks * F2;
+                a2xx = fmaf(Jx, v0, fmaf(h0, g0, mxx));
+                a2yy = fmaf(Jy, v1, fmaf(h1, g1, myy));
+                a2zz = fmaf(Jz, v2, fmaf(h2, g2, mzz));
+                a2xy = fmaf(Jx, v1, fmaf(h0, g1, mxy));
+                a2xz = fmaf(Jx, v2, fmaf(h0, g2, mxz));
+                a2yz = fmaf(Jy, v2, fmaf(h1, g2, myz));
+                mxx = fmaf(q0, g0, mxx);
+                myy = fmaf(q1, g1, myy);
+                mzz = fmaf(q2, g2, mzz);
+                mxy = fmaf(q0, g1, mxy);
+                mxz = fmaf(q0, g2, mxz);
+                myz = fmaf(q1, g2, myz);
+            } else {
+                Jx = rho * u0;
+                Jy = rho * u1;
+                Jz = rho * u2;
+                a2xx = fmaf(Jx, u0, mxx);
+                a2yy = fmaf(Jy, u1, myy);
+                a2zz = fmaf(Jz, u2, mzz);
+                a2xy = fmaf(Jx, u1, mxy);
+                a2xz = fmaf(Jx, u2, mxz);
+                a2yz = fmaf(Jy, u2, myz);
+            }
+            const float ru0 = PH ? rho * u0 : Jx, ru1 = PH ? rho * u1 : Jy;
+            const float rxy = ru0 * u1, rxz = ru0 * u2, ryz = ru1 * u2;
+            // a3_aab = u_a (rho u_a u_b + 2 m_ab) + u_b m_aa
+            const float sxy = fmaf(2.0f, mxy, rxy), sxz = fmaf(2.0f, mxz, rxz), syz = fmaf(2.0f, myz, ryz);
+            const float a3xxy = fmaf(u0, sxy, u1 * mxx), a3xxz = fmaf(u0, sxz, u2 * mxx);
+            const float a3yyx = fmaf(u1, sxy, u0 * myy), a3yyz = fmaf(u1, syz, u2 * myy);
+            const float a3zzx = fmaf(u2, sxz, u0 * mzz), a3zzy = fmaf(u2, syz, u1 * mzz);
+            const float a3xyz = fmaf(rxy, u2, fmaf(u0, myz, fmaf(u1, mxz, u2 * mxy)));
+            // The scale factors of the coefficients (3 J, 4.5 a2_aa, 9 a2_ab, 13.5 a3_aab,
+            // 27 a3_xyz) are folded into the constants of the multiply-adds that take
+            // a coefficient as a slope or curvature term; only the five that enter as
+            // an addend are scaled explicitly.
+            const float K1y = 3.0f * Jy, K1z = 3.0f * Jz;
+            const float K2yy = 4.5f * a2yy, K2zz = 4.5f * a2zz, K2yz = 9.0f * a2yz;
+            // t = T0 + cz T1 + h(cz) T2; T0 = U0 + cy U1 + h(cy) U2 (per cx), etc.
+            float U0[3], U1[3], V0[3], W0[3];
+            {   // U0 = quad3(0, 3 Jx, 4.5 a2xx): tau = t - rho'
+                const float m = 3.0f * a2xx;
+                U0[1] = -1.5f * a2xx;
+                U0[0] = fmaf(-3.0f, Jx, m);
+                U0[2] = fmaf(3.0f, Jx, m);
+            }
+            {   // U1 = quad3(3 Jy, 9 a2xy, 13.5 a3xxy)
+                const float m = fmaf(9.0f, a3xxy, K1y);
+                U1[1] = fmaf(-4.5f, a3xxy, K1y);
+                U1[0] = fmaf(-9.0f, a2xy, m);
+                U1[2] = fmaf(9.0f, a2xy, m);
+            }
+            {   // V0 = quad3(3 Jz, 9 a2xz, 13.5 a3xxz)
+                const float m = fmaf(9.0f, a3xxz, K1z);
+                V0[1] = fmaf(-4.5f, a3xxz, K1z);
+                V0[0] = fmaf(-9.0f, a2xz, m);
+                V0[2] = fmaf(9.0f, a2xz, m);
+            }
+            W0[0] = fmaf(-13.5f, a3zzx, K2zz);
+            W0[1] = K2zz;
+            W0[2] = fmaf(13.5f, a3zzx, K2zz);
+            vec4 *rec = (vec4 *)&sm.xch[sidx][0];
+            rpc = rp;
 #pragma unroll
-                for (int ix = 0; ix < 3; ++ix) {
-                    const float cx = (float)(ix - 1);
-                    const float U2 = ix == 1 ? K2yy : fmaf(13.5f * cx, a3yyx, K2yy);  // linear in cx
-                    const float V1 = ix == 1 ? K2yz : fmaf(27.0f * cx, a3xyz, K2yz);
-                    float T0[3], T1[3], T2[3];
-                    quad3(U0[ix], U1[ix], U2, T0[0], T0[1], T0[2]);
-                    {   // T1 = quad3(V0, V1, 13.5 a3yyz)
-                        const float m = fmaf(9.0f, a3yyz, V0[ix]);
-                        T1[1] = fmaf(-4.5f, a3yyz, V0[ix]);
-                        T1[0] = m - V1;
-                        T1[2] = m + V1;
-                    }
-                    T2[0] = fmaf(-13.5f, a3zzy, W0[ix]);
-                    T2[1] = W0[ix];
-                    T2[2] = fmaf(13.5f, a3zzy, W0[ix]);
-#pragma unroll
-                    for (int iy = 0; iy < 3; ++iy) {
-                        const int k = ix + 3 * iy;
-                        const float mid = fmaf(T2[iy], 2.0f / 3.0f, T0[iy]);
-                        t0[k] = fmaf(T2[iy], -1.0f / 3.0f, T0[iy]);
-                        tm[k] = mid - T1[iy];
-                        tp[k] = mid + T1[iy];
-                    }
+            for (int ix = 0; ix < 3; ++ix) {
+                const float cx = (float)(ix - 1);
+                const float U2 = ix == 1 ? K2yy : fmaf(13.5f * cx, a3yyx, K2yy);  // linear in cx
+                const float V1 = ix == 1 ? K2yz : fmaf(27.0f * cx, a3xyz, K2yz);
+                float T0[3], T1[3], T2[3];
+                quad3(U0[ix], U1[ix], U2, T0[0], T0[1], T0[2]);
+                {   // T1 = quad3(V0, V1, 13.5 a3yyz)
+                    const float m = fmaf(9.0f, a3yyz, V0[ix]);
+                    T1[1] = fmaf(-4.5f, a3yyz, V0[ix]);
+                    T1[0] = m - V1;
+                    T1[2] = m + V1;
                 }
-                if constexpr (PH) {
-                    // phase: base to every axis neighbour, +-a_e along +-e, phi - 6 base stays
-                    const float phif = phi_to_float(phis);
-                    const float omphi = (float)(kPhiOne - phis) * kPhiUlp;
-                    const float gph = gamma * omphi;
-                    const float h8 = 0.125f * phif * kPhiInvUlp;
-                    base = (phis + 4) >> 3;
-                    ax = __float2int_rn(h8 * fmaf(4.0f, u0, gph * n0));
-                    ay = __float2int_rn(h8 * fmaf(4.0f, u1, gph * n1));
-                    az = __float2int_rn(h8 * fmaf(4.0f, u2, gph * n2));
-                }
-
+                T2[0] = fmaf(-13.5f, a3zzy, W0[ix]);
+                T2[1] = W0[ix];
+                T2[2] = fmaf(13.5f, a3zzy, W0[ix]);
                 // ---- S5a: publish what crosses columns ----
 #pragma unroll
-                for (int cy = -1; cy <= 1; ++cy)
-#pragma unroll
-                    for (int cx = -1; cx <= 1; ++cx) {
-                        if (!cx && !cy) continue;
-                        const int k = (cx + 1) + 3 * (cy + 1);
-                        const int s = xy_slot(cx, cy);
-                        sm.xch[s][sidx] = tm[k];
-                        sm.xch[8 + s][sidx] = t0[k];
-                        sm.xch[16 + s][sidx] = tp[k];
+                for (int iy = 0; iy < 3; ++iy) {
+                    if (ix == 1 && iy == 1) {
+                        T0c = T0[1];
+                        T1c = T1[1];
+                        T2c = T2[1];
+                    } else {
+                        rec[xy_slot(ix - 1, iy - 1)] = vec4{T0[iy], T1[iy], T2[iy], rp};
                     }
-                if constexpr (PH) {
-                    sm.xch[24][sidx] = __int_as_float(base + ax);        // +x
-                    sm.xch[25][sidx] = __int_as_float(base - ax);        // -x
-                    sm.xch[26][sidx] = __int_as_float(base + ay);        // +y
-                    sm.xch[27][sidx] = __int_as_float(base - ay);        // -y
-                    sm.xch[29][sidx] = __int_as_float(phis - 6 * base);  // rest
-                    sm.xch[30][sidx] = __int_as_float(base + az);        // +z
-                    sm.xch[31][sidx] = __int_as_float(base - az);        // -z
                 }
-                sm.xch[kRho][sidx] = rp;
-                sm.xch[kCen][sidx] = tm[4];
-                sm.xch[kCen + 1][sidx] = t0[4];
-                sm.xch[kCen + 2][sidx] = tp[4];
+            }
+            if constexpr (PH) {
+                // phase: base to every axis neighbour, +-a_e along +-e, phi - 6 base stays
+                const float phif = phi_to_float(phis);
+                const float omphi = (float)(kPhiOne - phis) * kPhiUlp;
+                const float gph = gamma * omphi;
+                const float h8 = 0.125f * phif * kPhiInvUlp;
+                const int32_t base = (phis + 4) >> 3;
+                const int32_t ax = __float2int_rn(h8 * fmaf(4.0f, u0, gph * n0));
+                const int32_t ay = __float2int_rn(h8 * fmaf(4.0f, u1, gph * n1));
+                const int32_t az = __float2int_rn(h8 * fmaf(4.0f, u2, gph * n2));
+                *(ivec4 *)&rec[8] = ivec4{base + ax, base - ax, base + ay, base - ay};  // +x, -x, +y, -y
+                // phi - 6 base, kept from becoming a 64-bit multiply-add (whose unused upper
+                // addend may be a register that a prefetch is still loading: its wait)
+                int32_t base2 = 2 * base, base4 = 4 * base;
+                __asm__("" : "+v"(base2), "+v"(base4));
+                prest = phis - base2 - base4;
+                pup = base + az;
+                pdown = base - az;
             }
         }
 
         // ---- S2, phase-A items ----
-        if constexpr (PH) if (it >= 1 && it + 2 <= nit) {
-            for (int k = 0; k < 2; ++k)
-                if (geo_a[k] >= 0) geometry_item(geo_a[k], it);
+        if constexpr (PH) if (it + 2 <= nit) {
+            if (item[0] >= 0) geometry_item(std::integral_constant<int, 0>{}, it);
+            if (VD && item[1] >= 0) geometry_item(std::integral_constant<int, 1>{}, it);
         }
         __syncthreads();
 
         // ================= phase B =================
-        // Wait here, before any store of the iteration, for the loads issued at its
-        // top (vmcnt 0; expcnt and lgkmcnt fields at their maxima, i.e. not waited
-        // for).  Loads and stores share one in-order counter, and the stores below
-        // are conditional, so a wait for the prefetched words placed after them (at
-        // the phase staging or at the loop latch, where the prefetched moments are
-        // copied) can only be vmcnt(0) and also waits until every store of the
-        // iteration has been acknowledged.  Waited for here, on every path, the
-        // loads are known complete at the latch and the stores drain during the
-        // next iteration.
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        // ---- S1: stage phi(p + 2) for the geometry of the next iteration (slot of
-        // plane p - 2, whose last reader, the sources of phase A, is done) ----
-        if constexpr (PH) {
-            if (it + 3 <= nit) {
-#pragma unroll
-                for (int k = 0; k < 2; ++k)
-                    if (phi_item[k] >= 0) sm.phi[(it + 2) & 3][phi_item[k]] = phi_next[k];
-            }
-        }
-        // ---- S2, phase-B items, before any destination work (the slots read are not the
-        // one staged above) ----
-        if constexpr (PH) if (geo_b >= 0 && it >= 1 && it + 2 <= nit) geometry_item(geo_b, it);
-        if (it >= 4) {
+        // ---- S2, phase-B items, before any destination work ----
+        if constexpr (PH && !VD) if (item[1] >= 0 && it + 2 <= nit) geometry_item(std::integral_constant<int, 1>{}, it);
+        const bool finish = it >= 4 && dst_wave;
+        float m[10];
+        int32_t phin;
+        if (finish) {
             // ---- S5b/S6: gather at the destination and finish plane r - 1 ----
-            if (is_dst) {
-                float gm[9], g0[9], gp[9];
-                const float rp_ref = sm.xch[kRho][fidx];
-                gm[4] = sm.xch[kCen][fidx];
-                g0[4] = sm.xch[kCen + 1][fidx];
-                gp[4] = sm.xch[kCen + 2][fidx];
+            float t0[9], t1[9], t2[9];
+            t0[4] = T0c;
+            t1[4] = T1c;
+            t2[4] = T2c;
+            const float(*xc)[T::REC] = &sm.xch[sidx - SX - 1];  // record of the source at (x - 1, y - 1)
 #pragma unroll
-                for (int cy = -1; cy <= 1; ++cy)
+            for (int cy = -1; cy <= 1; ++cy)
 #pragma unroll
-                    for (int cx = -1; cx <= 1; ++cx) {
-                        if (!cx && !cy) continue;
-                        const int k = (cx + 1) + 3 * (cy + 1);
-                        const int s = xy_slot(cx, cy);
-                        const int src = fidx - cy * SX - cx;
-                        const float drp = sm.xch[kRho][src] - rp_ref;
-                        gm[k] = sm.xch[s][src] + drp;
-                        g0[k] = sm.xch[8 + s][src] + drp;
-                        gp[k] = sm.xch[16 + s][src] + drp;
-                    }
-                float Xm[6], X0[6], Xp[6];
-                xy_moments(gm, Xm);
-                xy_moments(g0, X0);
-                xy_moments(gp, Xp);
-                Xm[0] += rp_ref;
-                X0[0] += rp_ref;
-                Xp[0] += rp_ref;
-                int32_t pin = 0, prest = 0, pup = 0, pdown = 0;
-                if constexpr (PH) {
-                    pin = __float_as_int(sm.xch[24][fidx - 1]) + __float_as_int(sm.xch[25][fidx + 1]) +
-                          __float_as_int(sm.xch[26][fidx - SX]) + __float_as_int(sm.xch[27][fidx + SX]);
-                    prest = __float_as_int(sm.xch[29][fidx]);
-                    pup = __float_as_int(sm.xch[30][fidx]);
-                    pdown = __float_as_int(sm.xch[31][fidx]);
+                for (int cx = -1; cx <= 1; ++cx) {
+                    if (!cx && !cy) continue;
+                    const int k = (cx + 1) + 3 * (cy + 1);
+                    const vec4 v = ((const vec4 *)&xc[(1 - cy) * SX + (1 - cx)][0])[xy_slot(cx, cy)];
+                    t0[k] = v.x + (v.w - rpc);
+                    t1[k] = v.y;
+                    t2[k] = v.z;
                 }
-                // destination plane r - 1: X(-1) from source plane r, X(0) = XB, X(+1) = XA
-                const int zd = r - 1;
-                if (owned && zd >= z0 && zd < z1 && (g.per[2] || (zd > 0 && zd < g.nz - 1))) {
-                    const Tr3 m00 = tr3(Xm[0], XB[0], XA[0]);  // rho', j_z, H_zz
-                    const Tr3 m10 = tr3(Xm[1], XB[1], XA[1]);  // j_x, H_xz
-                    const Tr3 m01 = tr3(Xm[2], XB[2], XA[2]);  // j_y, H_yz
-                    const float Hxx = tr3_m0(Xm[3], XB[3], XA[3]);
-                    const float Hyy = tr3_m0(Xm[4], XB[4], XA[4]);
-                    const float Hxy = tr3_m0(Xm[5], XB[5], XA[5]);
-                    const float drho = m00.m0;
-                    const float jx = m10.m0, jy = m01.m0, jz = m00.m1;
-                    const float inv = VD ? 1.0f : recip(1.0f + drho);
-                    float m[10];
-                    m[0] = drho;
-                    m[1] = jx * inv;
-                    m[2] = jy * inv;
-                    m[3] = jz * inv;
-                    m[4] = fmaf(-jx * inv, jx, Hxx);
-                    m[5] = fmaf(-jy * inv, jy, Hyy);
-                    m[6] = fmaf(-jz * inv, jz, m00.m2);
-                    m[7] = fmaf(-jx * inv, jy, Hxy);
-                    m[8] = fmaf(-jx * inv, jz, m10.m1);
-                    m[9] = fmaf(-jy * inv, jz, m01.m1);
-                    // streamed phase, held to the clamp range (a stable run never reaches it)
-                    const int32_t phin = phi_clamp(PA + pdown);
-                    // the z walls of this column take the values of planes 1 and nz-2
-                    // (x_F of an edge node is interior in every coordinate, so the
-                    // image is made from the moments before any x/y rule)
-                    if (!g.per[2] && (zd == 1 || zd == g.nz - 2)) {
-                        const int zb = zd == 1 ? 0 : g.nz - 1;
+            float X0[6], X1[6], X2[6];
+            xy_moments(t0, X0);
+            xy_moments(t1, X1);
+            xy_moments(t2, X2);
+            int32_t pin = 0;
+            if constexpr (PH) {
+                const int32_t(*xi)[T::REC] = (const int32_t(*)[T::REC])xc;
+                pin = xi[SX][32] + xi[SX + 2][33] + xi[1][34] + xi[2 * SX + 1][35];
+            }
+            // The populations of c_z = -1, 0, +1 sum to M, Z, P (X = X0 + c_z X1 +
+            // (c_z^2 - 1/3) X2) and belong to planes r - 1, r, r + 1.  Kept for the
+            // plane above: P (ZP); for the plane r itself, which still lacks the M of
+            // plane r + 1: Z (ZA) and P(r - 1) - Z (ZD) where the first or second z
+            // moment is needed too (rho', j_x, j_y), else their weighted sum (ZQ).
+            // rho' of the own column comes back last, one rounding at its magnitude, which
+            // also keeps the density of a uniform stream from creeping by rounding (a
+            // tenth of an ulp a step stays below what the sum resolves).  With variable
+            // density p* is larger than the stress by far: there the sums stay without it
+            // and the exact differences between planes (dr, from ZR) enter, with which a
+            // droplet at density ratio 1:10 keeps its stress within 7e-6 of the oracle
+            // after 200 steps (1.1e-5 with p* added in).
+            // In this order (held by the empty asm statements) each carried value is
+            // formed in the register of the one it replaces.
+            float M[6];
+#pragma unroll
+            for (int k = 0; k < 6; ++k) M[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) - X1[k];
+            float dr = 0.f;
+            if constexpr (VD)
+                dr = rpc - ZR;
+            else
+                M[0] += rpc;
+            // (X carries the factors 1, 6, 6, 9, 9, 36 of xy_moments)
+            const float d00 = VD ? (M[0] - ZA[0]) + dr : M[0] - ZA[0], d10 = M[1] - ZA[1], d01 = M[2] - ZA[2];
+            const float s00 = d00 + ZD[0];
+            const float drho = VD ? ZR + fmaf(s00, 1.0f / 6.0f, ZA[0]) : fmaf(s00, 1.0f / 6.0f, ZA[0]);
+            const float jz = (ZD[0] - d00) * (1.0f / 6.0f), Hzz = s00 * (1.0f / 9.0f);
+            const float jx = fmaf(d10 + ZD[1], 1.0f / 6.0f, ZA[1]) * (1.0f / 6.0f), Hxz = (ZD[1] - d10) * (1.0f / 36.0f);
+            const float jy = fmaf(d01 + ZD[2], 1.0f / 6.0f, ZA[2]) * (1.0f / 6.0f), Hyz = (ZD[2] - d01) * (1.0f / 36.0f);
+            const float Hxx = fmaf(M[3], 1.0f / 54.0f, ZQ[0]);
+            const float Hyy = fmaf(M[4], 1.0f / 54.0f, ZQ[1]);
+            const float Hxy = fmaf(M[5], 1.0f / 216.0f, ZQ[2]);
+            const float inv = VD ? 1.0f : recip(1.0f + drho);
+            m[0] = drho;
+            m[1] = jx * inv;
+            m[2] = jy * inv;
+            m[3] = jz * inv;
+            m[4] = fmaf(-m[1], jx, Hxx);
+            m[5] = fmaf(-m[2], jy, Hyy);
+            m[6] = fmaf(-m[3], jz, Hzz);
+            m[7] = fmaf(-m[1], jy, Hxy);
+            m[8] = fmaf(-m[1], jz, Hxz);
+            m[9] = fmaf(-m[2], jz, Hyz);
+            // streamed phase, held to the clamp range (a stable run never reaches it)
+            phin = PH ? phi_clamp(PA + pdown) : 0;
+#pragma unroll
+            for (int k = 0; k < 10; ++k) __asm__ volatile("" : "+v"(m[k]));
+            __asm__ volatile("" : "+v"(phin));
+            if constexpr (PH) {
+                PA = PC + prest + pin;
+                PC = pup;
+            }
+#pragma unroll
+            for (int k = 0; k < 6; ++k) __asm__ volatile("" : "+v"(X0[k]), "+v"(X2[k]));
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                ZA[k] = fmaf(X2[k], -1.0f / 3.0f, X0[k]);
+                if (!VD && k == 0) ZA[0] += rpc;
+                ZD[k] = VD && k == 0 ? (ZP[k] - ZA[k]) - dr : ZP[k] - ZA[k];
+                const float c = k == 2 ? 1.0f / 216.0f : 1.0f / 54.0f;
+                ZQ[k] = fmaf(fmaf(X2[3 + k], -1.0f / 3.0f, X0[3 + k]), 4.0f * c, ZP[3 + k] * c);
+                __asm__ volatile("" : "+v"(ZA[k]), "+v"(ZD[k]), "+v"(ZQ[k]));
+            }
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                __asm__ volatile("" : "+v"(X2[k]));
+                ZP[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) + X1[k];
+            }
+            if constexpr (VD)
+                ZR = rpc;
+            else
+                ZP[0] += rpc;
+        }
+        // After the destinations' arithmetic and before any store of the iteration:
+        // wait for the loads issued at its top (vmcnt 0; expcnt and lgkmcnt fields at
+        // their maxima, i.e. not waited for) and stage phi(p + 2) for the geometry of
+        // the next iteration (slot of plane p - 2, whose last readers, the sources of
+        // phase A, are done; phase B reads another).
+        // Loads and stores share one in-order counter, and the stores are conditional,
+        // so a wait placed after them could only be vmcnt(0) and would also wait until
+        // every store of the iteration has been acknowledged.  Here the loads have had
+        // nearly the whole iteration to arrive, and the stores drain during the next one.
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        stage_phi(it + 2, phi_next);
+        if (finish) {
+            const int zd = r - 1;
+            const bool z_image = !g.per[2] && (zd == 1 || zd == g.nz - 2);
+            if (zd >= z0 && zd < z1 && (g.per[2] || (zd > 0 && zd < g.nz - 1))) {
+                if (!(tile_walls || z_image)) {
+                    if (own) {
+                        store_plane<ST>(out.mom, g.ld, plane * zd, off_dst, m, sc);
+                        if constexpr (PH) store_phi(out.phi, plane * zd, off_dst, phin);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 10; ++k) m[k] = __shfl(m[k], lane_f);
+                    if constexpr (PH) phin = __shfl(phin, lane_f);
+                    // the node itself (v = 0) and its images: on the z wall next to plane
+                    // zd (v & 1) and in the last row of an odd low lattice (v & 2).  x_F of
+                    // an edge node is interior in every coordinate, so each is made from
+                    // the moments before any rule.
+                    const bool yi = y_image && gys == g.ny - 2;
+#pragma unroll 1
+                    for (int v = 0; v < (y_image ? 4 : 2); ++v) {
+                        if ((v & 1) && !z_image) continue;
+                        if (!own || ((v & 2) && !yi)) continue;
+                        const int Y = (v & 2) ? g.ny - 1 : gys;
+                        const int Zp = !(v & 1) ? zd : (zd == 1 ? 0 : g.nz - 1);
                         float mb[10];
 #pragma unroll
                         for (int k = 0; k < 10; ++k) mb[k] = m[k];
                         int32_t pb = phin;
-                        apply_boundary_rule(ph, g, zd == 1 ? 4 : 5, gxs, gys, step_next, mb, pb);
-                        const long long ib = (long long)gxs + (long long)g.nx * gys + plane * zb;
-#pragma unroll
-                        for (int k = 0; k < 10; ++k) store_moment<ST, G>(out.mom, g.ld, k, ib, mb[k], sc);
-                        if constexpr (PH) store_nt(&mem<G>(out.phi)[ib], pb);
+                        const int face = boundary_face(g, gxs, Y, Zp);
+                        const uint32_t rule = face < 0 ? 0u : (rules >> (4 * face)) & 15u;
+                        if (rule == 2u)
+                            apply_inlet(*walls, g, gxs, Y, step_next, mb, pb);
+                        else
+                            apply_rule(rule, face >> 1, mb);
+                        const uint32_t off = (uint32_t)gxs + (uint32_t)g.nx * (uint32_t)Y;
+                        store_plane<ST>(out.mom, g.ld, plane * Zp, off, mb, sc);
+                        if constexpr (PH) store_phi(out.phi, plane * Zp, off, pb);
                     }
-                    // the node itself: interior, or on an x/y wall (face rule of step t+1)
-                    int32_t po = phin;
-                    if (dxf | dyf) {
-                        const int face = boundary_face(g, gxs, gys, zd);
-                        apply_boundary_rule(ph, g, face, gxs, gys, step_next, m, po);
-                    }
-                    const long long id = (long long)gxs + (long long)g.nx * gys + plane * zd;
-#pragma unroll
-                    for (int k = 0; k < 10; ++k) store_moment<ST, G>(out.mom, g.ld, k, id, m[k], sc);
-                    if constexpr (PH) store_nt(&mem<G>(out.phi)[id], po);
                 }
-                // carry: plane r gets X(+1) = XC, X(0) = X0; plane r+1 gets X(+1) = Xp
-#pragma unroll
-                for (int k = 0; k < 6; ++k) {
-                    XA[k] = XC[k];
-                    XB[k] = X0[k];
-                    XC[k] = Xp[k];
-                }
-                PA = PC + prest + pin;
-                PC = pup;
             }
         }
         __syncthreads();
@@ -749,12 +923,16 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 }
 
 
+static_assert(sizeof(Geo) % alignof(Phys) == 0 && alignof(Geo) == alignof(Phys), "ph follows g directly");
 template <int ST, bool PH, bool VD, int ROWS>
 __global__ __launch_bounds__(Tile<ROWS>::NT) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
                                                                int lz, int tiles_x, int tiles_y,
                                                                unsigned long long step_next) {
     __shared__ Smem<PH, VD, ROWS> sm;
-    step_fused<ST, PH, false, false, VD, ROWS>(sm, g, ph, sc, in, out, lz, tiles_x, tiles_y, step_next,
+    // ph sits behind g in the kernel's argument segment
+    const PhysMem walls = (PhysMem)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
+                                    sizeof(Geo));
+    step_fused<ST, PH, false, VD, ROWS>(sm, g, ph, walls, sc, in, out, lz, tiles_x, tiles_y, step_next,
                                                xcd_work_item(blockIdx.x, gridDim.x));
 }
 
@@ -787,9 +965,7 @@ __global__ __launch_bounds__(Tile<ROWS>::NT) void k_step_fused_multi(const Fused
     g.per[0] = d.g.per[0]; g.per[1] = d.g.per[1]; g.per[2] = d.g.per[2];
     g.N = d.g.N; g.ld = d.g.ld;
     Phys ph;
-    ph.omega = d.ph.omega; ph.sigma = d.ph.sigma; ph.gamma = d.ph.gamma; ph.eps = d.ph.eps; ph.width = d.ph.width;
-    ph.inlet_u = d.ph.inlet_u; ph.inlet_d = d.ph.inlet_d; ph.inlet_noise = d.ph.inlet_noise;
-    ph.noise_key = d.ph.noise_key;
+    ph.omega = d.ph.omega; ph.sigma = d.ph.sigma; ph.gamma = d.ph.gamma; ph.eps = d.ph.eps;
     ph.bc[0] = d.ph.bc[0]; ph.bc[1] = d.ph.bc[1]; ph.bc[2] = d.ph.bc[2];
     ph.bc[3] = d.ph.bc[3]; ph.bc[4] = d.ph.bc[4]; ph.bc[5] = d.ph.bc[5];
     if constexpr (VD) {
@@ -802,7 +978,7 @@ __global__ __launch_bounds__(Tile<ROWS>::NT) void k_step_fused_multi(const Fused
     in.mom = d.in.mom; in.phi = d.in.phi; out.mom = d.out.mom; out.phi = d.out.phi;
     const int lz = d.lz, tx = d.tiles_x, ty = d.tiles_y, wb = d.work_begin;
     const unsigned long long sn = d.step_next;
-    step_fused<ST, PH, (ST == ST_FP32), true, VD, ROWS>(sm, g, ph, sc, in, out, lz, tx, ty, sn, w - wb);
+    step_fused<ST, PH, true, VD, ROWS>(sm, g, ph, (PhysMem)&d.ph, sc, in, out, lz, tx, ty, sn, w - wb);
 }
 
 }  // namespace fused
@@ -931,66 +1107,44 @@ void launch_multi(unsigned blocks, hipStream_t s, const FusedDomain *doms, int n
 
 hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int lz, int64_t step_next,
                              hipStream_t s) {
+    if (c->storage != ST_FP32) return launch_step_half(c, in, out, lz, step_next, s);
     const int rows = fused_rows(c);
     const int tiles_x = (c->geo.nx + fused::Tile<16>::TX - 1) / fused::Tile<16>::TX;
     const int tiles_y = (c->geo.ny + rows - 1) / rows;
     const int chunks = (c->geo.nz + lz - 1) / lz;
     const unsigned blocks = (unsigned)tiles_x * tiles_y * chunks;
     const unsigned long long sn = (unsigned long long)step_next;
-    if (c->vd) {  // variable density: binary32 storage, two components, 16 rows (validated at creation)
-        if (c->storage != ST_FP32 || !c->phase || rows != 16) return hipErrorInvalidValue;
+    if (c->vd) {  // variable density: two components, 16 rows (validated at creation)
+        if (!c->phase || rows != 16) return hipErrorInvalidValue;
         launch_one<ST_FP32, true, true, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
         return hipGetLastError();
     }
-#define TSLB_FUSED_CASE(ST)                                                                            \
-    case ST:                                                                                           \
-        if (!c->phase)                                                                                 \
-            launch_one<ST, false, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);         \
-        else if (rows == 20)                                                                           \
-            launch_one<ST, true, false, 20>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
-        else                                                                                           \
-            launch_one<ST, true, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
-        break;
-    switch (c->storage) {
-        TSLB_FUSED_CASE(ST_FP32)
-        TSLB_FUSED_CASE(ST_FP16)
-        TSLB_FUSED_CASE(ST_BF16)
-        TSLB_FUSED_CASE(ST_FP16Q)
-    default:
-        return hipErrorInvalidValue;
-    }
-#undef TSLB_FUSED_CASE
+    if (!c->phase)
+        launch_one<ST_FP32, false, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
+    else if (rows == 20)
+        launch_one<ST_FP32, true, false, 20>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
+    else
+        launch_one<ST_FP32, true, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
     return hipGetLastError();
 }
 
 hipError_t launch_step_fused_multi(const FusedDomain *doms, int ndom, int total_work, int storage, bool phase,
                                    bool vd, int rows, hipStream_t s) {
     if (ndom <= 0 || total_work <= 0) return hipSuccess;
+    if (storage != ST_FP32) return vd ? hipErrorInvalidValue : launch_step_half_multi(doms, ndom, total_work, storage, phase, rows, s);
     const unsigned blocks = (unsigned)total_work;
     if (vd) {
-        if (storage != ST_FP32 || !phase || rows != 16) return hipErrorInvalidValue;
+        if (!phase || rows != 16) return hipErrorInvalidValue;
         launch_multi<ST_FP32, true, true, 16>(blocks, s, doms, ndom);
         return hipGetLastError();
     }
     if (rows != 16 && (rows != 20 || !phase)) return hipErrorInvalidValue;
-#define TSLB_MULTI_CASE(ST)                                                                            \
-    case ST:                                                                                           \
-        if (!phase)                                                                                    \
-            launch_multi<ST, false, false, 16>(blocks, s, doms, ndom);                                 \
-        else if (rows == 20)                                                                           \
-            launch_multi<ST, true, false, 20>(blocks, s, doms, ndom);                                  \
-        else                                                                                           \
-            launch_multi<ST, true, false, 16>(blocks, s, doms, ndom);                                  \
-        break;
-    switch (storage) {
-        TSLB_MULTI_CASE(ST_FP32)
-        TSLB_MULTI_CASE(ST_FP16)
-        TSLB_MULTI_CASE(ST_BF16)
-        TSLB_MULTI_CASE(ST_FP16Q)
-    default:
-        return hipErrorInvalidValue;
-    }
-#undef TSLB_MULTI_CASE
+    if (!phase)
+        launch_multi<ST_FP32, false, false, 16>(blocks, s, doms, ndom);
+    else if (rows == 20)
+        launch_multi<ST_FP32, true, false, 20>(blocks, s, doms, ndom);
+    else
+        launch_multi<ST_FP32, true, false, 16>(blocks, s, doms, ndom);
     return hipGetLastError();
 }
 
