@@ -3,10 +3,11 @@
 // (binary32 storage; tslb_step_half.hip is the step for 16-bit stored moments)
 //
 // Work decomposition.  A workgroup owns a 32 x 16 (or 32 x 20) tile of (x, y)
-// destination columns and marches through a chunk of z planes; its threads are
-// destination columns (each also the source of that column), columns of the
-// one-node halo ring (sources only) and, for the interface geometry, columns of a
-// two-node halo.  For every z plane the workgroup
+// destination columns and marches through a chunk of z planes.  Its waves have
+// fixed roles: destination columns (each also the source of that column), columns
+// of the one-node halo ring (sources only) and, with two components, the geometry
+// of the interface (columns of a one- and a two-node halo, two rows at a time).
+// For every z plane the workgroup
 //   S1  stages the fixed-point phase field of a plane (3-node halo) in LDS,
 //   S2  computes G = grad(phi) and n = G/(|G| + eps) (2-node halo) from the plane's
 //       nine values around a column and sums kept of the planes before it,
@@ -30,8 +31,15 @@
 //        difference then act on 6 sums and on T0 instead of on 27 populations), 16-byte
 //        LDS records per direction, G and kappa from running sums (9 LDS reads of phi
 //        a column instead of 26), state accesses with a scalar base, the memory wait
-//        after the destination's arithmetic.  Per 20-row plane 5.3k vector
-//        wave-instructions instead of 6.4k, 60 LDS instructions a wave instead of 129.
+//        after the destination's arithmetic
+//   195  geometry in waves of its own (six beside ten, or four beside twelve).  Spread
+//        over the source waves its work stood in the same chain: phase A was a source
+//        and a geometry item one after the other, phase B a destination and a curvature
+//        item, on 10 waves (2.5 a SIMD, so the third wave of two SIMDs set the pace).
+//        Now both run side by side on 16 waves, the geometry one plane ahead; two rows
+//        of an item share their 12 values of phi (instead of 9 each) and their sums of
+//        n.  256^3 vortex (one component, only the first moment load moved) 266 as before,
+//        variable density 237 -> 201, 512 x 512 x 2048 jet 14.1 -> 12.8 ms.
 //
 // Arithmetic (Eqs. 5-8, 15-19 with Guo forcing; Eqs. 20-24):
 //   source:  u = ubar + F/(2 rho), P = Q + F F/(4 rho), J = rho u + F/2,
@@ -66,23 +74,22 @@ namespace fused {
 
 // Tile shapes.  A workgroup owns TX x TY destination columns; its sources, the
 // geometry and the staged phase field cover the tile plus a halo of 1, 2 and 3
-// columns.  Two heights: 16 rows with 640 threads (10 waves) and 20 rows with
-// 768 threads (12 waves, three on every SIMD, less halo per column), chosen per
-// lattice by the host (fused_plan); the one-component and variable-density
-// steps take 16 rows.  A source's exchange record is 36 words: for each of the eight
-// directions across columns T0, T1, T2 and rho', then the phase sent to +x, -x, +y and
-// -y.  16-byte accesses a stride of 36 words apart cover all LDS banks.
+// columns.  Two heights: 16 rows (10 waves with a source, 6 of geometry) and 20
+// rows (12 and 4: 1.23 times the time a plane for 1.25 times the columns), chosen
+// per lattice by the host (fused_plan); the one-component and variable-density
+// steps take 16 rows, the former without geometry waves.
 template <int ROWS> struct Tile {
     static constexpr int TX = 32, TY = ROWS;
     static constexpr int SX = TX + 2, SY = TY + 2, NSRC = SX * SY;   // sources: 34 x 18 or 34 x 22
     static constexpr int GX = TX + 4, GY = TY + 4, NGEO = GX * GY;   // geometry: 36 x 20 or 36 x 24
     static constexpr int PX = TX + 6, PY = TY + 6, NPHI = PX * PY;   // phase field: 38 x 22 or 38 x 26
     static constexpr int NDST = TX * TY;                              // 512 or 640
-    static constexpr int NT = ROWS == 16 ? 640 : 768;                 // threads per workgroup
+    static constexpr int NST = ROWS == 16 ? 640 : 768;                // threads with a source or destination
+    static constexpr int NGT = ROWS == 16 ? 384 : 256;                // threads of the geometry waves (two components)
     static constexpr int REC = 36;                                    // words of a source's exchange record
     static_assert(ROWS == 16 || ROWS == 20, "tile heights: 16 or 20 rows");
-    static_assert(NSRC <= NT && NDST <= NSRC, "tile does not fit the workgroup");
-    static_assert(NPHI <= 2 * NT && NGEO <= 2 * NT, "staging loops assume two items per thread");
+    static_assert(NSRC <= NST && NDST <= NSRC && NST + NGT <= 1024, "tile does not fit the workgroup");
+    static constexpr int threads(bool phase) { return phase ? NST + NGT : NST; }
 };
 typedef float vec4 __attribute__((ext_vector_type(4)));
 typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
@@ -95,8 +102,9 @@ template <bool PH, bool VD, int ROWS> struct alignas(16) Smem {
     using T = Tile<ROWS>;
     float xch[T::NSRC][T::REC];        // populations crossing columns
     int32_t phi[4][T::NPHI];           // fixed-point phase field, ring of 4 planes
-    float n[3][3][T::NGEO];            // unit normal, ring of 3 planes
-    float G[3][VD ? 3 : 1][T::NSRC];   // gradient (VD) or |G| + eps on the source region, ring of 3 planes
+    float n[2][3][T::NGEO];            // unit normal, ring of 2 planes
+    float G[2][VD ? 3 : 1][T::NSRC];   // gradient (VD) or |G| + eps on the source region, ring of 2 planes
+    float kap[T::NSRC];                // 72 kappa of the next source plane
 };
 template <bool VD, int ROWS> struct alignas(16) Smem<false, VD, ROWS> {
     float xch[Tile<ROWS>::NSRC][Tile<ROWS>::REC];  // populations crossing columns
@@ -149,6 +157,18 @@ __device__ __forceinline__ int wrap_or_clamp(int v, int n, int periodic) {
         return v < 0 ? v + n : v;
     }
     return v < 0 ? 0 : (v >= n ? n - 1 : v);
+}
+
+// Column i of a W x H region (W > 32) in the order in which lanes take them: first
+// columns 0-31, one row per half-wave (32 neighbouring LDS words: no bank conflict),
+// then the remaining W - 32 columns, row by row.
+struct Item {
+    int x, y;
+};
+template <int W, int H> __device__ __forceinline__ Item item_of(int i) {
+    static_assert(W > 32 && W < 64, "rows are split into 32 + (W - 32) columns");
+    if (i < 32 * H) return {i & 31, i >> 5};
+    return {32 + (i - 32 * H) % (W - 32), (i - 32 * H) / (W - 32)};
 }
 
 // The six 2-D moments X_pq = sum_{cx,cy} w(cx) w(cy) h_p(cx) h_q(cy) t(cx, cy) of
@@ -265,7 +285,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 #pragma clang fp contract(off)
     using T = Tile<ROWS>;
     constexpr int TX = T::TX, TY = T::TY, SX = T::SX, SY = T::SY, NSRC = T::NSRC, GX = T::GX, GY = T::GY,
-                  NGEO = T::NGEO, PX = T::PX, NPHI = T::NPHI, NDST = T::NDST, NT = T::NT;
+                  NGEO = T::NGEO, PX = T::PX, NPHI = T::NPHI, NDST = T::NDST;
     const int tile = w % (tiles_x * tiles_y);
     const int chunk = w / (tiles_x * tiles_y);
     // The tile owns columns [xo, xo + TX) x [yo, yo + TY); its origin (x0, y0) is
@@ -276,7 +296,15 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     const int y0 = g.ny > TY ? min(yo, g.ny - TY) : 0;
     const int z0 = chunk * lz;
     const int z1 = min(z0 + lz, g.nz);  // destination planes [z0, z1)
-    const int t = threadIdx.x;
+    // Roles.  Waves are placed on the four SIMDs round-robin (wave w on SIMD w % 4).
+    // The first NDST / 64 waves hold the destination columns (and their sources), the
+    // next two the halo sources, the rest the geometry.  With 20 rows ten waves finish
+    // destinations, three of them on SIMDs 0 and 1 and two on SIMDs 2 and 3: the halo
+    // waves go to SIMDs 0 and 1 (waves 12 and 13), the geometry waves to 2 and 3, which
+    // evens out both phases.
+    int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    if constexpr (PH && ROWS == 20) wave = wave < 10 ? wave : (wave < 12 ? wave + 2 : (wave < 14 ? wave - 2 : wave));
+    const int t = wave * 64 + ((int)threadIdx.x & 63);
     const long long plane = (long long)g.nx * g.ny;
 
     // ---- this thread's source column (local sx, sy in the 34 x 18 or 34 x 22 region) ----
@@ -284,7 +312,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     const bool is_dst = t < NDST;
     const bool is_src = t < NSRC;
     static_assert(NDST % 64 == 0, "a wave has destinations in all lanes or in none");
-    const bool dst_wave = __builtin_amdgcn_readfirstlane(t >> 6) < NDST / 64;
+    const bool dst_wave = wave < NDST / 64, source_wave = wave < T::NST / 64;
     if (is_dst) {
         sx = t % TX + 1;
         sy = t / TX + 1;
@@ -322,67 +350,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     for (int f = 0; f < 6; ++f) rules |= (uint32_t)ph.bc[f] << (4 * f);
     const uint32_t off_dst = (uint32_t)gxs + (uint32_t)g.nx * (uint32_t)gys;  // used where owned
 
-    // ---- staging columns of the phase field (<= 2 per thread) ----
-    // (a thread without a second item loads the first again and stores nothing)
-    uint32_t off_phi[2];
-    const bool phi_two = t + NT < NPHI;
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        const int i = k && phi_two ? t + NT : t;
-        const int px = i % PX, py = i / PX;
-        const int gx = wrap_or_clamp(x0 - 3 + px, g.nx, g.per[0]);
-        const int gy = wrap_or_clamp(y0 - 3 + py, g.ny, g.per[1]);
-        off_phi[k] = (uint32_t)gx + (uint32_t)g.nx * (uint32_t)gy;
-    }
-    // Geometry items (S2 of plane p): a thread has at most two columns of the
-    // GX x GY region, `a` computed in phase A and `b` in phase B, the same ones on
-    // every plane (each keeps its own partial sums).
-    // Waves are placed on the four SIMDs round-robin (wave w on SIMD w % 4), and
-    // each phase ends at a barrier.  The normal and gradient of plane p are first
-    // read in the next iteration, so an item may run in either phase.
-    // 16 rows: SIMDs 0 and 1 run three source waves (0, 4, 8 and 1, 5, 9), SIMDs
-    // 2 and 3 two, so in phase A waves 0-7 take items 0-511, and in phase B waves 8
-    // and 9, which have no destination, the next 128 and waves 2 and 3 the last 80.
-    // 20 rows: phase A holds three source waves on every SIMD, phase B three
-    // destination waves on SIMDs 0 and 1 but two on SIMDs 2 and 3, so threads
-    // 0-479 (two waves per SIMD) take one item in phase A, and in phase B waves 10
-    // and 11 (no destination) and waves 2, 3, 6 and 7 (before their destination)
-    // one item each.
-    // The variable-density step (16 rows; its items store all of G) keeps every
-    // item in phase A, where that measured faster: waves 0-7 take items 0-511 and
-    // waves 2, 3, 6 and 7 the other 208.
-    static_assert(GX >= 32 && GX < 64, "geometry rows are split into 32 + (GX - 32) columns");
-    int item[2] = {-1, -1};
-    if constexpr (PH) {
-        const int wv = t >> 6, lane = t & 63;
-        const int r4 = wv == 2 ? 0 : wv == 3 ? 1 : wv == 6 ? 2 : wv == 7 ? 3 : -1;
-        constexpr int na = TY == 16 ? NDST : 480;  // phase-A items on threads 0 .. na - 1
-        if (t < na) item[0] = t;
-        if (VD) {
-            if (r4 >= 0 && r4 * 64 + lane < NGEO - na) item[1] = na + r4 * 64 + lane;
-        } else {
-            if (t >= NDST) item[1] = na + (t - NDST);
-            if (r4 >= 0 && NT - NDST + r4 * 64 + lane < NGEO - na) item[1] = na + (NT - NDST) + r4 * 64 + lane;
-        }
-        static_assert(NGEO - na <= (VD ? 256 : NT - NDST + 256), "every geometry item has a thread");
-    }
-    int gc[2], gi[2], gs[2];  // position of each item in the phi, geometry and source regions (-1: outside)
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        // items 0 .. 32 GY - 1 cover columns 0-31 of each row, one row per
-        // half-wave (contiguous LDS addresses, no bank conflicts); the
-        // rest cover columns 32 .. GX - 1
-        const int i = max(item[k], 0);
-        const int gxl = i < 32 * GY ? (i & 31) : 32 + (i - 32 * GY) % (GX - 32);
-        const int gyl = i < 32 * GY ? (i >> 5) : (i - 32 * GY) / (GX - 32);
-        gi[k] = gyl * GX + gxl;
-        gc[k] = (gyl + 1) * PX + (gxl + 1);
-        const int ssx = gxl - 1, ssy = gyl - 1;
-        gs[k] = ssx >= 0 && ssx < SX && ssy >= 0 && ssy < SY ? ssy * SX + ssx : -1;
-    }
-
     const float omega1 = 1.0f - ph.omega;
-    const float sigma72 = ph.sigma * (1.0f / 72.0f), gamma = ph.gamma, eps = ph.eps;
+    const float sigma72 = ph.sigma * (1.0f / 72.0f), gamma = ph.gamma;
 
     // carried destination state (see S6)
     float ZA[3], ZD[3], ZQ[3], ZP[6], ZR = 0.f;
@@ -391,17 +360,11 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 #pragma unroll
     for (int k = 0; k < 6; ++k) ZP[k] = 0.f;
     int32_t PA = 0, PC = 0;    // phase partial sums of planes r - 1 and r
-    float k1 = 0.f, k2 = 0.f, e1 = 0.f, e2 = 0.f;  // curvature partial sums (S3a)
-    // gradient partial sums of the two geometry items (S2)
-    float gSx[2] = {0.f, 0.f}, gAx[2] = {0.f, 0.f}, gSy[2] = {0.f, 0.f}, gAy[2] = {0.f, 0.f};
-    float gR0[2] = {0.f, 0.f}, gR1[2] = {0.f, 0.f};
-    int32_t gc0[2] = {0, 0}, gc1[2] = {0, 0};
+    float own_n[3] = {0.f, 0.f, 0.f}, own_G[3] = {0.f, 0.f, 0.f};  // n, |G| + eps (or G) and phi of the
+    int32_t own_phi = 0;                                           // next source plane (own column)
 
-    // prefetched raw moments of the next source plane (own column)
-    // (stored words: a 16-bit moment is converted only when the next iteration
-    // takes it over, so its load is not waited for in the iteration that issues it)
+    // prefetched moments of the next source plane (own column)
     uint32_t mom[10] = {};  // defined before the first prefetch (decoded but unused until then)
-    int32_t phi_next[2] = {0, 0};
 
     // z is uniform and at most a few planes outside [0, nz): wrapped by whole
     // periods, or clamped.  In the loop each index follows from the one before.
@@ -417,102 +380,224 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         const int n = g.per[2] ? 0 : g.nz - 1;
         return (!g.per[2] && z <= 0) ? 0 : (k + 1 >= g.nz ? n : k + 1);
     };
-    auto load_phi = [&](int k, int32_t v[2]) {
-        global_t<char> *q = uniform((global_t<char> *)in.phi + 4 * (plane * k));
-#pragma unroll
-        for (int k = 0; k < 2; ++k) v[k] = *(const global_t<int32_t> *)(q + lane_offset(off_phi[k] * 4u));
-    };
-    auto stage_phi = [&](int slot, const int32_t v[2]) {
-        if constexpr (PH) {
-            sm.phi[slot & 3][t] = v[0];
-            if (phi_two) sm.phi[slot & 3][t + NT] = v[1];
-        }
-    };
-
-    // ---- S2: G and n of plane p at geometry item k ----
-    // G = 3 sum_i w_i c_i phi(y + c_i) with the factorised weights (1, 4, 1)/6 per
-    // axis: G_x = (1/72) sum_z (1,4,1) sum_y (1,4,1) [phi(x+1) - phi(x-1)], G_y
-    // likewise, and G_z = (1/72) [36 (c(z+1) - c(z-1)) + R(z+1) - R(z-1)] with c the
-    // column's own value and R = sum_xy (1,4,1)(1,4,1) (phi - c).  So one plane of
-    // phi enters through nine values, and the item keeps its sums of the planes
-    // before it.  Differences of phi are exact integers, rounded once when they
-    // become binary32, so a uniform field gives exactly G = 0.
-    auto absorb_plane = [&](auto K, int slot, float &Gx, float &Gy, float &Gz) {
-        if constexpr (PH) {
-            constexpr int k = decltype(K)::value;
-            const int32_t *q = sm.phi[slot & 3] + gc[k];
-            const int32_t c = q[0], e = q[1], v = q[-1], n = q[PX], d = q[-PX];
-            const int32_t ne = q[PX + 1], sw = q[-PX - 1], se = q[-PX + 1], nw = q[PX - 1];
-            const float ew = (float)(e - v), ns = (float)(n - d), d1 = (float)(ne - sw), d2 = (float)(se - nw);
-            const float wc = (float)(v - c), sc = (float)(d - c), swc = (float)(sw - c), nwc = (float)(nw - c);
-            const float dd = d1 + d2;
-            const float A = fmaf(4.0f, ew, dd), B = fmaf(4.0f, ns, d1 - d2);
-            const float R = fmaf(4.0f, fmaf(2.0f, wc + sc, ew + ns), fmaf(2.0f, swc + nwc, dd));
-            Gx = gSx[k] + A;
-            Gy = gSy[k] + B;
-            Gz = fmaf(36.0f, (float)(c - gc0[k]), R - gR0[k]);
-            gSx[k] = fmaf(4.0f, A, gAx[k]);
-            gAx[k] = A;
-            gSy[k] = fmaf(4.0f, B, gAy[k]);
-            gAy[k] = B;
-            gR0[k] = gR1[k];
-            gR1[k] = R;
-            gc0[k] = gc1[k];
-            gc1[k] = c;
-        }
-    };
-    auto geometry_item = [&](auto K, int it) {
-        if constexpr (PH) {
-            constexpr int k = decltype(K)::value;
-            float Gx, Gy, Gz;
-            absorb_plane(K, it + 1, Gx, Gy, Gz);
-            constexpr float kS = kPhiUlp / 72.0f;
-            // hardware square root (1 ulp) and a refined reciprocal: |G| + eps >= eps
-            const float den = fmaf(__builtin_amdgcn_sqrtf(fmaf(Gx, Gx, fmaf(Gy, Gy, Gz * Gz))), kS, eps);
-            const float inv = recip(den) * kS;
-            float *n = &sm.n[it % 3][0][0];
-            n[gi[k]] = Gx * inv;
-            n[NGEO + gi[k]] = Gy * inv;
-            n[2 * NGEO + gi[k]] = Gz * inv;
-            if (gs[k] >= 0) {
-                float *Gs = &sm.G[it % 3][0][0];
-                if constexpr (VD) {
-                    Gs[gs[k]] = Gx * kS;
-                    Gs[NSRC + gs[k]] = Gy * kS;
-                    Gs[2 * NSRC + gs[k]] = Gz * kS;
-                } else {
-                    Gs[gs[k]] = den;
-                }
-            }
-        }
-    };
-
     const int nit = (z1 - z0) + 6;
-    // prologue: phase planes z0 - 3 and z0 - 2 staged (slots 0, 1)
-    if constexpr (PH) {
-        int32_t v[2] = {0, 0};
-        load_phi(plane_of(z0 - 3), v);
-        stage_phi(0, v);
-        load_phi(plane_of(z0 - 2), v);
-        stage_phi(1, v);
-    }
-    __syncthreads();
-    if constexpr (PH) {  // the geometry takes in plane z0 - 3 (slot 0)
-        float gx, gy, gz;
-        if (item[0] >= 0) absorb_plane(std::integral_constant<int, 0>{}, 0, gx, gy, gz);
-        if (item[1] >= 0) absorb_plane(std::integral_constant<int, 1>{}, 0, gx, gy, gz);
-    }
-    int kmom = plane_of(z0 - 1), kphi = plane_of(z0 - 2);  // z planes of the loads
 
+    // ---- geometry waves (two components): waves NST / 64 and up ----
+    // They stage the phase field and hand the sources n, G and kappa in LDS, each a
+    // phase or more before it is used.
+    if constexpr (PH) {
+        if (!source_wave) {
+            constexpr int NGT = T::NGT;
+            constexpr int NP = (NPHI + NGT - 1) / NGT;
+            // geometry and curvature go by pairs of rows, which share the values between them
+            constexpr int NGP = GX * GY / 2, NCP = SX * SY / 2, NG = (NGP + NGT - 1) / NGT, NC = (NCP + NGT - 1) / NGT;
+            static_assert(GY % 2 == 0 && SY % 2 == 0, "rows come in pairs");
+            const int l = t - T::NST;
+            // staged columns of the phase field, geometry and source columns of
+            // this thread (the same ones on every plane; a surplus item repeats the last
+            // column and writes nothing)
+            uint32_t off_phi[NP];
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const int i = min(l + k * NGT, NPHI - 1);
+                const int px = i % PX, py = i / PX;
+                const int gx = wrap_or_clamp(x0 - 3 + px, g.nx, g.per[0]);
+                const int gy = wrap_or_clamp(y0 - 3 + py, g.ny, g.per[1]);
+                off_phi[k] = (uint32_t)gx + (uint32_t)g.nx * (uint32_t)gy;
+            }
+            int gc[NG], gi[NG], gs[NG];  // lower column's position in the phi, geometry and source regions
+            bool gin[NG][2];             // the two columns lie in the source region
+#pragma unroll
+            for (int k = 0; k < NG; ++k) {
+                const Item i = item_of<GX, GY / 2>(min(l + k * NGT, NGP - 1));
+                const int gxl = i.x, gyl = 2 * i.y;
+                gi[k] = gyl * GX + gxl;
+                gc[k] = (gyl + 1) * PX + (gxl + 1);
+                gs[k] = (gyl - 1) * SX + (gxl - 1);
+                for (int j = 0; j < 2; ++j) gin[k][j] = gxl >= 1 && gxl <= SX && gyl + j >= 1 && gyl + j <= SY;
+            }
+            int cs[NC], cg[NC];  // source index, corner (x-1, y-1) in the geometry region
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+                const Item i = item_of<SX, SY / 2>(min(l + k * NGT, NCP - 1));
+                const int cx = i.x, cy = 2 * i.y;
+                cs[k] = cy * SX + cx;
+                cg[k] = cy * GX + cx;
+            }
+            const float eps = ph.eps;
+            float gSx[2 * NG], gAx[2 * NG], gSy[2 * NG], gAy[2 * NG], gR0[2 * NG], gR1[2 * NG];  // gradient partial sums (S2)
+            int32_t gc0[2 * NG], gc1[2 * NG];
+#pragma unroll
+            for (int k = 0; k < 2 * NG; ++k) {
+                gSx[k] = gAx[k] = gSy[k] = gAy[k] = gR0[k] = gR1[k] = 0.f;
+                gc0[k] = gc1[k] = 0;
+            }
+            float k1[2 * NC], k2[2 * NC], e1[2 * NC], e2[2 * NC];  // curvature partial sums (S3a)
+#pragma unroll
+            for (int k = 0; k < 2 * NC; ++k) k1[k] = k2[k] = e1[k] = e2[k] = 0.f;
+            auto load_phi = [&](int z, int32_t v[NP]) {
+                global_t<char> *q = uniform((global_t<char> *)in.phi + 4 * (plane * z));
+#pragma unroll
+                for (int k = 0; k < NP; ++k) v[k] = *(const global_t<int32_t> *)(q + lane_offset(off_phi[k] * 4u));
+            };
+            auto stage_phi = [&](int slot, const int32_t v[NP]) {
+#pragma unroll
+                for (int k = 0; k < NP; ++k)
+                    if (l + k * NGT < NPHI) sm.phi[slot & 3][l + k * NGT] = v[k];
+            };
+            // ---- S2: G and n of plane p at geometry column k ----
+            // G = 3 sum_i w_i c_i phi(y + c_i) with the factorised weights (1, 4, 1)/6 per
+            // axis: G_x = (1/72) sum_z (1,4,1) sum_y (1,4,1) [phi(x+1) - phi(x-1)], G_y
+            // likewise, and G_z = (1/72) [36 (c(z+1) - c(z-1)) + R(z+1) - R(z-1)] with c the
+            // column's own value and R = sum_xy (1,4,1)(1,4,1) (phi - c).  So one plane of
+            // phi enters through nine values, and the column keeps its sums of the planes
+            // before it.  Differences of phi are exact integers, rounded once when they
+            // become binary32, so a uniform field gives exactly G = 0.
+            auto absorb_plane = [&](int k, const int32_t *q, float &Gx, float &Gy, float &Gz) {
+                const int32_t c = q[4], e = q[5], v = q[3], n = q[7], d = q[1];
+                const int32_t ne = q[8], sw = q[0], se = q[2], nw = q[6];
+                const float ew = (float)(e - v), ns = (float)(n - d), d1 = (float)(ne - sw), d2 = (float)(se - nw);
+                const float wc = (float)(v - c), sc = (float)(d - c), swc = (float)(sw - c), nwc = (float)(nw - c);
+                const float dd = d1 + d2;
+                const float A = fmaf(4.0f, ew, dd), B = fmaf(4.0f, ns, d1 - d2);
+                const float R = fmaf(4.0f, fmaf(2.0f, wc + sc, ew + ns), fmaf(2.0f, swc + nwc, dd));
+                Gx = gSx[k] + A;
+                Gy = gSy[k] + B;
+                Gz = fmaf(36.0f, (float)(c - gc0[k]), R - gR0[k]);
+                gSx[k] = fmaf(4.0f, A, gAx[k]);
+                gAx[k] = A;
+                gSy[k] = fmaf(4.0f, B, gAy[k]);
+                gAy[k] = B;
+                gR0[k] = gR1[k];
+                gR1[k] = R;
+                gc0[k] = gc1[k];
+                gc1[k] = c;
+            };
+            auto read_phi = [&](int k, int slot, int32_t q[12]) {  // rows y - 1 .. y + 2, columns x - 1 .. x + 1
+                const int32_t *b = sm.phi[slot & 3] + gc[k];
+#pragma unroll
+                for (int j = 0; j < 12; ++j) q[j] = b[(j / 3 - 1) * PX + j % 3 - 1];
+            };
+            // prologue: phase planes z0 - 3 .. z0 staged (slots 0 - 3) and the first taken in,
+            // so that the first two iterations wait for no load
+            int32_t v[NP];
+            {
+                int32_t first[4][NP];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) load_phi(plane_of(z0 - 3 + j), first[j]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) stage_phi(j, first[j]);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < NG; ++k) {
+                float gx, gy, gz;
+                int32_t q[12];
+                read_phi(k, 0, q);
+                absorb_plane(2 * k, q, gx, gy, gz);
+                absorb_plane(2 * k + 1, q + 3, gx, gy, gz);
+            }
+            int kphi = plane_of(z0);
+            for (int it = 0; it < nit; ++it) {
+                const int p = z0 - 3 + it;
+                if (it >= 2) {
+                    kphi = plane_after(p + 2, kphi);
+                    load_phi(kphi, v);
+                }
+                // ================= phase A =================
+                constexpr float kS = kPhiUlp / 72.0f;
+#pragma unroll
+                for (int k = 0; k < NG; ++k) {
+                    if (k && l + k * NGT >= NGP) break;  // whole waves have no further pair
+                    int32_t q[12];
+                    read_phi(k, it + 1, q);
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        float Gx, Gy, Gz;
+                        absorb_plane(2 * k + j, q + 3 * j, Gx, Gy, Gz);
+                        // hardware square root (1 ulp) and a refined reciprocal: |G| + eps >= eps
+                        const float den = fmaf(__builtin_amdgcn_sqrtf(fmaf(Gx, Gx, fmaf(Gy, Gy, Gz * Gz))), kS, eps);
+                        const float inv = recip(den) * kS;
+                        if (l + k * NGT < NGP) {
+                            const int i = gi[k] + j * GX, si = gs[k] + j * SX;
+                            sm.n[it & 1][0][i] = Gx * inv;
+                            sm.n[it & 1][1][i] = Gy * inv;
+                            sm.n[it & 1][2][i] = Gz * inv;
+                            if (gin[k][j]) {
+                                if constexpr (VD) {
+                                    sm.G[it & 1][0][si] = Gx * kS;
+                                    sm.G[it & 1][1][si] = Gy * kS;
+                                    sm.G[it & 1][2][si] = Gz * kS;
+                                } else {
+                                    sm.G[it & 1][0][si] = den;
+                                }
+                            }
+                        }
+                    }
+                }
+                __syncthreads();
+                // ================= phase B =================
+                // ---- S3a: per-column partial sums of the curvature stencil (plane p) ----
+                // With w_i = w1(c_x) w1(c_y) w1(c_z), w1 = (1, 4, 1)/6, the stencil
+                // kappa = 3 sum_i w_i c_i . n(x + c_i) factorises into sums over one plane:
+                //   72 kappa(q) = C(q-1) + 4 C(q) + C(q+1) + E(q+1) - E(q-1),
+                //   C = sum_cy (1,4,1) (n_x(x+1, y+cy) - n_x(x-1, y+cy))
+                //     + sum_cx (1,4,1) (n_y(x+cx, y+1) - n_y(x+cx, y-1)),
+                //   E = sum_{cx,cy} (1,4,1)(1,4,1) n_z(x+cx, y+cy),
+                // so each column keeps k1 = C(q-1) + 4 C(q), k2 = C(q), e1 = E(q-1) and e2 = E(q)
+                // (E apart: it is of order 36 where C, a sum of differences, is small).
+                // The kappa of plane p - 1 is then complete and goes out.
+#pragma unroll
+                for (int k = 0; k < NC; ++k) {
+                    if (k && l + k * NGT >= NCP) break;
+                    const float *bx = sm.n[it & 1][0] + cg[k], *by = bx + NGEO, *bz = by + NGEO;
+                    float ny[4][3], nz[4][3], D[4], e[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        D[j] = bx[j * GX + 2] - bx[j * GX];
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            ny[j][i] = by[j * GX + i];
+                            nz[j][i] = bz[j * GX + i];
+                        }
+                        e[j] = fmaf(4.0f, nz[j][1], nz[j][0] + nz[j][2]);
+                    }
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const int m = 2 * k + j, si = cs[k] + j * SX;
+                        const float Cx = fmaf(4.0f, D[j + 1], D[j] + D[j + 2]);
+                        const float Cy = fmaf(4.0f, ny[j + 2][1] - ny[j][1], (ny[j + 2][0] - ny[j][0]) + (ny[j + 2][2] - ny[j][2]));
+                        const float C = Cx + Cy, E = fmaf(4.0f, e[j + 1], e[j] + e[j + 2]);
+                        const float kap = (k1[m] + C) + (E - e1[m]);
+                        k1[m] = fmaf(4.0f, C, k2[m]);
+                        k2[m] = C;
+                        e1[m] = e2[m];
+                        e2[m] = E;
+                        if (l + k * NGT < NCP) sm.kap[si] = kap;
+                    }
+                }
+                // slot of plane p - 2, whose last readers (own_phi, phase B of it - 1) are done
+                if (it >= 2) stage_phi(it + 2, v);
+                __syncthreads();
+            }
+            return;
+        }
+    }
+    if constexpr (PH) __syncthreads();  // the geometry waves' prologue
+
+    int kmom = plane_of(z0 - 1);  // z plane of the last load
     // Iteration it works on three planes: p = z0 - 3 + it (geometry), q = p - 1
     // (normal of the curvature sums) and r = p - 2 (sources), and finishes
     // destination plane r - 1.  Rings: phi plane p at slot it mod 4, n and G of
-    // plane p at slot it mod 3.  Phase A (sources and geometry) and phase B
-    // (destinations and phase staging) are separated by barriers.
-    for (int it = 0; it < nit; ++it) {
+    // plane p at slot it mod 2.  Phase A (sources; G and n) and phase B
+    // (destinations; kappa and the staging of phi) are separated by barriers.
+    constexpr int IT0 = PH ? 0 : 3;  // one component has no geometry to wait for
+    for (int it = IT0; it < nit; ++it) {
         const int p = z0 - 3 + it;
         const int r = p - 2;
 
+        float kap = 0.f;
+        if constexpr (PH) kap = sm.kap[sidx];  // read ahead of the loads' address work
         // moments of source plane r + 1 for the next iteration
         float mom_cur[10];
 #pragma unroll
@@ -522,48 +607,13 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             // formed before the loads below, which then reuse the words' registers
             __asm__ volatile("" : "+v"(mom_cur[k]));
         }
-        // (the first source plane is z0 - 1, loaded while it <= 3; lanes without a
-        // source load a column of the lattice and drop it)
-        if (it > 3) kmom = plane_after(r + 1, kmom);
-        load_plane<ST>(in.mom, g.ld, plane * kmom, off_src, mom);
-        // phase plane p + 2, staged at the start of phase B.  Issued here, next to
-        // the moment prefetch, so that both have all of phase A to arrive (both are
-        // waited for at the start of phase B).
-        if constexpr (PH) {
-            kphi = plane_after(p + 2, kphi);
-            load_phi(kphi, phi_next);
+        // (the first source plane is z0 - 1, loaded at the first iteration; lanes without
+        // a source load a column of the lattice and drop it)
+        if (it == IT0 || it >= 4) {
+            if (it >= 4) kmom = plane_after(r + 1, kmom);
+            load_plane<ST>(in.mom, g.ld, plane * kmom, off_src, mom);
         }
-
         // ================= phase A =================
-        // ---- S3a: per-column partial sums of the curvature stencil (plane q) ----
-        // With w_i = w1(c_x) w1(c_y) w1(c_z), w1 = (1, 4, 1)/6, the stencil
-        // kappa = 3 sum_i w_i c_i . n(x + c_i) factorises into sums over one plane:
-        //   72 kappa(r) = C(r-1) + 4 C(r) + C(r+1) + E(r+1) - E(r-1),
-        //   C = sum_cy (1,4,1) (n_x(x+1, y+cy) - n_x(x-1, y+cy))
-        //     + sum_cx (1,4,1) (n_y(x+cx, y+1) - n_y(x+cx, y-1)),
-        //   E = sum_{cx,cy} (1,4,1)(1,4,1) n_z(x+cx, y+cy),
-        // so each source keeps k1 = C(r-1) + 4 C(r), k2 = C(r), e1 = E(r-1) and e2 = E(r)
-        // (E apart: it is of order 36 where C, a sum of differences, is small).
-        float kap = 0.f;
-        if constexpr (PH) {
-            if (it >= 2 && is_src) {
-                // plane q, written one iteration ago; entry 0 is the corner (x-1, y-1)
-                const float *nq = &sm.n[(it + 2) % 3][0][0] + sy * GX + sx;
-                const float *nyq = nq + NGEO, *nzq = nq + 2 * NGEO;
-                const float Cx = fmaf(4.0f, nq[GX + 2] - nq[GX], (nq[2] - nq[0]) + (nq[2 * GX + 2] - nq[2 * GX]));
-                const float Cy = fmaf(4.0f, nyq[2 * GX + 1] - nyq[1], (nyq[2 * GX] - nyq[0]) + (nyq[2 * GX + 2] - nyq[2]));
-                const float Em = fmaf(4.0f, nzq[1], nzq[0] + nzq[2]);
-                const float E0 = fmaf(4.0f, nzq[GX + 1], nzq[GX] + nzq[GX + 2]);
-                const float Ep = fmaf(4.0f, nzq[2 * GX + 1], nzq[2 * GX] + nzq[2 * GX + 2]);
-                const float C = Cx + Cy, E = fmaf(4.0f, E0, Em + Ep);
-                kap = (k1 + C) + (E - e1);
-                k1 = fmaf(4.0f, C, k2);
-                k2 = C;
-                e1 = e2;
-                e2 = E;
-            }
-        }
-
         // what the source's own column takes of its populations (used in phase B)
         float T0c, T1c, T2c, rpc;
         int32_t prest, pup, pdown;
@@ -576,26 +626,24 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             if constexpr (PH) {
                 const bool bnd = src_bnd_xy || (!g.per[2] && (r <= 0 || r >= g.nz - 1));
                 const float a = bnd ? 0.f : -sigma72 * kap;
-                const float *nr = &sm.n[(it + 1) % 3][0][0] + (sy + 1) * GX + (sx + 1);  // plane r
-                n0 = nr[0];
-                n1 = nr[NGEO];
-                n2 = nr[2 * NGEO];
-                const float *Gs = &sm.G[(it + 1) % 3][0][0] + sidx;  // plane r
+                n0 = own_n[0];
+                n1 = own_n[1];
+                n2 = own_n[2];
+                phis = own_phi;
                 if constexpr (VD) {
-                    Gx = Gs[0];
-                    Gy = Gs[NSRC];
-                    Gz = Gs[2 * NSRC];
+                    Gx = own_G[0];
+                    Gy = own_G[1];
+                    Gz = own_G[2];
                     sbnd = bnd;
                     F0 = a * Gx;
                     F1 = a * Gy;
                     F2 = a * Gz;
                 } else {
-                    const float ag = a * Gs[0];  // G = n (|G| + eps)
+                    const float ag = a * own_G[0];  // G = n (|G| + eps)
                     F0 = ag * n0;
                     F1 = ag * n1;
                     F2 = ag * n2;
                 }
-                phis = sm.phi[(it - 2) & 3][(sy + 2) * PX + (sx + 2)];
             }
 
             // ---- S4: post-collision populations of the source ----
@@ -753,16 +801,20 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             }
         }
 
-        // ---- S2, phase-A items ----
-        if constexpr (PH) if (it + 2 <= nit) {
-            if (item[0] >= 0) geometry_item(std::integral_constant<int, 0>{}, it);
-            if (VD && item[1] >= 0) geometry_item(std::integral_constant<int, 1>{}, it);
-        }
         __syncthreads();
 
         // ================= phase B =================
-        // ---- S2, phase-B items, before any destination work ----
-        if constexpr (PH && !VD) if (item[1] >= 0 && it + 2 <= nit) geometry_item(std::integral_constant<int, 1>{}, it);
+        // what the next iteration's source (plane p - 1) takes of the geometry at its own
+        // column (the slots are free for plane p + 1 from the next phase A on)
+        if constexpr (PH) {
+            const float *nq = &sm.n[(it + 1) & 1][0][0] + (sy + 1) * GX + (sx + 1);
+            const float *Gq = &sm.G[(it + 1) & 1][0][0] + sidx;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) own_n[k] = nq[k * NGEO];
+#pragma unroll
+            for (int k = 0; k < (VD ? 3 : 1); ++k) own_G[k] = Gq[k * NSRC];
+            own_phi = sm.phi[(it - 1) & 3][(sy + 2) * PX + (sx + 2)];
+        }
         const bool finish = it >= 4 && dst_wave;
         float m[10];
         int32_t phin;
@@ -868,15 +920,12 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         }
         // After the destinations' arithmetic and before any store of the iteration:
         // wait for the loads issued at its top (vmcnt 0; expcnt and lgkmcnt fields at
-        // their maxima, i.e. not waited for) and stage phi(p + 2) for the geometry of
-        // the next iteration (slot of plane p - 2, whose last readers, the sources of
-        // phase A, are done; phase B reads another).
+        // their maxima, i.e. not waited for).
         // Loads and stores share one in-order counter, and the stores are conditional,
         // so a wait placed after them could only be vmcnt(0) and would also wait until
         // every store of the iteration has been acknowledged.  Here the loads have had
         // nearly the whole iteration to arrive, and the stores drain during the next one.
         __builtin_amdgcn_s_waitcnt(0x0F70);
-        stage_phi(it + 2, phi_next);
         if (finish) {
             const int zd = r - 1;
             const bool z_image = !g.per[2] && (zd == 1 || zd == g.nz - 2);
@@ -925,7 +974,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 
 static_assert(sizeof(Geo) % alignof(Phys) == 0 && alignof(Geo) == alignof(Phys), "ph follows g directly");
 template <int ST, bool PH, bool VD, int ROWS>
-__global__ __launch_bounds__(Tile<ROWS>::NT) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
+__global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
                                                                int lz, int tiles_x, int tiles_y,
                                                                unsigned long long step_next) {
     __shared__ Smem<PH, VD, ROWS> sm;
@@ -939,7 +988,7 @@ __global__ __launch_bounds__(Tile<ROWS>::NT) void k_step_fused(Geo g, Phys ph, S
 // Several lattices in one launch: the work items of domain k are
 // [work_begin, work_begin + tiles * chunks); domains are sorted by work_begin.
 template <int ST, bool PH, bool VD, int ROWS>
-__global__ __launch_bounds__(Tile<ROWS>::NT) void k_step_fused_multi(const FusedDomain *__restrict__ doms, int ndom) {
+__global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(const FusedDomain *__restrict__ doms, int ndom) {
     __shared__ Smem<PH, VD, ROWS> sm;
     const int w = xcd_work_item(blockIdx.x, gridDim.x);
     int lo = 0, hi = ndom - 1;
@@ -1093,14 +1142,14 @@ template <int ST, bool PH, bool VD, int ROWS>
 void launch_one(unsigned blocks, hipStream_t s, const tslb_ctx *c, StateView in, StateView out, int lz, int tiles_x,
                 int tiles_y, unsigned long long sn) {
     using namespace fused;
-    hipLaunchKernelGGL((k_step_fused<ST, PH, VD, ROWS>), dim3(blocks), dim3(Tile<ROWS>::NT), 0, s, c->geo, c->phys,
+    hipLaunchKernelGGL((k_step_fused<ST, PH, VD, ROWS>), dim3(blocks), dim3(Tile<ROWS>::threads(PH)), 0, s, c->geo, c->phys,
                        c->scales, in, out, lz, tiles_x, tiles_y, sn);
 }
 
 template <int ST, bool PH, bool VD, int ROWS>
 void launch_multi(unsigned blocks, hipStream_t s, const FusedDomain *doms, int ndom) {
     using namespace fused;
-    hipLaunchKernelGGL((k_step_fused_multi<ST, PH, VD, ROWS>), dim3(blocks), dim3(Tile<ROWS>::NT), 0, s, doms, ndom);
+    hipLaunchKernelGGL((k_step_fused_multi<ST, PH, VD, ROWS>), dim3(blocks), dim3(Tile<ROWS>::threads(PH)), 0, s, doms, ndom);
 }
 
 }  // namespace
