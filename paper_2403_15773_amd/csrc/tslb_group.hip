@@ -103,7 +103,7 @@ int chunk_under_bound(int nz, int L) {
     return (nz + k - 1) / k;
 }
 
-// End time, in pipeline planes, of one launch whose work items take cost[i]
+// End time, in half planes, of one launch whose work items take cost[i] half
 // planes each: the items are split into eight contiguous ranges, one per XCD
 // (xcd_work_item), and the compute units of an XCD take their range's items
 // in order as they free up.
@@ -128,9 +128,11 @@ long long launch_end(const std::vector<int> &cost, int cus, std::vector<long lon
 
 // The chunk bound of launch class cl: every stepping member of the class
 // splits its z extent into chunks under one bound L, and the launch takes the
-// L whose simulated end time is earliest (a workgroup on a chunk of l planes
-// walks l + 6 pipeline planes, so long chunks recompute less, short ones leave
-// fewer compute units idle while the last items finish).  The choice is kept
+// L whose simulated end time is earliest (a workgroup walks its chunk and the
+// fill of its pipeline, so long chunks recompute less, short ones leave fewer
+// compute units idle while the last items finish).  Bounds below 8 planes are
+// tried while the items fit the device in two rounds: beyond that the fill, which
+// every round pays, outweighs them, and the items to simulate become many.  The choice is kept
 // until a member is admitted or leaves, or one of the class stops stepping.
 // The result of a step does not depend on the chunk length.
 int plan_chunk_bound(tslb_group *g, int cl) {
@@ -143,20 +145,25 @@ int plan_chunk_bound(tslb_group *g, int cl) {
         }
     if (now.empty()) return 64;
     if (now == g->plan_members[cl] && g->plan_bound[cl] > 0) return g->plan_bound[cl];
-    static const int kBounds[] = {8, 12, 16, 24, 32, 48, 64, 96, 128};
+    static const int kBounds[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
     std::vector<int> cost;
     std::vector<long long> heap;
     long long best = -1;
     int best_L = 64;
     for (int L : kBounds) {
+        if (L < 8) {
+            long long items = 0;
+            for (const tslb_ctx *c : now) items += fused_work_items(c, chunk_under_bound(c->geo.nz, L));
+            if (items > 2ll * cus) continue;
+        }
         cost.clear();
         for (const tslb_ctx *c : now) {
             const int nz = c->geo.nz, lz = chunk_under_bound(nz, L);
             const int chunks = (nz + lz - 1) / lz;
             const int tiles = fused_work_items(c, nz);  // one chunk of nz planes: the tile count
             for (int j = 0; j < chunks; ++j) {
-                const int planes = std::min(lz, nz - j * lz) + 6;
-                for (int t = 0; t < tiles; ++t) cost.push_back(planes);
+                const int walk = fused_walk2(c, std::min(lz, nz - j * lz));
+                for (int t = 0; t < tiles; ++t) cost.push_back(walk);
             }
         }
         const long long e = launch_end(cost, std::max(cus, 8), heap);

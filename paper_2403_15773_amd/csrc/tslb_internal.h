@@ -123,6 +123,9 @@ struct FusedPlan {
 FusedPlan fused_plan(const tslb_ctx *c);
 int fused_chunk(const tslb_ctx *c);
 int fused_rows(const tslb_ctx *c);
+// Cost of a chunk of lz planes for its workgroup, in half planes (the chunk and
+// the fill of the pipeline).
+int fused_walk2(const tslb_ctx *c, int lz);
 // Whether the 20-row tile serves ctx c (two components, equal densities).
 bool fused_wide_allowed(const tslb_ctx *c);
 // Describe one step of ctx c (in -> out) as a domain of a multi-domain launch

@@ -1033,26 +1033,34 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(co
 }  // namespace fused
 
 // Tile height and z planes per workgroup.  A workgroup on a chunk of lz planes
-// walks lz + 6 planes (the pipeline refills its rings), and the W work items of
-// a launch give each CU ceil(W / CUs) of them, so the cost of a plan is
-// ceil(W / CUs) (lz + 6) c, with c the time of one pipeline plane of a
-// workgroup: 1 for 16 rows and kWideCost for 20 rows (measured on the
-// 512 x 512 x 2048 jet: a 32 x 20 workgroup walks a plane in 1.18 times the
-// time of a 32 x 16 one and updates 1.25 times the columns).  Long chunks
-// recompute less halo, short ones keep every unit busy; ties go to the shorter
-// chunk, then to 16 rows.  Chunks are capped (kMaxChunk16, kMaxChunk20 planes):
+// walks lz planes and the fill of its pipeline, and the W work items of a launch
+// give each CU ceil(W / CUs) of them, so the cost of a plan is
+// ceil(W / CUs) (lz + fill) c, with c the time of one pipeline plane of a
+// workgroup: 1 for 16 rows and kWideCost for 20 rows.
+// fill: one round of workgroups takes 1.99 (lz + 6.6) us with two components and
+// 1.55 (lz + 4.5) with one (32^3 to 64^3 lattices, lz 1 to 8, launch included), of
+// which 6 and 3 are planes of the loop.  So the shortest chunks pay as long as
+// they fill idle CUs: 32^3 droplet 21.2 us a step at 4 planes, 15.3 at 1; 61 x 45 x
+// 83 box 23.2 at 4, 18.6 at 2; 40^3 vortex 13.2 at 4, 8.6 at 1.
+// kWideCost: 400 x 400 x 800 jet 2.83 us a plane on 16 rows, 3.47 on 20 (1.22);
+// 512 x 512 x 2048 jet 2.87 and 3.59 (1.25); 100 x 100 x 200 1.24.
+// Long chunks recompute less halo, short ones keep every unit busy; ties go to the
+// shorter chunk, then to 16 rows.  Chunks are capped at kMaxChunk planes:
 // workgroups that share halo columns run side by side, but over a long chunk
 // they drift apart in z and their shared halo planes leave L2 before the
 // neighbour reads them (HBM reads 1.48x the state at 2048 planes on a
-// 512 x 512 x 2048 lattice, against 1.06x at 64 on 128 x 128 x 512).  The caps
-// are measured on that lattice: 16-row tiles gained nothing beyond 128 planes,
-// 20-row tiles ran 1.6 % faster at 256 than at 128 and slower at 342 or 683.
-// 20 rows serve the two-component
-// step with equal densities; the one-component step (whose 16-row workgroups
-// fit twice in a CU's LDS) and the variable-density step take 16.  A height or
-// chunk length fixed with tslb_set_tile / tslb_set_kernel is taken as given.
-constexpr int kMaxChunk16 = 128, kMaxChunk20 = 256;
-constexpr double kWideCost = 1.18;
+// 512 x 512 x 2048 lattice, against 1.06x at 64 on 128 x 128 x 512).  On that
+// lattice 16 rows take 12.38 and 12.36 ms at 64 and 128 planes, 20 rows 12.50,
+// 12.54 and 12.79 at 64, 128 and 256; the step for 16-bit moments takes 13.95 ms
+// there at 128 planes and 13.77 at 256, so its cap on 20 rows is 256.
+// 20 rows serve the two-component step with equal densities; the one-component
+// and the variable-density step take 16.  A height or chunk length fixed with
+// tslb_set_tile / tslb_set_kernel is taken as given.
+constexpr int kMaxChunk = 128, kMaxChunkHalf20 = 256;
+constexpr double kWideCost = 1.22;
+
+// Planes a workgroup on a chunk of lz planes walks, doubled.
+int fused_walk2(const tslb_ctx *c, int lz) { return 2 * lz + (c->phase || c->storage != ST_FP32 ? 13 : 9); }
 
 bool fused_wide_allowed(const tslb_ctx *c) { return c->phase && !c->vd; }
 
@@ -1070,19 +1078,18 @@ double best_chunk(const tslb_ctx *c, int rows, int *lz_out) {
     const double f = rows == 16 ? 1.0 : kWideCost;
     auto cost_of = [&](int lz) {
         const long long w = tiles * ((nz + lz - 1) / lz);
-        return (double)((w + cus - 1) / cus) * (double)(lz + 6) * f;
+        return (double)((w + cus - 1) / cus) * (0.5 * fused_walk2(c, lz)) * f;
     };
     if (c->chunk_z > 0) {
         *lz_out = c->chunk_z;
         return cost_of(c->chunk_z);
     }
-    int best_lz = std::min(nz, 4);
+    int best_lz = 1;
     double best = -1.0;
     for (int k = 1; k <= nz; ++k) {  // k chunks of ceil(nz / k) planes
         const int lz = (nz + k - 1) / k;
-        if (lz < 4 && k > 1) break;
         if (k > 1 && lz == (nz + k - 2) / (k - 1)) continue;  // same length as k - 1 chunks
-        if (lz > (rows == 16 ? kMaxChunk16 : kMaxChunk20)) continue;
+        if (lz > (rows == 20 && c->storage != ST_FP32 ? kMaxChunkHalf20 : kMaxChunk)) continue;
         const double cost = cost_of(lz);
         if (best < 0 || cost <= best) {
             best = cost;
