@@ -275,18 +275,18 @@ int tslb_step_kernel_times(tslb_ctx *ctx, float *ms, int64_t cap, int64_t *count
 
 /* Select the step kernel (TSLB_KERNEL_*) and, for the fused kernel, the number
  * of z planes a workgroup marches through: chunk_z >= 1 fixes it, 0 (the
- * default) lets the library choose per lattice (at most 128 planes, 256 for
- * 16-bit moments on 20-row tiles, the length that minimises the rounds of
- * workgroups per compute unit times the planes each round walks, its chunk plus
- * the fill of the pipeline).  Both kernels compute the
- * same step up to rounding, and the fused result does not depend on chunk_z. */
+ * default) lets the library choose per lattice (at most 128 planes, the
+ * length that minimises the rounds of workgroups per compute unit times the
+ * planes each round walks, its chunk plus the fill of the pipeline).  Both
+ * kernels compute the same step up to rounding, and the fused result does not
+ * depend on chunk_z. */
 int tslb_set_kernel(tslb_ctx *ctx, int kernel, int chunk_z);
 
 /* Height of the fused step's tiles (workgroups of 32 x rows destination
  * columns): rows = 16 or 20 fixes it, 0 (the default) lets the library choose
  * per lattice together with the z chunk, by the same cost model (a 20-row
- * workgroup walks a plane in 1.22 times the time of a 16-row one and updates
- * 1.25 times the columns; the height that gives each compute unit the least
+ * workgroup walks a plane in 1.22 times the time of a 16-row one, 1.35 times
+ * with 16-bit moments, and updates 1.25 times the columns; the height that gives each compute unit the least
  * time wins).  20 rows serve the two-component step with equal densities only
  * (TSLB_E_INVAL otherwise); the result is bitwise the same at either height.
  * Not while the ctx is in a serving group (TSLB_E_STATE). */

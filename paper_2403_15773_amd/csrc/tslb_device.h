@@ -58,25 +58,12 @@ struct Scales {
 // the stress Q in binary16 (Q/U^2).
 enum { ST_FP32 = 0, ST_FP16 = 1, ST_BF16 = 2, ST_FP16Q = 3 };
 
-// Memory views.  A kernel that takes its state pointers from a table in memory
-// (the multi-lattice step) can access them as global_t pointers (G = true): the
-// compiler cannot tell otherwise that they address global memory and uses flat
-// instructions, which also hold up every LDS wait.  The typed view keeps more
-// plane addresses in scalar registers, so it pays only where those do not spill
-// (binary32 storage of the multi-lattice step).  Where the pointers are kernel
-// arguments the plain view (G = false) compiles better (the compiler infers
-// global itself).
+// Pointers to global memory.  Where a kernel takes its state pointers from a table
+// in memory (the multi-lattice step) the compiler cannot tell otherwise that they
+// address global memory and uses flat instructions, which also hold up every LDS
+// wait.
 template <class T>
 using global_t = __attribute__((address_space(1))) T;
-template <bool G, class T> struct MemView { using P = T *; };
-template <class T> struct MemView<true, T> { using P = global_t<T> *; };
-template <bool G, class T>
-__device__ __forceinline__ typename MemView<G, T>::P mem(T *p) {
-    if constexpr (G)
-        return (typename MemView<G, T>::P)p;
-    else
-        return p;
-}
 
 // binary32 -> bfloat16 bits, rounded to nearest even (a NaN stays a quiet NaN):
 // one hardware conversion on gfx950 (v_cvt_pk_bf16_f32).
@@ -138,21 +125,8 @@ __device__ __forceinline__ float load_moment(const void *mom, long long ld, int 
     }
 }
 
-// The same moment in two halves, so that a prefetch can be issued long before
-// its value is used: load_moment_bits returns the stored word (a 16-bit word
-// zero-extended), decode_moment turns it into what load_moment returns.
-template <int ST, bool G = false>
-__device__ __forceinline__ uint32_t load_moment_bits(const void *mom, long long ld, int p, long long id) {
-    if constexpr (ST == ST_FP32) {
-        return mem<G>((const uint32_t *)mom)[p * ld + id];
-    } else if constexpr (ST == ST_FP16Q) {
-        if (p < 4) return mem<G>((const uint32_t *)mom)[p * ld + id];
-        return mem<G>((const uint16_t *)((const float *)mom + 4 * ld))[(p - 4) * ld + id];
-    } else {
-        return mem<G>((const uint16_t *)mom)[p * ld + id];
-    }
-}
-
+// The value of a stored word of moment p (a 16-bit word zero-extended), for a
+// prefetch that is issued long before its value is used.
 template <int ST>
 __device__ __forceinline__ float decode_moment(uint32_t b, int p, const Scales &sc) {
     if constexpr (ST == ST_FP32) {
@@ -184,19 +158,19 @@ template <int ST> __device__ __forceinline__ uint16_t half_bits(float v, int p, 
         return __builtin_bit_cast(uint16_t, f16_of(s));
 }
 
-template <int ST, bool G = false>
+template <int ST>
 __device__ __forceinline__ void store_moment(void *mom, long long ld, int p, long long id, float v, const Scales &sc) {
     if constexpr (ST == ST_FP32) {
-        store_nt(&mem<G>((float *)mom)[p * ld + id], v);
+        store_nt(&((float *)mom)[p * ld + id], v);
     } else if constexpr (ST == ST_FP16Q) {
         if (p < 4)
-            store_nt(&mem<G>((float *)mom)[p * ld + id], v);
+            store_nt(&((float *)mom)[p * ld + id], v);
         else
-            store_nt(&mem<G>((_Float16 *)((float *)mom + 4 * ld) + (p - 4) * ld)[id], f16_of(v * sc.inv_s2));
+            store_nt(&((_Float16 *)((float *)mom + 4 * ld) + (p - 4) * ld)[id], f16_of(v * sc.inv_s2));
     } else if constexpr (ST == ST_FP16) {
-        store_nt(&mem<G>((_Float16 *)mom + p * ld)[id], f16_of(v * ((p >= 1 && p < 4) ? sc.inv_s1 : sc.inv_s2)));
+        store_nt(&((_Float16 *)mom + p * ld)[id], f16_of(v * ((p >= 1 && p < 4) ? sc.inv_s1 : sc.inv_s2)));
     } else {
-        store_nt(&mem<G>((uint16_t *)mom + p * ld)[id], bf16_bits(v * ((p >= 1 && p < 4) ? sc.inv_s1 : sc.inv_s2)));
+        store_nt(&((uint16_t *)mom + p * ld)[id], bf16_bits(v * ((p >= 1 && p < 4) ? sc.inv_s1 : sc.inv_s2)));
     }
 }
 

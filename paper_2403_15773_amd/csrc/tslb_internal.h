@@ -139,10 +139,6 @@ int fused_work_items(const tslb_ctx *c, int lz);
 // component count, density model and tile height).
 hipError_t launch_step_fused_multi(const FusedDomain *doms, int ndom, int total_work, int storage, bool phase,
                                    bool vd, int rows, hipStream_t s);
-// The same two launches for 16-bit storage (tslb_step_half.hip).
-hipError_t launch_step_half(const tslb_ctx *c, StateView in, StateView out, int lz, int64_t step_next, hipStream_t s);
-hipError_t launch_step_half_multi(const FusedDomain *doms, int ndom, int total_work, int storage, bool phase,
-                                  int rows, hipStream_t s);
 hipError_t launch_copy_probe(const void *src, void *dst, size_t bytes, hipStream_t s);
 hipError_t launch_diagnostics(const tslb_ctx *c, StateView st, const Scratch &sc, hipStream_t s);
 size_t diagnostics_blocks(const tslb_ctx *c);

@@ -1,6 +1,5 @@
 // Fused thread-safe LB step for gfx950: one kernel reads the raw moments and
 // phase field of step t once from HBM and writes those of step t+1 once.
-// (binary32 storage; tslb_step_half.hip is the step for 16-bit stored moments)
 //
 // Work decomposition.  A workgroup owns a 32 x 16 (or 32 x 20) tile of (x, y)
 // destination columns and marches through a chunk of z planes.  Its waves have
@@ -51,6 +50,14 @@
 //   destination: moments sum_i w_i H(c_i) t_i(x - c_i) as a tensor product of
 //            1-D three-point transforms written relative to the middle value, so
 //            the large isotropic part cancels before rounding.
+// 16-bit stored moments (FP16, BF16, FP16Q) keep another order of this arithmetic, the
+// one above the k-space exchange grew from: populations instead of the T are
+// exchanged, G comes from 13 pairs of neighbours, and sums carry their factors.  A
+// change of rounding in binary32 turns into other roundings of stored moments, and
+// those travel: ten steps of a jet with BF16 moments then differ by 5e-3 in the
+// stress, as much as from the exact result.  Waves, tiles and the LDS records are the
+// same.  It takes 30 % more vector instructions (128 x 128 x 512 jet, FP16, 207 us a
+// step; 248 with its geometry spread over the source waves).
 // Variable density and viscosity (VD): the velocity-based form of the phase-field
 // scheme for components of different density.  The stored rho' is then the
 // normalised pressure p*, the velocity terms of the rebuild take unit density,
@@ -188,6 +195,31 @@ __device__ __forceinline__ void xy_moments(const float t[9], float X[6]) {
     X[5] = b.m1;                       // 11
     X[4] = tr3_m0(y0.m2, y1.m2, y2.m2);  // 02
 }
+
+// The forms of the arithmetic that 16-bit stored moments keep (see the header): the
+// transforms with their factors multiplied out, and the weighted three-point sum
+// (1/6) m + (2/3) z + (1/6) p.
+__device__ __forceinline__ Tr3 tr3_scaled(float am, float a0, float ap) {
+    const float dm = am - a0, dp = ap - a0;
+    const float s = dm + dp;
+    Tr3 r;
+    r.m0 = fmaf(s, 1.0f / 6.0f, a0);
+    r.m1 = (dp - dm) * (1.0f / 6.0f);
+    r.m2 = s * (1.0f / 9.0f);
+    return r;
+}
+__device__ __forceinline__ void xy_moments_scaled(const float t[9], float X[6]) {
+    const Tr3 y0 = tr3_scaled(t[0], t[3], t[6]), y1 = tr3_scaled(t[1], t[4], t[7]), y2 = tr3_scaled(t[2], t[5], t[8]);
+    const Tr3 a = tr3_scaled(y0.m0, y1.m0, y2.m0);
+    X[0] = a.m0;
+    X[1] = a.m1;
+    X[3] = a.m2;
+    const Tr3 b = tr3_scaled(y0.m1, y1.m1, y2.m1);
+    X[2] = b.m0;
+    X[5] = b.m1;
+    X[4] = tr3_m0(y0.m2, y1.m2, y2.m2);
+}
+__device__ __forceinline__ float w1sum(float m, float z, float p) { return fmaf(z, 2.0f / 3.0f, (m + p) * (1.0f / 6.0f)); }
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
 // Work item w is assigned so that every XCD receives a contiguous range of w:
@@ -350,6 +382,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     for (int f = 0; f < 6; ++f) rules |= (uint32_t)ph.bc[f] << (4 * f);
     const uint32_t off_dst = (uint32_t)gxs + (uint32_t)g.nx * (uint32_t)gys;  // used where owned
 
+    constexpr bool H = ST != ST_FP32;  // the arithmetic of 16-bit stored moments
     const float omega1 = 1.0f - ph.omega;
     const float sigma72 = ph.sigma * (1.0f / 72.0f), gamma = ph.gamma;
 
@@ -359,6 +392,9 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     for (int k = 0; k < 3; ++k) ZA[k] = ZD[k] = ZQ[k] = 0.f;
 #pragma unroll
     for (int k = 0; k < 6; ++k) ZP[k] = 0.f;
+    float XA[6], XB[6], XC[6];  // with 16-bit moments: X(+1) and X(0) of plane r - 1, X(+1) of plane r
+#pragma unroll
+    for (int k = 0; k < 6; ++k) XA[k] = XB[k] = XC[k] = 0.f;
     int32_t PA = 0, PC = 0;    // phase partial sums of planes r - 1 and r
     float own_n[3] = {0.f, 0.f, 0.f}, own_G[3] = {0.f, 0.f, 0.f};  // n, |G| + eps (or G) and phi of the
     int32_t own_phi = 0;                                           // next source plane (own column)
@@ -478,6 +514,26 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 #pragma unroll
                 for (int j = 0; j < 12; ++j) q[j] = b[(j / 3 - 1) * PX + j % 3 - 1];
             };
+            // G of the middle column of q0 from 13 pairs of opposite neighbours (16-bit
+            // moments), planes p - 1, p and p + 1 in qm, q0 and qp
+            auto pair_gradient = [&](const int32_t *qm, const int32_t *q0, const int32_t *qp, float &Gx, float &Gy, float &Gz) {
+                Gx = Gy = Gz = 0.f;
+#pragma unroll
+                for (int cz = -1; cz <= 1; ++cz)
+#pragma unroll
+                    for (int cy = -1; cy <= 1; ++cy)
+#pragma unroll
+                        for (int cx = -1; cx <= 1; ++cx) {
+                            const bool lead = cx > 0 || (cx == 0 && (cy > 0 || (cy == 0 && cz > 0)));
+                            if (!lead) continue;
+                            const int32_t *qa = cz > 0 ? qp : (cz < 0 ? qm : q0), *qb = cz > 0 ? qm : (cz < 0 ? qp : q0);
+                            const float d = (float)(qa[4 + 3 * cy + cx] - qb[4 - 3 * cy - cx]);
+                            const float w = 3.0f * w27(cx, cy, cz) * kPhiUlp;
+                            if (cx) Gx = fmaf(w * cx, d, Gx);
+                            if (cy) Gy = fmaf(w * cy, d, Gy);
+                            if (cz) Gz = fmaf(w * cz, d, Gz);
+                        }
+            };
             // prologue: phase planes z0 - 3 .. z0 staged (slots 0 - 3) and the first taken in,
             // so that the first two iterations wait for no load
             int32_t v[NP];
@@ -509,15 +565,25 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
                     if (k && l + k * NGT >= NGP) break;  // whole waves have no further pair
-                    int32_t q[12];
+                    int32_t q[12], q0[12], qm[12];
                     read_phi(k, it + 1, q);
+                    if constexpr (H) {
+                        read_phi(k, it, q0);
+                        read_phi(k, it + 3, qm);
+                    }
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
-                        float Gx, Gy, Gz;
-                        absorb_plane(2 * k + j, q + 3 * j, Gx, Gy, Gz);
+                        float Gx, Gy, Gz, den, inv;
                         // hardware square root (1 ulp) and a refined reciprocal: |G| + eps >= eps
-                        const float den = fmaf(__builtin_amdgcn_sqrtf(fmaf(Gx, Gx, fmaf(Gy, Gy, Gz * Gz))), kS, eps);
-                        const float inv = recip(den) * kS;
+                        if constexpr (H) {
+                            pair_gradient(qm + 3 * j, q0 + 3 * j, q + 3 * j, Gx, Gy, Gz);
+                            den = __builtin_amdgcn_sqrtf(fmaf(Gx, Gx, fmaf(Gy, Gy, Gz * Gz))) + eps;
+                            inv = recip(den);
+                        } else {
+                            absorb_plane(2 * k + j, q + 3 * j, Gx, Gy, Gz);
+                            den = fmaf(__builtin_amdgcn_sqrtf(fmaf(Gx, Gx, fmaf(Gy, Gy, Gz * Gz))), kS, eps);
+                            inv = recip(den) * kS;
+                        }
                         if (l + k * NGT < NGP) {
                             const int i = gi[k] + j * GX, si = gs[k] + j * SX;
                             sm.n[it & 1][0][i] = Gx * inv;
@@ -560,11 +626,23 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                             ny[j][i] = by[j * GX + i];
                             nz[j][i] = bz[j * GX + i];
                         }
-                        e[j] = fmaf(4.0f, nz[j][1], nz[j][0] + nz[j][2]);
+                        e[j] = H ? w1sum(nz[j][0], nz[j][1], nz[j][2]) : fmaf(4.0f, nz[j][1], nz[j][0] + nz[j][2]);
                     }
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         const int m = 2 * k + j, si = cs[k] + j * SX;
+                        if constexpr (H) {  // kappa itself, its weights multiplied out
+                            const float C = w1sum(D[j], D[j + 1], D[j + 2]) +
+                                            w1sum(ny[j + 2][0] - ny[j][0], ny[j + 2][1] - ny[j][1], ny[j + 2][2] - ny[j][2]);
+                            const float E = w1sum(e[j], e[j + 1], e[j + 2]);
+                            const float kap = 0.5f * (w1sum(k1[m], k2[m], C) + (E - e1[m]));
+                            k1[m] = k2[m];
+                            k2[m] = C;
+                            e1[m] = e2[m];
+                            e2[m] = E;
+                            if (l + k * NGT < NCP) sm.kap[si] = kap;
+                            continue;
+                        }
                         const float Cx = fmaf(4.0f, D[j + 1], D[j] + D[j + 2]);
                         const float Cy = fmaf(4.0f, ny[j + 2][1] - ny[j][1], (ny[j + 2][0] - ny[j][0]) + (ny[j + 2][2] - ny[j][2]));
                         const float C = Cx + Cy, E = fmaf(4.0f, e[j + 1], e[j] + e[j + 2]);
@@ -599,11 +677,15 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         float kap = 0.f;
         if constexpr (PH) kap = sm.kap[sidx];  // read ahead of the loads' address work
         // moments of source plane r + 1 for the next iteration
-        float mom_cur[10];
+        float mom_cur[10], rho_cur = 0.f;
+        if constexpr (ST == ST_FP16) {  // 1 + rho' with one rounding
+            rho_cur = fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)mom[0]), sc.s2, 1.0f);
+            __asm__ volatile("" : "+v"(rho_cur));
+        }
 #pragma unroll
         for (int k = 0; k < 10; ++k) {
             mom_cur[k] = decode_moment<ST>(mom[k], k, sc);
-            if (!VD && k >= 4) mom_cur[k] *= omega1;  // (1 - omega) Q
+            if (!VD && !H && k >= 4) mom_cur[k] *= omega1;  // (1 - omega) Q
             // formed before the loads below, which then reuse the words' registers
             __asm__ volatile("" : "+v"(mom_cur[k]));
         }
@@ -625,7 +707,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             int32_t phis = 0;
             if constexpr (PH) {
                 const bool bnd = src_bnd_xy || (!g.per[2] && (r <= 0 || r >= g.nz - 1));
-                const float a = bnd ? 0.f : -sigma72 * kap;
+                const float a = bnd ? 0.f : -(H ? ph.sigma : sigma72) * kap;
                 n0 = own_n[0];
                 n1 = own_n[1];
                 n2 = own_n[2];
@@ -670,10 +752,104 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 #pragma unroll
                 for (int k = 4; k < 10; ++k) mom_cur[k] *= om1;
             }
-            const float rho = VD ? 1.0f : 1.0f + rp;  // density of the velocity terms
+            const float rho = VD ? 1.0f : ST == ST_FP16 ? rho_cur : 1.0f + rp;  // density of the velocity terms
+            float u0 = mom_cur[1], u1 = mom_cur[2], u2 = mom_cur[3];
+            vec4 *rec = (vec4 *)&sm.xch[sidx][0];
+            rpc = rp;
+            if constexpr (H) {
+                // populations of c_z = -1, 0, +1 in place of the three T
+#pragma clang fp contract(fast)
+                float tm[9], t0[9], tp[9];
+                const float inv = recip(rho);
+                const float hF = 0.5f * inv, qF = 0.25f * inv;
+                u0 = fmaf(hF, F0, u0);
+                u1 = fmaf(hF, F1, u1);
+                u2 = fmaf(hF, F2, u2);
+                const float Pxx = fmaf(qF * F0, F0, mom_cur[4]), Pyy = fmaf(qF * F1, F1, mom_cur[5]);
+                const float Pzz = fmaf(qF * F2, F2, mom_cur[6]), Pxy = fmaf(qF * F0, F1, mom_cur[7]);
+                const float Pxz = fmaf(qF * F0, F2, mom_cur[8]), Pyz = fmaf(qF * F1, F2, mom_cur[9]);
+                // Hermite coefficients, pre-scaled: t(c) = K0 + sum K1 c + ... (see header)
+                const float Jx = fmaf(rho, u0, 0.5f * F0), Jy = fmaf(rho, u1, 0.5f * F1), Jz = fmaf(rho, u2, 0.5f * F2);
+                const float mxx = omega1 * Pxx, myy = omega1 * Pyy, mzz = omega1 * Pzz;
+                const float mxy = omega1 * Pxy, mxz = omega1 * Pxz, myz = omega1 * Pyz;
+                const float ru0 = rho * u0, ru1 = rho * u1, ru2 = rho * u2;
+                const float a2xx = fmaf(ru0, u0, mxx) + u0 * F0;
+                const float a2yy = fmaf(ru1, u1, myy) + u1 * F1;
+                const float a2zz = fmaf(ru2, u2, mzz) + u2 * F2;
+                const float a2xy = fmaf(ru0, u1, mxy) + 0.5f * (u0 * F1 + F0 * u1);
+                const float a2xz = fmaf(ru0, u2, mxz) + 0.5f * (u0 * F2 + F0 * u2);
+                const float a2yz = fmaf(ru1, u2, myz) + 0.5f * (u1 * F2 + F1 * u2);
+                // a3_aab = u_a (rho u_a u_b + 2 m_ab) + u_b m_aa
+                const float a3xxy = fmaf(u0, fmaf(ru0, u1, 2.0f * mxy), u1 * mxx);
+                const float a3xxz = fmaf(u0, fmaf(ru0, u2, 2.0f * mxz), u2 * mxx);
+                const float a3yyx = fmaf(u1, fmaf(ru1, u0, 2.0f * mxy), u0 * myy);
+                const float a3yyz = fmaf(u1, fmaf(ru1, u2, 2.0f * myz), u2 * myy);
+                const float a3zzx = fmaf(u2, fmaf(ru2, u0, 2.0f * mxz), u0 * mzz);
+                const float a3zzy = fmaf(u2, fmaf(ru2, u1, 2.0f * myz), u1 * mzz);
+                const float a3xyz = fmaf(ru0 * u1, u2, fmaf(u0, myz, fmaf(u1, mxz, u2 * mxy)));
+                // The scale factors of the coefficients (3 J, 4.5 a2_aa, 9 a2_ab, 13.5 a3_aab,
+                // 27 a3_xyz) are folded into the constants of the multiply-adds that take
+                // a coefficient as a slope or curvature term; only the five that enter as
+                // an addend are scaled explicitly.
+                const float K1y = 3.0f * Jy, K1z = 3.0f * Jz;
+                const float K2yy = 4.5f * a2yy, K2zz = 4.5f * a2zz, K2yz = 9.0f * a2yz;
+                // t = T0 + cz T1 + h(cz) T2; T0 = U0 + cy U1 + h(cy) U2 (per cx), etc.
+                float U0[3], U1[3], V0[3], W0[3];
+                {   // U0 = quad3(0, 3 Jx, 4.5 a2xx): tau = t - rho'
+                    const float m = 3.0f * a2xx;
+                    U0[1] = -1.5f * a2xx;
+                    U0[0] = fmaf(-3.0f, Jx, m);
+                    U0[2] = fmaf(3.0f, Jx, m);
+                }
+                {   // U1 = quad3(3 Jy, 9 a2xy, 13.5 a3xxy)
+                    const float m = fmaf(9.0f, a3xxy, K1y);
+                    U1[1] = fmaf(-4.5f, a3xxy, K1y);
+                    U1[0] = fmaf(-9.0f, a2xy, m);
+                    U1[2] = fmaf(9.0f, a2xy, m);
+                }
+                {   // V0 = quad3(3 Jz, 9 a2xz, 13.5 a3xxz)
+                    const float m = fmaf(9.0f, a3xxz, K1z);
+                    V0[1] = fmaf(-4.5f, a3xxz, K1z);
+                    V0[0] = fmaf(-9.0f, a2xz, m);
+                    V0[2] = fmaf(9.0f, a2xz, m);
+                }
+                W0[0] = fmaf(-13.5f, a3zzx, K2zz);
+                W0[1] = K2zz;
+                W0[2] = fmaf(13.5f, a3zzx, K2zz);
+#pragma unroll
+                for (int ix = 0; ix < 3; ++ix) {
+                    const float cx = (float)(ix - 1);
+                    const float U2 = ix == 1 ? K2yy : fmaf(13.5f * cx, a3yyx, K2yy);  // linear in cx
+                    const float V1 = ix == 1 ? K2yz : fmaf(27.0f * cx, a3xyz, K2yz);
+                    float T0[3], T1[3], T2[3];
+                    quad3(U0[ix], U1[ix], U2, T0[0], T0[1], T0[2]);
+                    {   // T1 = quad3(V0, V1, 13.5 a3yyz)
+                        const float m = fmaf(9.0f, a3yyz, V0[ix]);
+                        T1[1] = fmaf(-4.5f, a3yyz, V0[ix]);
+                        T1[0] = m - V1;
+                        T1[2] = m + V1;
+                    }
+                    T2[0] = fmaf(-13.5f, a3zzy, W0[ix]);
+                    T2[1] = W0[ix];
+                    T2[2] = fmaf(13.5f, a3zzy, W0[ix]);
+#pragma unroll
+                    for (int iy = 0; iy < 3; ++iy) {
+                        const int k = ix + 3 * iy;
+                        const float mid = fmaf(T2[iy], 2.0f / 3.0f, T0[iy]);
+                        t0[k] = fmaf(T2[iy], -1.0f / 3.0f, T0[iy]);
+                        tm[k] = mid - T1[iy];
+                        tp[k] = mid + T1[iy];
+                    }
+                }
+                T0c = tm[4];
+                T1c = t0[4];
+                T2c = tp[4];
+#pragma unroll
+                for (int k = 0; k < 9; ++k)
+                    if (k != 4) rec[xy_slot(k % 3 - 1, k / 3 - 1)] = vec4{tm[k], t0[k], tp[k], rp};
+            } else {
             // m = (1 - omega) P and a2 of the header, with g = F/rho, v = ubar + g, J = rho v:
             //   a2_ab = J_a v_b + (1 - omega) Q_ab - (omega/4) F_a g_b
-            float u0 = mom_cur[1], u1 = mom_cur[2], u2 = mom_cur[3];
             float mxx = mom_cur[4], myy = mom_cur[5], mzz = mom_cur[6], mxy = mom_cur[7], mxz = mom_cur[8],
                   myz = mom_cur[9];
             float Jx, Jy, Jz, a2xx, a2yy, a2zz, a2xy, a2xz, a2yz;
@@ -750,8 +926,6 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             W0[0] = fmaf(-13.5f, a3zzx, K2zz);
             W0[1] = K2zz;
             W0[2] = fmaf(13.5f, a3zzx, K2zz);
-            vec4 *rec = (vec4 *)&sm.xch[sidx][0];
-            rpc = rp;
 #pragma unroll
             for (int ix = 0; ix < 3; ++ix) {
                 const float cx = (float)(ix - 1);
@@ -779,6 +953,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                         rec[xy_slot(ix - 1, iy - 1)] = vec4{T0[iy], T1[iy], T2[iy], rp};
                     }
                 }
+            }
             }
             if constexpr (PH) {
                 // phase: base to every axis neighbour, +-a_e along +-e, phi - 6 base stays
@@ -832,19 +1007,58 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                     if (!cx && !cy) continue;
                     const int k = (cx + 1) + 3 * (cy + 1);
                     const vec4 v = ((const vec4 *)&xc[(1 - cy) * SX + (1 - cx)][0])[xy_slot(cx, cy)];
-                    t0[k] = v.x + (v.w - rpc);
-                    t1[k] = v.y;
-                    t2[k] = v.z;
+                    const float drp = v.w - rpc;
+                    t0[k] = v.x + drp;
+                    t1[k] = H ? v.y + drp : v.y;
+                    t2[k] = H ? v.z + drp : v.z;
                 }
             float X0[6], X1[6], X2[6];
-            xy_moments(t0, X0);
-            xy_moments(t1, X1);
-            xy_moments(t2, X2);
+            if constexpr (H) {
+                xy_moments_scaled(t0, X0);
+                xy_moments_scaled(t1, X1);
+                xy_moments_scaled(t2, X2);
+            } else {
+                xy_moments(t0, X0);
+                xy_moments(t1, X1);
+                xy_moments(t2, X2);
+            }
             int32_t pin = 0;
             if constexpr (PH) {
                 const int32_t(*xi)[T::REC] = (const int32_t(*)[T::REC])xc;
                 pin = xi[SX][32] + xi[SX + 2][33] + xi[1][34] + xi[2 * SX + 1][35];
             }
+            float dr = 0.f;
+            if constexpr (H) {
+                // X0, X1, X2 are the sums of the populations of c_z = -1, 0, +1
+#pragma clang fp contract(fast)
+                X0[0] += rpc;
+                X1[0] += rpc;
+                X2[0] += rpc;
+                const Tr3 m00 = tr3_scaled(X0[0], XB[0], XA[0]);  // rho', j_z, H_zz
+                const Tr3 m10 = tr3_scaled(X0[1], XB[1], XA[1]);  // j_x, H_xz
+                const Tr3 m01 = tr3_scaled(X0[2], XB[2], XA[2]);  // j_y, H_yz
+                const float Hxx = tr3_m0(X0[3], XB[3], XA[3]);
+                const float Hyy = tr3_m0(X0[4], XB[4], XA[4]);
+                const float Hxy = tr3_m0(X0[5], XB[5], XA[5]);
+                const float jx = m10.m0, jy = m01.m0, jz = m00.m1;
+                const float inv = recip(1.0f + m00.m0);
+                m[0] = m00.m0;
+                m[1] = jx * inv;
+                m[2] = jy * inv;
+                m[3] = jz * inv;
+                m[4] = fmaf(-m[1], jx, Hxx);
+                m[5] = fmaf(-m[2], jy, Hyy);
+                m[6] = fmaf(-m[3], jz, m00.m2);
+                m[7] = fmaf(-m[1], jy, Hxy);
+                m[8] = fmaf(-m[1], jz, m10.m1);
+                m[9] = fmaf(-m[2], jz, m01.m1);
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    XA[k] = XC[k];
+                    XB[k] = X1[k];
+                    XC[k] = X2[k];
+                }
+            } else {
             // The populations of c_z = -1, 0, +1 sum to M, Z, P (X = X0 + c_z X1 +
             // (c_z^2 - 1/3) X2) and belong to planes r - 1, r, r + 1.  Kept for the
             // plane above: P (ZP); for the plane r itself, which still lacks the M of
@@ -862,7 +1076,6 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             float M[6];
 #pragma unroll
             for (int k = 0; k < 6; ++k) M[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) - X1[k];
-            float dr = 0.f;
             if constexpr (VD)
                 dr = rpc - ZR;
             else
@@ -888,6 +1101,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             m[7] = fmaf(-m[1], jy, Hxy);
             m[8] = fmaf(-m[1], jz, Hxz);
             m[9] = fmaf(-m[2], jz, Hyz);
+            }
             // streamed phase, held to the clamp range (a stable run never reaches it)
             phin = PH ? phi_clamp(PA + pdown) : 0;
 #pragma unroll
@@ -897,6 +1111,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 PA = PC + prest + pin;
                 PC = pup;
             }
+            if constexpr (!H) {
 #pragma unroll
             for (int k = 0; k < 6; ++k) __asm__ volatile("" : "+v"(X0[k]), "+v"(X2[k]));
 #pragma unroll
@@ -917,6 +1132,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 ZR = rpc;
             else
                 ZP[0] += rpc;
+            }
         }
         // After the destinations' arithmetic and before any store of the iteration:
         // wait for the loads issued at its top (vmcnt 0; expcnt and lgkmcnt fields at
@@ -1005,10 +1221,7 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(co
     // inside the plane loop (the loads sit in conditional code, so the compiler
     // does not hoist them), together with the 64-bit products derived from them;
     // copied as a whole, the record stays in scratch memory.  Field by field, the
-    // step compiles to the same loop as the single-lattice kernel.  The state is
-    // accessed through global-address-space pointers for binary32 storage only:
-    // for 16-bit storage that view spills scalar registers, and the flat
-    // instructions cost less.
+    // step compiles to the same loop as the single-lattice kernel.
     Geo g;
     g.nx = d.g.nx; g.ny = d.g.ny; g.nz = d.g.nz;
     g.per[0] = d.g.per[0]; g.per[1] = d.g.per[1]; g.per[2] = d.g.per[2];
@@ -1051,16 +1264,17 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(co
 // neighbour reads them (HBM reads 1.48x the state at 2048 planes on a
 // 512 x 512 x 2048 lattice, against 1.06x at 64 on 128 x 128 x 512).  On that
 // lattice 16 rows take 12.38 and 12.36 ms at 64 and 128 planes, 20 rows 12.50,
-// 12.54 and 12.79 at 64, 128 and 256; the step for 16-bit moments takes 13.95 ms
-// there at 128 planes and 13.77 at 256, so its cap on 20 rows is 256.
+// 12.54 and 12.79 at 64, 128 and 256.
+// 16-bit moments: 20 rows cost 1.31 (512 x 512 x 2048) to 1.48 (200 x 200 x 400), since
+// their geometry, four waves' work there, is the longest chain of phase A.
 // 20 rows serve the two-component step with equal densities; the one-component
 // and the variable-density step take 16.  A height or chunk length fixed with
 // tslb_set_tile / tslb_set_kernel is taken as given.
-constexpr int kMaxChunk = 128, kMaxChunkHalf20 = 256;
-constexpr double kWideCost = 1.22;
+constexpr int kMaxChunk = 128;
+constexpr double kWideCost = 1.22, kWideCostHalf = 1.35;
 
 // Planes a workgroup on a chunk of lz planes walks, doubled.
-int fused_walk2(const tslb_ctx *c, int lz) { return 2 * lz + (c->phase || c->storage != ST_FP32 ? 13 : 9); }
+int fused_walk2(const tslb_ctx *c, int lz) { return 2 * lz + (c->phase ? 13 : 9); }
 
 bool fused_wide_allowed(const tslb_ctx *c) { return c->phase && !c->vd; }
 
@@ -1075,7 +1289,7 @@ double best_chunk(const tslb_ctx *c, int rows, int *lz_out) {
     const long long tiles = tiles_of(c, rows);
     const long long cus = std::max(1, c->cu_count);
     const int nz = c->geo.nz;
-    const double f = rows == 16 ? 1.0 : kWideCost;
+    const double f = rows == 16 ? 1.0 : c->storage == ST_FP32 ? kWideCost : kWideCostHalf;
     auto cost_of = [&](int lz) {
         const long long w = tiles * ((nz + lz - 1) / lz);
         return (double)((w + cus - 1) / cus) * (0.5 * fused_walk2(c, lz)) * f;
@@ -1089,7 +1303,7 @@ double best_chunk(const tslb_ctx *c, int rows, int *lz_out) {
     for (int k = 1; k <= nz; ++k) {  // k chunks of ceil(nz / k) planes
         const int lz = (nz + k - 1) / k;
         if (k > 1 && lz == (nz + k - 2) / (k - 1)) continue;  // same length as k - 1 chunks
-        if (lz > (rows == 20 && c->storage != ST_FP32 ? kMaxChunkHalf20 : kMaxChunk)) continue;
+        if (lz > kMaxChunk) continue;
         const double cost = cost_of(lz);
         if (best < 0 || cost <= best) {
             best = cost;
@@ -1163,7 +1377,6 @@ void launch_multi(unsigned blocks, hipStream_t s, const FusedDomain *doms, int n
 
 hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int lz, int64_t step_next,
                              hipStream_t s) {
-    if (c->storage != ST_FP32) return launch_step_half(c, in, out, lz, step_next, s);
     const int rows = fused_rows(c);
     const int tiles_x = (c->geo.nx + fused::Tile<16>::TX - 1) / fused::Tile<16>::TX;
     const int tiles_y = (c->geo.ny + rows - 1) / rows;
@@ -1175,32 +1388,55 @@ hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int
         launch_one<ST_FP32, true, true, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
         return hipGetLastError();
     }
-    if (!c->phase)
-        launch_one<ST_FP32, false, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
-    else if (rows == 20)
-        launch_one<ST_FP32, true, false, 20>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
-    else
-        launch_one<ST_FP32, true, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
+#define TSLB_FUSED_CASE(ST)                                                                            \
+    case ST:                                                                                           \
+        if (!c->phase)                                                                                 \
+            launch_one<ST, false, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);         \
+        else if (rows == 20)                                                                           \
+            launch_one<ST, true, false, 20>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
+        else                                                                                           \
+            launch_one<ST, true, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
+        break;
+    switch (c->storage) {
+        TSLB_FUSED_CASE(ST_FP32)
+        TSLB_FUSED_CASE(ST_FP16)
+        TSLB_FUSED_CASE(ST_BF16)
+        TSLB_FUSED_CASE(ST_FP16Q)
+    default:
+        return hipErrorInvalidValue;
+    }
+#undef TSLB_FUSED_CASE
     return hipGetLastError();
 }
 
 hipError_t launch_step_fused_multi(const FusedDomain *doms, int ndom, int total_work, int storage, bool phase,
                                    bool vd, int rows, hipStream_t s) {
     if (ndom <= 0 || total_work <= 0) return hipSuccess;
-    if (storage != ST_FP32) return vd ? hipErrorInvalidValue : launch_step_half_multi(doms, ndom, total_work, storage, phase, rows, s);
     const unsigned blocks = (unsigned)total_work;
     if (vd) {
-        if (!phase || rows != 16) return hipErrorInvalidValue;
+        if (!phase || rows != 16 || storage != ST_FP32) return hipErrorInvalidValue;
         launch_multi<ST_FP32, true, true, 16>(blocks, s, doms, ndom);
         return hipGetLastError();
     }
     if (rows != 16 && (rows != 20 || !phase)) return hipErrorInvalidValue;
-    if (!phase)
-        launch_multi<ST_FP32, false, false, 16>(blocks, s, doms, ndom);
-    else if (rows == 20)
-        launch_multi<ST_FP32, true, false, 20>(blocks, s, doms, ndom);
-    else
-        launch_multi<ST_FP32, true, false, 16>(blocks, s, doms, ndom);
+#define TSLB_MULTI_CASE(ST)                                                                            \
+    case ST:                                                                                           \
+        if (!phase)                                                                                    \
+            launch_multi<ST, false, false, 16>(blocks, s, doms, ndom);                                 \
+        else if (rows == 20)                                                                           \
+            launch_multi<ST, true, false, 20>(blocks, s, doms, ndom);                                  \
+        else                                                                                           \
+            launch_multi<ST, true, false, 16>(blocks, s, doms, ndom);                                  \
+        break;
+    switch (storage) {
+        TSLB_MULTI_CASE(ST_FP32)
+        TSLB_MULTI_CASE(ST_FP16)
+        TSLB_MULTI_CASE(ST_BF16)
+        TSLB_MULTI_CASE(ST_FP16Q)
+    default:
+        return hipErrorInvalidValue;
+    }
+#undef TSLB_MULTI_CASE
     return hipGetLastError();
 }
 
