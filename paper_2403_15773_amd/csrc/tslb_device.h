@@ -141,9 +141,8 @@ __device__ __forceinline__ float decode_moment(uint32_t b, int p, const Scales &
     }
 }
 
-// Stores of a new state carry the non-temporal hint: the fused step never reads
-// back what it writes, and lines written without the hint take L2 capacity from
-// the halo lines that its neighbouring workgroups read again.
+// A store with the non-temporal hint, for states written off the fused step (which
+// chooses by lattice).
 template <class T, class P>
 __device__ __forceinline__ void store_nt(P ptr, T v) {
     __builtin_nontemporal_store(v, ptr);

@@ -319,6 +319,10 @@ int tslb_group_poll(tslb_group *g, tslb_ctx **done, int32_t cap, int32_t *ndone)
     int nrec = 0;
     // one launch per class (storage type, component count, tile height; variable density) present
     int first[kClasses] = {}, count[kClasses] = {}, work[kClasses] = {};
+    long long stream[kClasses] = {};  // bytes stored with the non-temporal hint less those without
+    size_t bytes = 0;  // of the states that the members' launches write
+    for (const tslb_group::Member &m : g->members)
+        if (m.remaining > 0) bytes += m.ctx->buffer_bytes;
     for (int cl = 0; cl < kClasses; ++cl) {
         first[cl] = nrec;
         const int bound = plan_chunk_bound(g, cl);
@@ -328,6 +332,7 @@ int tslb_group_poll(tslb_group *g, tslb_ctx **done, int32_t cap, int32_t *ndone)
             h[nrec] = fused_domain(c, c->buf[c->cur], c->buf[c->cur ^ 1], c->step + 1, work[cl],
                                    chunk_under_bound(c->geo.nz, bound));
             work[cl] += h[nrec].work_count;
+            stream[cl] += (fused_stream_stores(c, bytes) ? 1 : -1) * (long long)c->buffer_bytes;
             ++nrec;
             ++count[cl];
         }
@@ -340,7 +345,7 @@ int tslb_group_poll(tslb_group *g, tslb_ctx **done, int32_t cap, int32_t *ndone)
             GHIP_TRY(g, launch_step_fused_multi(g->d_tab[slot] + first[cl], count[cl], work[cl],
                                                 cl == kClassVD ? (int)ST_FP32 : cl / 3,
                                                 cl == kClassVD || cl % 3 != 0, cl == kClassVD,
-                                                cl != kClassVD && cl % 3 == 2 ? 20 : 16, g->stream));
+                                                cl != kClassVD && cl % 3 == 2 ? 20 : 16, stream[cl] >= 0, g->stream));
     GHIP_TRY(g, hipEventRecord(g->ev[slot], g->stream));
     g->slot_launch[slot] = id;
     g->launches = id + 1;

@@ -133,12 +133,15 @@ bool fused_wide_allowed(const tslb_ctx *c);
 // lattice's own choice).
 FusedDomain fused_domain(const tslb_ctx *c, StateView in, StateView out, int64_t step_next, int work_begin,
                          int lz = 0);
+// Whether the fused step of ctx c stores with the non-temporal hint, in a launch
+// that writes launch_bytes in all.
+bool fused_stream_stores(const tslb_ctx *c, size_t launch_bytes);
 // Work items of one fused step of ctx c with z chunk lz.
 int fused_work_items(const tslb_ctx *c, int lz);
 // One fused step of every domain of a device table (all of one storage type,
 // component count, density model and tile height).
 hipError_t launch_step_fused_multi(const FusedDomain *doms, int ndom, int total_work, int storage, bool phase,
-                                   bool vd, int rows, hipStream_t s);
+                                   bool vd, int rows, bool nt, hipStream_t s);
 hipError_t launch_copy_probe(const void *src, void *dst, size_t bytes, hipStream_t s);
 hipError_t launch_diagnostics(const tslb_ctx *c, StateView st, const Scratch &sc, hipStream_t s);
 size_t diagnostics_blocks(const tslb_ctx *c);

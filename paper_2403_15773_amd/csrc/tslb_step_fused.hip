@@ -274,32 +274,39 @@ __device__ __forceinline__ void load_plane(const void *mom, long long ld, long l
     }
 }
 
-template <int ST>
-__device__ __forceinline__ void store_plane(void *mom, long long ld, long long zoff, uint32_t off, const float m[10],
-                                            const Scales &sc) {
-    global_t<char> *q = (global_t<char> *)mom + moment_size<ST>(0) * zoff;
+// One word of a new state: with the non-temporal hint or without (fused_stream_stores;
+// a template parameter, since the choice at run time cost 1 to 3 % of a step).
+template <bool NT, class T> __device__ __forceinline__ void store_word(global_t<char> *q, T v) {
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, (global_t<T> *)q);
+    else
+        *(global_t<T> *)q = v;
+}
+
+template <int ST, bool PH, bool NT>
+__device__ __forceinline__ void store_plane(const StateView &out, long long ld, long long zoff, uint32_t off,
+                                               const float m[10], int32_t phi, const Scales &sc) {
+    global_t<char> *q = (global_t<char> *)out.mom + moment_size<ST>(0) * zoff;
     uint32_t o = lane_offset(off * moment_size<ST>(0));
 #pragma unroll
     for (int p = 0; p < 10; ++p) {
         const int sz = moment_size<ST>(p);
         q = uniform(q);
         if (sz == 4)
-            store_nt((global_t<float> *)(q + o), m[p]);
+            store_word<NT>(q + o, m[p]);
         else
-            store_nt((global_t<uint16_t> *)(q + o), half_bits<ST>(m[p], p, sc));
+            store_word<NT>(q + o, half_bits<ST>(m[p], p, sc));
         q += sz * ld;
         if (p < 9 && moment_size<ST>(p + 1) != sz) {
             q -= (sz - moment_size<ST>(p + 1)) * zoff;
             o = lane_offset(off * moment_size<ST>(p + 1));
         }
     }
+    if constexpr (PH) {
+        q = uniform((global_t<char> *)out.phi + 4 * zoff);
+        store_word<NT>(q + lane_offset(off * 4u), phi);
+    }
 }
-
-__device__ __forceinline__ void store_phi(int32_t *phi, long long zoff, uint32_t off, int32_t v) {
-    global_t<char> *q = uniform((global_t<char> *)phi + 4 * zoff);
-    store_nt((global_t<int32_t> *)(q + lane_offset(off * 4u)), v);
-}
-
 // The lattice's parameters in memory: what only the inlet rule needs is read where
 // an inlet node is written (loaded at kernel entry it would sit in scalar registers
 // through the whole loop).
@@ -309,7 +316,7 @@ using PhysMem = const __attribute__((address_space(4))) Phys *;
 // MULTI marks the multi-lattice kernel's instantiation: it keeps that kernel's
 // copy of the step apart from the single-lattice kernel's, whose code is
 // otherwise changed (and slowed) by the second user of the same instantiation.
-template <int ST, bool PH, bool MULTI, bool VD, int ROWS>
+template <int ST, bool PH, bool MULTI, bool VD, int ROWS, bool NT>
 __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g, const Phys &ph, PhysMem walls,
                                            const Scales &sc, const StateView &in, const StateView &out, int lz,
                                            int tiles_x, int tiles_y, unsigned long long step_next, int w) {
@@ -1148,8 +1155,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             if (zd >= z0 && zd < z1 && (g.per[2] || (zd > 0 && zd < g.nz - 1))) {
                 if (!(tile_walls || z_image)) {
                     if (own) {
-                        store_plane<ST>(out.mom, g.ld, plane * zd, off_dst, m, sc);
-                        if constexpr (PH) store_phi(out.phi, plane * zd, off_dst, phin);
+                        store_plane<ST, PH, NT>(out, g.ld, plane * zd, off_dst, m, phin, sc);
                     }
                 } else {
 #pragma unroll
@@ -1177,8 +1183,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                         else
                             apply_rule(rule, face >> 1, mb);
                         const uint32_t off = (uint32_t)gxs + (uint32_t)g.nx * (uint32_t)Y;
-                        store_plane<ST>(out.mom, g.ld, plane * Zp, off, mb, sc);
-                        if constexpr (PH) store_phi(out.phi, plane * Zp, off, pb);
+                        store_plane<ST, PH, NT>(out, g.ld, plane * Zp, off, mb, pb, sc);
                     }
                 }
             }
@@ -1189,7 +1194,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 
 
 static_assert(sizeof(Geo) % alignof(Phys) == 0 && alignof(Geo) == alignof(Phys), "ph follows g directly");
-template <int ST, bool PH, bool VD, int ROWS>
+template <int ST, bool PH, bool VD, int ROWS, bool NT>
 __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
                                                                int lz, int tiles_x, int tiles_y,
                                                                unsigned long long step_next) {
@@ -1197,13 +1202,13 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused(Geo g, P
     // ph sits behind g in the kernel's argument segment
     const PhysMem walls = (PhysMem)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
                                     sizeof(Geo));
-    step_fused<ST, PH, false, VD, ROWS>(sm, g, ph, walls, sc, in, out, lz, tiles_x, tiles_y, step_next,
+    step_fused<ST, PH, false, VD, ROWS, NT>(sm, g, ph, walls, sc, in, out, lz, tiles_x, tiles_y, step_next,
                                                xcd_work_item(blockIdx.x, gridDim.x));
 }
 
 // Several lattices in one launch: the work items of domain k are
 // [work_begin, work_begin + tiles * chunks); domains are sorted by work_begin.
-template <int ST, bool PH, bool VD, int ROWS>
+template <int ST, bool PH, bool VD, int ROWS, bool NT>
 __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(const FusedDomain *__restrict__ doms, int ndom) {
     __shared__ Smem<PH, VD, ROWS> sm;
     const int w = xcd_work_item(blockIdx.x, gridDim.x);
@@ -1240,7 +1245,7 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(co
     in.mom = d.in.mom; in.phi = d.in.phi; out.mom = d.out.mom; out.phi = d.out.phi;
     const int lz = d.lz, tx = d.tiles_x, ty = d.tiles_y, wb = d.work_begin;
     const unsigned long long sn = d.step_next;
-    step_fused<ST, PH, true, VD, ROWS>(sm, g, ph, (PhysMem)&d.ph, sc, in, out, lz, tx, ty, sn, w - wb);
+    step_fused<ST, PH, true, VD, ROWS, NT>(sm, g, ph, (PhysMem)&d.ph, sc, in, out, lz, tx, ty, sn, w - wb);
 }
 
 }  // namespace fused
@@ -1275,6 +1280,30 @@ constexpr double kWideCost = 1.22, kWideCostHalf = 1.35;
 
 // Planes a workgroup on a chunk of lz planes walks, doubled.
 int fused_walk2(const tslb_ctx *c, int lz) { return 2 * lz + (c->phase ? 13 : 9); }
+
+// Whether the step's stores carry the non-temporal hint, where a launch writes
+// launch_bytes in all (a launch over several lattices takes what most of its bytes
+// call for).  A line stored with it goes out at once; without it the line
+// stays in L2 until it is complete and then in the 256 MB cache behind.
+//  - A lattice up to kTinyState bytes: hint.  Its launch is a few planes long and
+//    would end with the lines still to be written back (61 x 45 x 83 box 18.6 us a step
+//    with, 19.5 without; 64^3 vortex 10.6, 11.0; 66^3 droplet, 12.7 MB, 22.6 both).
+//  - Rows that do not begin at 128-byte lines: none.  The two tiles that share a
+//    line write it at different times, and the halves go to memory as partial writes
+//    (250 x 256 x 400 jet: 26.4 M write requests against 18.0 M at 256 wide; 250 x 250 x
+//    400 jet 832 us with, 618 without; 300 x 300 x 600 jet 1919 and 1418; 200 x 200 x 400
+//    FP16Q 506 and 487; 16-bit rows of a tile are half a line).
+//  - Whole lines, state and new state within the cache: none, the next step reads from
+//    it (128^3 droplet 55.4 and 48.6, 128^3 vortex 42.1 and 34.4).
+//  - Whole lines, larger: hint, since lines written without it take L2 from the halo
+//    lines that neighbouring workgroups read again (512 x 512 x 2048 jet 12.3 ms and
+//    12.6, 256^3 vortex 262 us and 271, 160^3 droplet 101.5 and 102).
+constexpr size_t kTinyState = 13u << 20, kFarCache = 256u << 20;
+bool fused_stream_stores(const tslb_ctx *c, size_t launch_bytes) {
+    if (launch_bytes <= kTinyState) return true;
+    if (c->geo.nx * (c->storage == ST_FP32 ? 4 : 2) % 128) return false;
+    return 2 * launch_bytes > kFarCache;
+}
 
 bool fused_wide_allowed(const tslb_ctx *c) { return c->phase && !c->vd; }
 
@@ -1363,14 +1392,16 @@ template <int ST, bool PH, bool VD, int ROWS>
 void launch_one(unsigned blocks, hipStream_t s, const tslb_ctx *c, StateView in, StateView out, int lz, int tiles_x,
                 int tiles_y, unsigned long long sn) {
     using namespace fused;
-    hipLaunchKernelGGL((k_step_fused<ST, PH, VD, ROWS>), dim3(blocks), dim3(Tile<ROWS>::threads(PH)), 0, s, c->geo, c->phys,
-                       c->scales, in, out, lz, tiles_x, tiles_y, sn);
+    const bool nt = fused_stream_stores(c, c->buffer_bytes);
+    hipLaunchKernelGGL((nt ? k_step_fused<ST, PH, VD, ROWS, true> : k_step_fused<ST, PH, VD, ROWS, false>), dim3(blocks),
+                       dim3(Tile<ROWS>::threads(PH)), 0, s, c->geo, c->phys, c->scales, in, out, lz, tiles_x, tiles_y, sn);
 }
 
 template <int ST, bool PH, bool VD, int ROWS>
-void launch_multi(unsigned blocks, hipStream_t s, const FusedDomain *doms, int ndom) {
+void launch_multi(unsigned blocks, hipStream_t s, const FusedDomain *doms, int ndom, bool nt) {
     using namespace fused;
-    hipLaunchKernelGGL((k_step_fused_multi<ST, PH, VD, ROWS>), dim3(blocks), dim3(Tile<ROWS>::threads(PH)), 0, s, doms, ndom);
+    hipLaunchKernelGGL((nt ? k_step_fused_multi<ST, PH, VD, ROWS, true> : k_step_fused_multi<ST, PH, VD, ROWS, false>),
+                       dim3(blocks), dim3(Tile<ROWS>::threads(PH)), 0, s, doms, ndom);
 }
 
 }  // namespace
@@ -1410,23 +1441,23 @@ hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int
 }
 
 hipError_t launch_step_fused_multi(const FusedDomain *doms, int ndom, int total_work, int storage, bool phase,
-                                   bool vd, int rows, hipStream_t s) {
+                                   bool vd, int rows, bool nt, hipStream_t s) {
     if (ndom <= 0 || total_work <= 0) return hipSuccess;
     const unsigned blocks = (unsigned)total_work;
     if (vd) {
         if (!phase || rows != 16 || storage != ST_FP32) return hipErrorInvalidValue;
-        launch_multi<ST_FP32, true, true, 16>(blocks, s, doms, ndom);
+        launch_multi<ST_FP32, true, true, 16>(blocks, s, doms, ndom, nt);
         return hipGetLastError();
     }
     if (rows != 16 && (rows != 20 || !phase)) return hipErrorInvalidValue;
 #define TSLB_MULTI_CASE(ST)                                                                            \
     case ST:                                                                                           \
         if (!phase)                                                                                    \
-            launch_multi<ST, false, false, 16>(blocks, s, doms, ndom);                                 \
+            launch_multi<ST, false, false, 16>(blocks, s, doms, ndom, nt);                                 \
         else if (rows == 20)                                                                           \
-            launch_multi<ST, true, false, 20>(blocks, s, doms, ndom);                                  \
+            launch_multi<ST, true, false, 20>(blocks, s, doms, ndom, nt);                                  \
         else                                                                                           \
-            launch_multi<ST, true, false, 16>(blocks, s, doms, ndom);                                  \
+            launch_multi<ST, true, false, 16>(blocks, s, doms, ndom, nt);                                  \
         break;
     switch (storage) {
         TSLB_MULTI_CASE(ST_FP32)
