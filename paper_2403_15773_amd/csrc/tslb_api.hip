@@ -722,7 +722,23 @@ int tslb_stats_get(tslb_ctx *c, float *mean_phi, float *mean_u, float *rms_uz, i
     if (!mean_phi && !mean_u && !rms_uz) return TSLB_OK;
     if (!c->stats.sum || c->stats.samples == 0) return fail(c, TSLB_E_STATE, "no samples: call tslb_stats_start and step");
     const size_t N = (size_t)c->geo.N, ld = (size_t)c->geo.ld;
-    // the five sum planes come over in blocks of nodes through a bounded host buffer
+    const double inv = 1.0 / (double)c->stats.samples;
+    if (c->scratch.geo) {
+        // while sampling goes on the geometry planes are there, and every sample writes
+        // them anew: the means are formed in them and copied out
+        float *out = c->scratch.geo;
+        hipError_t e = launch_stats_means(c, inv, c->stats.sum, out, c->stream);
+        if (e == hipSuccess && mean_phi) e = hipMemcpyAsync(mean_phi, out, N * 4, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess && mean_u)
+            e = hipMemcpy2DAsync(mean_u, N * 4, out + ld, ld * 4, N * 4, 3, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess && rms_uz)
+            e = hipMemcpyAsync(rms_uz, out + 4 * ld, N * 4, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return fail(c, TSLB_E_DEVICE, std::string("statistics: ") + hipGetErrorString(e));
+        return TSLB_OK;
+    }
+    // After tslb_stats_stop they are gone, and nothing is allocated here: the five sum
+    // planes come over in blocks of nodes through a bounded host buffer.
     const size_t blk = std::min(N, (size_t)1 << 22);
     std::vector<double> h;
     try {
@@ -730,7 +746,6 @@ int tslb_stats_get(tslb_ctx *c, float *mean_phi, float *mean_u, float *rms_uz, i
     } catch (const std::bad_alloc &) {
         return fail(c, TSLB_E_NOMEM, "host allocation failed (statistics block)");
     }
-    const double inv = 1.0 / (double)c->stats.samples;
     for (size_t b0 = 0; b0 < N; b0 += blk) {
         const size_t nb = std::min(blk, N - b0);
         HIP_TRY(c, hipMemcpy2DAsync(h.data(), blk * sizeof(double), c->stats.sum + b0, ld * sizeof(double),

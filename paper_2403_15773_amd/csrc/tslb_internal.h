@@ -154,5 +154,7 @@ hipError_t launch_diagnostics_raw(const Geo &g, const Scales &sc, int storage, S
 int diagnostics_blocks_for(long long N);
 // Add phi, u (= ubar + F/(2 rho), F from geo) and u_z^2 of every node of st to the sums.
 hipError_t launch_stats_accum(const tslb_ctx *c, StateView st, const float *geo, double *sum, hipStream_t s);
+// mean phi, mean u and rms u_z of `sum` into five planes at out (inv = 1 / samples).
+hipError_t launch_stats_means(const tslb_ctx *c, double inv, const double *sum, float *out, hipStream_t s);
 
 }  // namespace tslb

@@ -369,6 +369,23 @@ __global__ __launch_bounds__(kBlock) void k_stats_accum(Geo g, Scales sc, StateV
     sum[4 * ld + id] += u2 * u2;
 }
 
+// The means of those sums in binary32: out = mean phi, mean u (3), rms of u_z - its
+// mean, planes of ld words.  Here rather than on the host, half the bytes cross to it
+// and none is touched there (100 x 100 x 200: 2.2 ms a call, most of it the copy;
+// 22.8 ms on the host, most of it the loop over the nodes and first touches of the
+// block buffer).  The same binary64
+// operations in the same order, so the same bits.
+__global__ __launch_bounds__(kBlock) void k_stats_means(long long N, long long ld, double inv, const double *__restrict__ sum,
+                                                        float *__restrict__ out) {
+#pragma clang fp contract(off)
+    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= N) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[k * ld + id] = (float)(sum[k * ld + id] * inv);
+    const double m = sum[3 * ld + id] * inv, var = sum[4 * ld + id] * inv - m * m;
+    out[4 * ld + id] = (float)sqrt(var > 0.0 ? var : 0.0);
+}
+
 // ---- the gather step (simple reference kernel) ----
 
 // One thread per interior destination x: for each velocity c_i, read the raw
@@ -546,6 +563,11 @@ size_t diagnostics_blocks(const tslb_ctx *c) { return (size_t)diagnostics_blocks
 hipError_t launch_stats_accum(const tslb_ctx *c, StateView st, const float *geo, double *sum, hipStream_t s) {
     TSLB_DISPATCH(c->storage, k_stats_accum, dim3(grid_for(c->geo.N)), dim3(kBlock), 0, s, c->geo, c->scales, st, geo,
                   sum);
+    return hipGetLastError();
+}
+
+hipError_t launch_stats_means(const tslb_ctx *c, double inv, const double *sum, float *out, hipStream_t s) {
+    hipLaunchKernelGGL(k_stats_means, dim3(grid_for(c->geo.N)), dim3(kBlock), 0, s, c->geo.N, c->geo.ld, inv, sum, out);
     return hipGetLastError();
 }
 
