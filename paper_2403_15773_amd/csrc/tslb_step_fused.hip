@@ -39,6 +39,8 @@
 //        of an item share their 12 values of phi (instead of 9 each) and their sums of
 //        n.  256^3 vortex (one component, only the first moment load moved) 266 as before,
 //        variable density 237 -> 201, 512 x 512 x 2048 jet 14.1 -> 12.8 ms.
+//   182  wall lanes served by register moves (at `edge` below), and the moments no longer
+//        one register tuple (at `each`); 512 x 512 x 2048 jet 12.3 -> 11.5 ms
 //
 // Arithmetic (Eqs. 5-8, 15-19 with Guo forcing; Eqs. 20-24):
 //   source:  u = ubar + F/(2 rho), P = Q + F F/(4 rho), J = rho u + F/2,
@@ -73,6 +75,7 @@
 // the magnitude of rho' except in z and in the final density itself.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "tslb_internal.h"
 
@@ -118,6 +121,20 @@ template <bool VD, int ROWS> struct alignas(16) Smem<false, VD, ROWS> {
 };
 static_assert(sizeof(Smem<true, false, 20>) <= 160 * 1024 && sizeof(Smem<true, true, 16>) <= 160 * 1024,
               "LDS of one workgroup");
+
+// f(0), ..., f(N - 1) with compile-time indices.  An unrolled loop over an array that
+// lives across branches or iterations is too late: the compiler has made the array one
+// wide register tuple by then, which it copies as a whole (ten moves a plane for the
+// moments, and a tuple carried through the loop).
+template <class F, int... I> __device__ __forceinline__ void each_of(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void each(F &&f) { each_of(f, std::make_integer_sequence<int, N>{}); }
+
+// Values formed here, in program order with the other pins (an empty asm statement).
+__device__ __forceinline__ void keep_here(float &a) { __asm__ volatile("" : "+v"(a)); }
+__device__ __forceinline__ void keep_here(float &a, float &b) { __asm__ volatile("" : "+v"(a), "+v"(b)); }
+__device__ __forceinline__ void keep_here(float &a, float &b, float &c) { __asm__ volatile("" : "+v"(a), "+v"(b), "+v"(c)); }
 
 // 1-D three-point transform of (a_-, a_0, a_+) with weights (1/6, 2/3, 1/6):
 // m0 = sum w a, 6 m1 = 6 sum w c a, 9 m2 = 9 sum w (c^2 - 1/3) a, written relative to
@@ -258,8 +275,8 @@ template <int ST>
 __device__ __forceinline__ void load_plane(const void *mom, long long ld, long long zoff, uint32_t off, uint32_t m[10]) {
     global_t<char> *q = (global_t<char> *)mom + moment_size<ST>(0) * zoff;
     uint32_t o = lane_offset(off * moment_size<ST>(0));
-#pragma unroll
-    for (int p = 0; p < 10; ++p) {
+    each<10>([&](auto i_) {
+        constexpr int p = i_;
         const int sz = moment_size<ST>(p);
         q = uniform(q);
         if (sz == 4)
@@ -271,7 +288,7 @@ __device__ __forceinline__ void load_plane(const void *mom, long long ld, long l
             q -= (sz - moment_size<ST>(p + 1)) * zoff;
             o = lane_offset(off * moment_size<ST>(p + 1));
         }
-    }
+    });
 }
 
 // One word of a new state: with the non-temporal hint or without (fused_stream_stores;
@@ -288,8 +305,8 @@ __device__ __forceinline__ void store_plane(const StateView &out, long long ld, 
                                                const float m[10], int32_t phi, const Scales &sc) {
     global_t<char> *q = (global_t<char> *)out.mom + moment_size<ST>(0) * zoff;
     uint32_t o = lane_offset(off * moment_size<ST>(0));
-#pragma unroll
-    for (int p = 0; p < 10; ++p) {
+    each<10>([&](auto i_) {
+        constexpr int p = i_;
         const int sz = moment_size<ST>(p);
         q = uniform(q);
         if (sz == 4)
@@ -301,12 +318,32 @@ __device__ __forceinline__ void store_plane(const StateView &out, long long ld, 
             q -= (sz - moment_size<ST>(p + 1)) * zoff;
             o = lane_offset(off * moment_size<ST>(p + 1));
         }
-    }
+    });
     if constexpr (PH) {
         q = uniform((global_t<char> *)out.phi + 4 * zoff);
         store_word<NT>(q + lane_offset(off * 4u), phi);
     }
 }
+// The moments and phase of each wall lane from the lane of its nearest interior node:
+// edge & 1, 2: columns 0 and 31 of each half-wave from columns 1 and 30; edge & 4, 8:
+// the lower from the upper half-wave or the reverse; edge & 16: from lane lane_f.
+__device__ __forceinline__ void take_over(int edge, int lane_f, float m[10], int32_t &phi) {
+    auto move = [&](auto f) {
+        each<10>([&](auto i_) {
+            constexpr int k = i_;
+            m[k] = __uint_as_float(f(__float_as_uint(m[k])));
+        });
+        phi = (int32_t)f((uint32_t)phi);
+    };
+    // quads 1, 1, 2, 3 in the first quad of rows (16 lanes) 0 and 2; 0, 1, 2, 2 in the last of 1 and 3
+    if (edge & 1) move([](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xE5, 0x5, 0x1, false); });
+    if (edge & 2) move([](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xA4, 0xA, 0x8, false); });
+    // swap of one operand's upper half with the other's lower half: both halves lower, both upper
+    if (edge & 4) move([](uint32_t v) { return (uint32_t)__builtin_amdgcn_permlane32_swap(v, v, false, false)[1]; });
+    if (edge & 8) move([](uint32_t v) { return (uint32_t)__builtin_amdgcn_permlane32_swap(v, v, false, false)[0]; });
+    if (edge & 16) move([=](uint32_t v) { return (uint32_t)__shfl((int)v, lane_f); });
+}
+
 // The lattice's parameters in memory: what only the inlet rule needs is read where
 // an inlet node is written (loaded at kernel entry it would sit in scalar registers
 // through the whole loop).
@@ -383,10 +420,26 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     const bool y_image = !g.per[1] && g.ny < TY && (g.ny & 1);
     const bool own = owned && !(y_image && gys == g.ny - 1);
     const int lane_f = (t & 63) + dxf + TX * (y_image && dyf < 0 ? 0 : dyf);  // lane of x_F
-    const bool tile_walls = (!g.per[0] && (x0 == 0 || x0 + TX >= g.nx)) || (!g.per[1] && (y0 == 0 || y0 + TY >= g.ny));
     uint32_t rules = 0;  // four bits per face
 #pragma unroll
     for (int f = 0; f < 6; ++f) rules |= (uint32_t)ph.bc[f] << (4 * f);
+    // `edge` says which walls this wave's columns meet: x walls are columns 0 and 31 of
+    // its half-waves (in a lattice at least a tile wide), y walls its lower (y = 0) or
+    // upper half-wave.  `keep`: the moments that the column's x or y rule leaves (bit k;
+    // the inlet is a z face).  Moved within quads and between half-waves in place of
+    // 11 LDS permutes in each wave of a tile with walls, a 128 x 128 x 512 jet takes
+    // 182 us a step instead of 190 (periodic: 176).
+    const int edge = __builtin_amdgcn_readfirstlane(!g.per[0] && g.nx < TX ? 16 :
+        (!g.per[0] && x0 == 0 ? 1 : 0) | (!g.per[0] && x0 + TX >= g.nx ? 2 : 0) |
+        (!g.per[1] && y0 + 2 * wave == 0 ? 4 : 0) | (!g.per[1] && y0 + 2 * wave + 1 == g.ny - 1 ? 8 : 0));
+    uint32_t keep = ~0u;
+    if (edge) {
+        const int face = boundary_face(g, gxs, gys, 1);
+        const uint32_t rule = face < 0 ? 0u : (rules >> (4 * face)) & 15u;
+        if (rule == 1u) keep = face < 2 ? ~(1u << 1 | 1u << 7 | 1u << 8) : ~(1u << 2 | 1u << 7 | 1u << 9);
+        if (rule == 4u) keep = ~(7u << 1);
+        if (rule == 3u) keep = ~1u;
+    }
     const uint32_t off_dst = (uint32_t)gxs + (uint32_t)g.nx * (uint32_t)gys;  // used where owned
 
     constexpr bool H = ST != ST_FP32;  // the arithmetic of 16-bit stored moments
@@ -395,13 +448,19 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 
     // carried destination state (see S6)
     float ZA[3], ZD[3], ZQ[3], ZP[6], ZR = 0.f;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) ZA[k] = ZD[k] = ZQ[k] = 0.f;
-#pragma unroll
-    for (int k = 0; k < 6; ++k) ZP[k] = 0.f;
+    each<3>([&](auto i_) {
+        constexpr int k = i_;
+        ZA[k] = ZD[k] = ZQ[k] = 0.f;
+    });
+    each<6>([&](auto i_) {
+        constexpr int k = i_;
+        ZP[k] = 0.f;
+    });
     float XA[6], XB[6], XC[6];  // with 16-bit moments: X(+1) and X(0) of plane r - 1, X(+1) of plane r
-#pragma unroll
-    for (int k = 0; k < 6; ++k) XA[k] = XB[k] = XC[k] = 0.f;
+    each<6>([&](auto i_) {
+        constexpr int k = i_;
+        XA[k] = XB[k] = XC[k] = 0.f;
+    });
     int32_t PA = 0, PC = 0;    // phase partial sums of planes r - 1 and r
     float own_n[3] = {0.f, 0.f, 0.f}, own_G[3] = {0.f, 0.f, 0.f};  // n, |G| + eps (or G) and phi of the
     int32_t own_phi = 0;                                           // next source plane (own column)
@@ -689,13 +748,13 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             rho_cur = fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)mom[0]), sc.s2, 1.0f);
             __asm__ volatile("" : "+v"(rho_cur));
         }
-#pragma unroll
-        for (int k = 0; k < 10; ++k) {
+        each<10>([&](auto i_) {
+            constexpr int k = i_;
             mom_cur[k] = decode_moment<ST>(mom[k], k, sc);
             if (!VD && !H && k >= 4) mom_cur[k] *= omega1;  // (1 - omega) Q
             // formed before the loads below, which then reuse the words' registers
-            __asm__ volatile("" : "+v"(mom_cur[k]));
-        }
+            keep_here(mom_cur[k]);
+        });
         // (the first source plane is z0 - 1, loaded at the first iteration; lanes without
         // a source load a column of the lattice and drop it)
         if (it == IT0 || it >= 4) {
@@ -991,8 +1050,10 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         if constexpr (PH) {
             const float *nq = &sm.n[(it + 1) & 1][0][0] + (sy + 1) * GX + (sx + 1);
             const float *Gq = &sm.G[(it + 1) & 1][0][0] + sidx;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) own_n[k] = nq[k * NGEO];
+            each<3>([&](auto i_) {
+                constexpr int k = i_;
+                own_n[k] = nq[k * NGEO];
+            });
 #pragma unroll
             for (int k = 0; k < (VD ? 3 : 1); ++k) own_G[k] = Gq[k * NSRC];
             own_phi = sm.phi[(it - 1) & 3][(sy + 2) * PX + (sx + 2)];
@@ -1059,12 +1120,12 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 m[7] = fmaf(-m[1], jy, Hxy);
                 m[8] = fmaf(-m[1], jz, m10.m1);
                 m[9] = fmaf(-m[2], jz, m01.m1);
-#pragma unroll
-                for (int k = 0; k < 6; ++k) {
+                each<6>([&](auto i_) {
+                    constexpr int k = i_;
                     XA[k] = XC[k];
                     XB[k] = X1[k];
                     XC[k] = X2[k];
-                }
+                });
             } else {
             // The populations of c_z = -1, 0, +1 sum to M, Z, P (X = X0 + c_z X1 +
             // (c_z^2 - 1/3) X2) and belong to planes r - 1, r, r + 1.  Kept for the
@@ -1081,8 +1142,10 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             // In this order (held by the empty asm statements) each carried value is
             // formed in the register of the one it replaces.
             float M[6];
-#pragma unroll
-            for (int k = 0; k < 6; ++k) M[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) - X1[k];
+            each<6>([&](auto i_) {
+                constexpr int k = i_;
+                M[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) - X1[k];
+            });
             if constexpr (VD)
                 dr = rpc - ZR;
             else
@@ -1111,30 +1174,34 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             }
             // streamed phase, held to the clamp range (a stable run never reaches it)
             phin = PH ? phi_clamp(PA + pdown) : 0;
-#pragma unroll
-            for (int k = 0; k < 10; ++k) __asm__ volatile("" : "+v"(m[k]));
+            each<10>([&](auto i_) {
+                constexpr int k = i_;
+                keep_here(m[k]);
+            });
             __asm__ volatile("" : "+v"(phin));
             if constexpr (PH) {
                 PA = PC + prest + pin;
                 PC = pup;
             }
             if constexpr (!H) {
-#pragma unroll
-            for (int k = 0; k < 6; ++k) __asm__ volatile("" : "+v"(X0[k]), "+v"(X2[k]));
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
+            each<6>([&](auto i_) {
+                constexpr int k = i_;
+                keep_here(X0[k], X2[k]);
+            });
+            each<3>([&](auto i_) {
+                constexpr int k = i_;
                 ZA[k] = fmaf(X2[k], -1.0f / 3.0f, X0[k]);
                 if (!VD && k == 0) ZA[0] += rpc;
                 ZD[k] = VD && k == 0 ? (ZP[k] - ZA[k]) - dr : ZP[k] - ZA[k];
                 const float c = k == 2 ? 1.0f / 216.0f : 1.0f / 54.0f;
                 ZQ[k] = fmaf(fmaf(X2[3 + k], -1.0f / 3.0f, X0[3 + k]), 4.0f * c, ZP[3 + k] * c);
-                __asm__ volatile("" : "+v"(ZA[k]), "+v"(ZD[k]), "+v"(ZQ[k]));
-            }
-#pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                __asm__ volatile("" : "+v"(X2[k]));
+                keep_here(ZA[k], ZD[k], ZQ[k]);
+            });
+            each<6>([&](auto i_) {
+                constexpr int k = i_;
+                keep_here(X2[k]);
                 ZP[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) + X1[k];
-            }
+            });
             if constexpr (VD)
                 ZR = rpc;
             else
@@ -1149,18 +1216,32 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         // every store of the iteration has been acknowledged.  Here the loads have had
         // nearly the whole iteration to arrive, and the stores drain during the next one.
         __builtin_amdgcn_s_waitcnt(0x0F70);
-        if (finish) {
+        // (an opaque copy: with the same condition the two blocks are joined into one, the
+        // wait is doubled, and a path without it is left on paper, for which the compiler
+        // then waits at the top of the loop, stores included)
+        int storing = __builtin_amdgcn_readfirstlane((int)finish);
+        __asm__ volatile("" : "+s"(storing));
+        if (storing) {
             const int zd = r - 1;
             const bool z_image = !g.per[2] && (zd == 1 || zd == g.nz - 2);
             if (zd >= z0 && zd < z1 && (g.per[2] || (zd > 0 && zd < g.nz - 1))) {
-                if (!(tile_walls || z_image)) {
+                int e = __builtin_amdgcn_readfirstlane(edge);
+                __asm__ volatile("" : "+s"(e));  // tested here, not kept as four masks
+                const bool images = z_image || y_image;
+                if (e) {
+                    take_over(e, lane_f, m, phin);
+                    if (!images)
+                        each<10>([&](auto i_) {
+                            constexpr int k = i_;
+                            if (k < 4 || k > 6)
+                                m[k] = __uint_as_float(__float_as_uint(m[k]) & (uint32_t)((int32_t)(keep << (31 - k)) >> 31));
+                        });
+                }
+                if (!images) {
                     if (own) {
                         store_plane<ST, PH, NT>(out, g.ld, plane * zd, off_dst, m, phin, sc);
                     }
                 } else {
-#pragma unroll
-                    for (int k = 0; k < 10; ++k) m[k] = __shfl(m[k], lane_f);
-                    if constexpr (PH) phin = __shfl(phin, lane_f);
                     // the node itself (v = 0) and its images: on the z wall next to plane
                     // zd (v & 1) and in the last row of an odd low lattice (v & 2).  x_F of
                     // an edge node is interior in every coordinate, so each is made from
@@ -1173,8 +1254,10 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                         const int Y = (v & 2) ? g.ny - 1 : gys;
                         const int Zp = !(v & 1) ? zd : (zd == 1 ? 0 : g.nz - 1);
                         float mb[10];
-#pragma unroll
-                        for (int k = 0; k < 10; ++k) mb[k] = m[k];
+                        each<10>([&](auto i_) {
+                            constexpr int k = i_;
+                            mb[k] = m[k];
+                        });
                         int32_t pb = phin;
                         const int face = boundary_face(g, gxs, Y, Zp);
                         const uint32_t rule = face < 0 ? 0u : (rules >> (4 * face)) & 15u;
