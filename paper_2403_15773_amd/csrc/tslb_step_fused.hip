@@ -41,6 +41,10 @@
 //        variable density 237 -> 201, 512 x 512 x 2048 jet 14.1 -> 12.8 ms.
 //   182  wall lanes served by register moves (at `edge` below), and the moments no longer
 //        one register tuple (at `each`); 512 x 512 x 2048 jet 12.3 -> 11.5 ms
+// and the same here, but 32^3 droplet 15.4 -> 14.6, 96^3 29.6 -> 28.5, 128^3 48.7 -> 47.1,
+// 200 x 200 x 400 FP16Q jet 449 -> 433: the first geometry planes in a prologue of three
+// barriers instead of three iterations, and LDS reads around one address (at lds_base; a
+// geometry wave's vector instructions a plane 162 -> 153, 233 -> 207 with 16-bit moments).
 //
 // Arithmetic (Eqs. 5-8, 15-19 with Guo forcing; Eqs. 20-24):
 //   source:  u = ubar + F/(2 rho), P = Q + F F/(4 rho), J = rho u + F/2,
@@ -262,6 +266,16 @@ __device__ __forceinline__ global_t<char> *uniform(global_t<char> *p) {
 __device__ __forceinline__ uint32_t lane_offset(uint32_t off) {
     __asm__ volatile("" : "+v"(off));
     return off;
+}
+
+// An LDS address kept in one register: reads around it then take their offsets in the
+// instruction.  Else every pair of words (ds_read2, whose offsets span 1 KB) gets an
+// address of its own, the position in LDS folded into each.
+template <class T> using lds_t = __attribute__((address_space(3))) T;
+template <class T> __device__ __forceinline__ const lds_t<T> *lds_base(const T *p) {
+    const lds_t<T> *q = (const lds_t<T> *)p;
+    __asm__ volatile("" : "+v"(q));
+    return q;
 }
 
 // Bytes of a word of moment plane p.
@@ -576,9 +590,9 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 gc1[k] = c;
             };
             auto read_phi = [&](int k, int slot, int32_t q[12]) {  // rows y - 1 .. y + 2, columns x - 1 .. x + 1
-                const int32_t *b = sm.phi[slot & 3] + gc[k];
+                const lds_t<int32_t> *b = lds_base(sm.phi[slot & 3] + gc[k] - PX - 1);
 #pragma unroll
-                for (int j = 0; j < 12; ++j) q[j] = b[(j / 3 - 1) * PX + j % 3 - 1];
+                for (int j = 0; j < 12; ++j) q[j] = b[(j / 3) * PX + j % 3];
             };
             // G of the middle column of q0 from 13 pairs of opposite neighbours (16-bit
             // moments), planes p - 1, p and p + 1 in qm, q0 and qp
@@ -600,33 +614,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                             if (cz) Gz = fmaf(w * cz, d, Gz);
                         }
             };
-            // prologue: phase planes z0 - 3 .. z0 staged (slots 0 - 3) and the first taken in,
-            // so that the first two iterations wait for no load
-            int32_t v[NP];
-            {
-                int32_t first[4][NP];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) load_phi(plane_of(z0 - 3 + j), first[j]);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) stage_phi(j, first[j]);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int k = 0; k < NG; ++k) {
-                float gx, gy, gz;
-                int32_t q[12];
-                read_phi(k, 0, q);
-                absorb_plane(2 * k, q, gx, gy, gz);
-                absorb_plane(2 * k + 1, q + 3, gx, gy, gz);
-            }
-            int kphi = plane_of(z0);
-            for (int it = 0; it < nit; ++it) {
-                const int p = z0 - 3 + it;
-                if (it >= 2) {
-                    kphi = plane_after(p + 2, kphi);
-                    load_phi(kphi, v);
-                }
-                // ================= phase A =================
+            // G and n of the plane of iteration it (see below), from the phase planes around it
+            auto geometry = [&](int it) {
                 constexpr float kS = kPhiUlp / 72.0f;
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
@@ -667,8 +656,9 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                         }
                     }
                 }
-                __syncthreads();
-                // ================= phase B =================
+            };
+            // and its share of the curvature sums
+            auto curvature = [&](int it) {
                 // ---- S3a: per-column partial sums of the curvature stencil (plane p) ----
                 // With w_i = w1(c_x) w1(c_y) w1(c_z), w1 = (1, 4, 1)/6, the stencil
                 // kappa = 3 sum_i w_i c_i . n(x + c_i) factorises into sums over one plane:
@@ -682,7 +672,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 #pragma unroll
                 for (int k = 0; k < NC; ++k) {
                     if (k && l + k * NGT >= NCP) break;
-                    const float *bx = sm.n[it & 1][0] + cg[k], *by = bx + NGEO, *bz = by + NGEO;
+                    const lds_t<float> *bx = lds_base(sm.n[it & 1][0] + cg[k]), *by = lds_base(sm.n[it & 1][1] + cg[k]),
+                                       *bz = lds_base(sm.n[it & 1][2] + cg[k]);
                     float ny[4][3], nz[4][3], D[4], e[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
@@ -720,14 +711,58 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                         if (l + k * NGT < NCP) sm.kap[si] = kap;
                     }
                 }
+            };
+            // Prologue: what iterations 1 and 2 would do, whose planes have no source yet,
+            // between two barriers instead of four (iteration 0 has nothing that is used).
+            // Phase planes z0 - 3 .. z0 are staged at once (slots 0 - 3), z0 + 1 after them.
+            {
+                int32_t first[5][NP];
+#pragma unroll
+                for (int j = 0; j < 5; ++j) load_phi(plane_of(z0 - 3 + j), first[j]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) stage_phi(j, first[j]);
+                __syncthreads();
+#pragma unroll
+                for (int k = 0; k < NG; ++k) {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        float gx, gy, gz;
+                        int32_t q[12];
+                        read_phi(k, j, q);
+                        absorb_plane(2 * k, q, gx, gy, gz);
+                        absorb_plane(2 * k + 1, q + 3, gx, gy, gz);
+                    }
+                }
+#pragma unroll 1
+                for (int it = 1; it < 3; ++it) geometry(it);
+                __syncthreads();
+#pragma unroll 1
+                for (int it = 1; it < 3; ++it) curvature(it);
+                stage_phi(4, first[4]);
+                __syncthreads();
+            }
+            int32_t v[NP];
+            int kphi = plane_of(z0 + 1);
+            for (int it = 3; it < nit; ++it) {
+                kphi = plane_after(z0 - 1 + it, kphi);
+                load_phi(kphi, v);
+                // ================= phase A =================
+                geometry(it);
+                __syncthreads();
+                // ================= phase B =================
+                curvature(it);
                 // slot of plane p - 2, whose last readers (own_phi, phase B of it - 1) are done
-                if (it >= 2) stage_phi(it + 2, v);
+                stage_phi(it + 2, v);
                 __syncthreads();
             }
             return;
         }
     }
-    if constexpr (PH) __syncthreads();  // the geometry waves' prologue
+    if constexpr (PH) {  // the geometry waves' prologue
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+    }
 
     int kmom = plane_of(z0 - 1);  // z plane of the last load
     // Iteration it works on three planes: p = z0 - 3 + it (geometry), q = p - 1
@@ -735,7 +770,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     // destination plane r - 1.  Rings: phi plane p at slot it mod 4, n and G of
     // plane p at slot it mod 2.  Phase A (sources; G and n) and phase B
     // (destinations; kappa and the staging of phi) are separated by barriers.
-    constexpr int IT0 = PH ? 0 : 3;  // one component has no geometry to wait for
+    constexpr int IT0 = 3;  // the first source plane is loaded; it is expanded at 4
     for (int it = IT0; it < nit; ++it) {
         const int p = z0 - 3 + it;
         const int r = p - 2;
@@ -1338,11 +1373,11 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(co
 // give each CU ceil(W / CUs) of them, so the cost of a plan is
 // ceil(W / CUs) (lz + fill) c, with c the time of one pipeline plane of a
 // workgroup: 1 for 16 rows and kWideCost for 20 rows.
-// fill: one round of workgroups takes 1.99 (lz + 6.6) us with two components and
+// fill: one round of workgroups takes 1.97 (lz + 6.4) us with two components and
 // 1.55 (lz + 4.5) with one (32^3 to 64^3 lattices, lz 1 to 8, launch included), of
-// which 6 and 3 are planes of the loop.  So the shortest chunks pay as long as
-// they fill idle CUs: 32^3 droplet 21.2 us a step at 4 planes, 15.3 at 1; 61 x 45 x
-// 83 box 23.2 at 4, 18.6 at 2; 40^3 vortex 13.2 at 4, 8.6 at 1.
+// which 3 are planes of the loop and, with two, the geometry's prologue.  So the
+// shortest chunks pay as long as they fill idle CUs: 32^3 droplet 20.4 us a step at 4
+// planes, 14.6 at 1; 48^3 21.2 at 4, 17.0 at 2; 40^3 vortex 13.2 at 4, 8.6 at 1.
 // kWideCost: 400 x 400 x 800 jet 2.83 us a plane on 16 rows, 3.47 on 20 (1.22);
 // 512 x 512 x 2048 jet 2.87 and 3.59 (1.25); 100 x 100 x 200 1.24.
 // Long chunks recompute less halo, short ones keep every unit busy; ties go to the
