@@ -1419,7 +1419,7 @@ int fused_walk2(const tslb_ctx *c, int lz) { return 2 * lz + (c->phase ? 13 : 9)
 constexpr size_t kTinyState = 13u << 20, kFarCache = 256u << 20;
 bool fused_stream_stores(const tslb_ctx *c, size_t launch_bytes) {
     if (launch_bytes <= kTinyState) return true;
-    if (c->geo.nx * (c->storage == ST_FP32 ? 4 : 2) % 128) return false;
+    if (c->geo.nx % (c->storage == ST_FP32 ? 32 : 64)) return false;  // words of a 128-byte line
     return 2 * launch_bytes > kFarCache;
 }
 
