@@ -217,6 +217,26 @@ __device__ __forceinline__ void xy_moments(const float t[9], float X[6]) {
     X[4] = tr3_m0(y0.m2, y1.m2, y2.m2);  // 02
 }
 
+// The same of t + (w - w[4]), the brackets t without their density and the densities w.
+// Differences of t and of w are taken before the two are added, so that the sums of
+// three columns are not rounded at the magnitude of a population (the velocity's) for
+// the sake of a difference of densities.
+__device__ __forceinline__ void xy_moments(const float t[9], const float w[9], float X[6]) {
+    const float m0 = (t[0] - t[3]) + (w[0] - w[3]), p0 = (t[6] - t[3]) + (w[6] - w[3]);
+    const float m1 = t[1] - (t[4] - (w[1] - w[4])), p1 = t[7] - (t[4] - (w[7] - w[4]));
+    const float m2 = (t[2] - t[5]) + (w[2] - w[5]), p2 = (t[8] - t[5]) + (w[8] - w[5]);
+    const float s0 = m0 + p0, s1 = m1 + p1, s2 = m2 + p2;
+    const float a0 = fmaf(s0, 1.0f / 6.0f, t[3]), a1 = fmaf(s1, 1.0f / 6.0f, t[4]), a2 = fmaf(s2, 1.0f / 6.0f, t[5]);
+    const float dm = a0 - (a1 - (w[3] - w[4])), dp = a2 - (a1 - (w[5] - w[4]));
+    X[3] = dm + dp;
+    X[0] = fmaf(X[3], 1.0f / 6.0f, a1);
+    X[1] = dp - dm;
+    const Tr3 b = tr3(p0 - m0, p1 - m1, p2 - m2);
+    X[2] = b.m0;
+    X[5] = b.m1;
+    X[4] = tr3_m0(s0, s1, s2);
+}
+
 // The forms of the arithmetic that 16-bit stored moments keep (see the header): the
 // transforms with their factors multiplied out, and the weighted three-point sum
 // (1/6) m + (2/3) z + (1/6) p.
@@ -461,14 +481,12 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
     const float sigma72 = ph.sigma * (1.0f / 72.0f), gamma = ph.gamma;
 
     // carried destination state (see S6)
-    float ZA[3], ZD[3], ZQ[3], ZP[6], ZR = 0.f;
-    each<3>([&](auto i_) {
-        constexpr int k = i_;
-        ZA[k] = ZD[k] = ZQ[k] = 0.f;
-    });
+    float ZA = 0.f, ZD = 0.f, ZR = 0.f, ZS[5], ZO[2], ZP[6];
     each<6>([&](auto i_) {
         constexpr int k = i_;
         ZP[k] = 0.f;
+        if (k < 5) ZS[k] = 0.f;
+        if (k < 2) ZO[k] = 0.f;
     });
     float XA[6], XB[6], XC[6];  // with 16-bit moments: X(+1) and X(0) of plane r - 1, X(+1) of plane r
     each<6>([&](auto i_) {
@@ -949,7 +967,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 for (int k = 0; k < 9; ++k)
                     if (k != 4) rec[xy_slot(k % 3 - 1, k / 3 - 1)] = vec4{tm[k], t0[k], tp[k], rp};
             } else {
-            // m = (1 - omega) P and a2 of the header, with g = F/rho, v = ubar + g, J = rho v:
+            // m = (1 - omega) P and a2 of the header, with g = F/rho, v = ubar + g, J = rho v
+            // (formed from ubar and F: one rounding):
             //   a2_ab = J_a v_b + (1 - omega) Q_ab - (omega/4) F_a g_b
             float mxx = mom_cur[4], myy = mom_cur[5], mzz = mom_cur[6], mxy = mom_cur[7], mxz = mom_cur[8],
                   myz = mom_cur[9];
@@ -958,12 +977,12 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 const float inv = VD ? 1.0f : recip(rho);
                 const float g0 = F0 * inv, g1 = F1 * inv, g2 = F2 * inv;
                 const float v0 = u0 + g0, v1 = u1 + g1, v2 = u2 + g2;
+                Jx = fmaf(rho, u0, F0);
+                Jy = fmaf(rho, u1, F1);
+                Jz = fmaf(rho, u2, F2);
                 u0 = fmaf(0.5f, g0, u0);
                 u1 = fmaf(0.5f, g1, u1);
                 u2 = fmaf(0.5f, g2, u2);
-                Jx = rho * v0;
-                Jy = rho * v1;
-                Jz = rho * v2;
                 const float hs = 0.25f * (om1 - 1.0f), ks = 0.25f * om1;
                 const float h0 = hs * F0, h1 = hs * F1, h2 = hs * F2;
                 const float q0 = ks * F0, q1 = ks * F1, q2 = ks * F2;
@@ -1098,7 +1117,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         int32_t phin;
         if (finish) {
             // ---- S5b/S6: gather at the destination and finish plane r - 1 ----
-            float t0[9], t1[9], t2[9];
+            float t0[9], t1[9], t2[9], w[9];
+            w[4] = rpc;
             t0[4] = T0c;
             t1[4] = T1c;
             t2[4] = T2c;
@@ -1110,10 +1130,17 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                     if (!cx && !cy) continue;
                     const int k = (cx + 1) + 3 * (cy + 1);
                     const vec4 v = ((const vec4 *)&xc[(1 - cy) * SX + (1 - cx)][0])[xy_slot(cx, cy)];
-                    const float drp = v.w - rpc;
-                    t0[k] = v.x + drp;
-                    t1[k] = H ? v.y + drp : v.y;
-                    t2[k] = H ? v.z + drp : v.z;
+                    if constexpr (H) {
+                        const float drp = v.w - rpc;
+                        t0[k] = v.x + drp;
+                        t1[k] = v.y + drp;
+                        t2[k] = v.z + drp;
+                    } else {
+                        t0[k] = v.x;
+                        t1[k] = v.y;
+                        t2[k] = v.z;
+                        w[k] = v.w;
+                    }
                 }
             float X0[6], X1[6], X2[6];
             if constexpr (H) {
@@ -1121,7 +1148,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 xy_moments_scaled(t1, X1);
                 xy_moments_scaled(t2, X2);
             } else {
-                xy_moments(t0, X0);
+                xy_moments(t0, w, X0);
                 xy_moments(t1, X1);
                 xy_moments(t2, X2);
             }
@@ -1163,10 +1190,11 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 });
             } else {
             // The populations of c_z = -1, 0, +1 sum to M, Z, P (X = X0 + c_z X1 +
-            // (c_z^2 - 1/3) X2) and belong to planes r - 1, r, r + 1.  Kept for the
-            // plane above: P (ZP); for the plane r itself, which still lacks the M of
-            // plane r + 1: Z (ZA) and P(r - 1) - Z (ZD) where the first or second z
-            // moment is needed too (rho', j_x, j_y), else their weighted sum (ZQ).
+            // (c_z^2 - 1/3) X2) and belong to planes r - 1, r, r + 1.  The plane r still
+            // lacks the M of plane r + 1.  Kept for it: of rho', which needs all three z
+            // moments, Z (ZA) and P(r - 1) - Z (ZD); of the others the weighted sum of
+            // Z and P(r - 1) (ZS), and of j_x and j_y, whose first z moment is needed too,
+            // P(r - 1) itself (ZO).  For the plane above: P (ZP).
             // rho' of the own column comes back last, one rounding at its magnitude, which
             // also keeps the density of a uniform stream from creeping by rounding (a
             // tenth of an ulp a step stays below what the sum resolves).  With variable
@@ -1174,27 +1202,34 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             // and the exact differences between planes (dr, from ZR) enter, with which a
             // droplet at density ratio 1:10 keeps its stress within 7e-6 of the oracle
             // after 200 steps (1.1e-5 with p* added in).
+            // Elsewhere the large term comes in last, so that M, P and ZS are rounded once
+            // at its magnitude.  With that, the differences of xy_moments and J rounded
+            // once, the rms error of the stress against binary64 is, after ten steps of a
+            // 256^3 vortex 8.3e-10 (9.2e-10 with Z, P - Z and a rounding more in each of M,
+            // P and J; 8.5e-10 where 27 populations are summed), of a 128 x 128 x 256 jet
+            // 2.26e-10 (2.33e-10, 2.28e-10); of the velocity 2.5e-9 and 1.11e-9 (5.7e-9 and
+            // 1.16e-9, 5.7e-9 and 1.20e-9).
             // In this order (held by the empty asm statements) each carried value is
             // formed in the register of the one it replaces.
             float M[6];
             each<6>([&](auto i_) {
                 constexpr int k = i_;
-                M[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) - X1[k];
+                M[k] = k ? X0[k] + fmaf(X2[k], 2.0f / 3.0f, -X1[k]) : fmaf(X2[k], 2.0f / 3.0f, X0[k]) - X1[k];
             });
             if constexpr (VD)
                 dr = rpc - ZR;
             else
                 M[0] += rpc;
             // (X carries the factors 1, 6, 6, 9, 9, 36 of xy_moments)
-            const float d00 = VD ? (M[0] - ZA[0]) + dr : M[0] - ZA[0], d10 = M[1] - ZA[1], d01 = M[2] - ZA[2];
-            const float s00 = d00 + ZD[0];
-            const float drho = VD ? ZR + fmaf(s00, 1.0f / 6.0f, ZA[0]) : fmaf(s00, 1.0f / 6.0f, ZA[0]);
-            const float jz = (ZD[0] - d00) * (1.0f / 6.0f), Hzz = s00 * (1.0f / 9.0f);
-            const float jx = fmaf(d10 + ZD[1], 1.0f / 6.0f, ZA[1]) * (1.0f / 6.0f), Hxz = (ZD[1] - d10) * (1.0f / 36.0f);
-            const float jy = fmaf(d01 + ZD[2], 1.0f / 6.0f, ZA[2]) * (1.0f / 6.0f), Hyz = (ZD[2] - d01) * (1.0f / 36.0f);
-            const float Hxx = fmaf(M[3], 1.0f / 54.0f, ZQ[0]);
-            const float Hyy = fmaf(M[4], 1.0f / 54.0f, ZQ[1]);
-            const float Hxy = fmaf(M[5], 1.0f / 216.0f, ZQ[2]);
+            const float d00 = VD ? (M[0] - ZA) + dr : M[0] - ZA;
+            const float s00 = d00 + ZD;
+            const float drho = VD ? ZR + fmaf(s00, 1.0f / 6.0f, ZA) : fmaf(s00, 1.0f / 6.0f, ZA);
+            const float jz = (ZD - d00) * (1.0f / 6.0f), Hzz = s00 * (1.0f / 9.0f);
+            const float jx = fmaf(M[1], 1.0f / 36.0f, ZS[0]), Hxz = (ZO[0] - M[1]) * (1.0f / 36.0f);
+            const float jy = fmaf(M[2], 1.0f / 36.0f, ZS[1]), Hyz = (ZO[1] - M[2]) * (1.0f / 36.0f);
+            const float Hxx = fmaf(M[3], 1.0f / 54.0f, ZS[2]);
+            const float Hyy = fmaf(M[4], 1.0f / 54.0f, ZS[3]);
+            const float Hxy = fmaf(M[5], 1.0f / 216.0f, ZS[4]);
             const float inv = VD ? 1.0f : recip(1.0f + drho);
             m[0] = drho;
             m[1] = jx * inv;
@@ -1223,19 +1258,25 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 constexpr int k = i_;
                 keep_here(X0[k], X2[k]);
             });
-            each<3>([&](auto i_) {
-                constexpr int k = i_;
-                ZA[k] = fmaf(X2[k], -1.0f / 3.0f, X0[k]);
-                if (!VD && k == 0) ZA[0] += rpc;
-                ZD[k] = VD && k == 0 ? (ZP[k] - ZA[k]) - dr : ZP[k] - ZA[k];
-                const float c = k == 2 ? 1.0f / 216.0f : 1.0f / 54.0f;
-                ZQ[k] = fmaf(fmaf(X2[3 + k], -1.0f / 3.0f, X0[3 + k]), 4.0f * c, ZP[3 + k] * c);
-                keep_here(ZA[k], ZD[k], ZQ[k]);
+            ZA = fmaf(X2[0], -1.0f / 3.0f, X0[0]);
+            if (!VD) ZA += rpc;
+            ZD = VD ? (ZP[0] - ZA) - dr : ZP[0] - ZA;
+            keep_here(ZA, ZD);
+            each<5>([&](auto i_) {
+                constexpr int k = i_ + 1;  // weights (1, 4, 1)/6 over the factor of X
+                constexpr float c = k < 3 ? 1.0f / 36.0f : k < 5 ? 1.0f / 54.0f : 1.0f / 216.0f;
+                constexpr float c3 = k < 3 ? 1.0f / 27.0f : k < 5 ? 2.0f / 81.0f : 1.0f / 162.0f;  // 4 c / 3
+                ZS[k - 1] = fmaf(X0[k], 4.0f * c, fmaf(X2[k], -c3, ZP[k] * c));
+                keep_here(ZS[k - 1]);
+                if constexpr (k < 3) {
+                    ZO[k - 1] = ZP[k];
+                    keep_here(ZO[k - 1]);
+                }
             });
             each<6>([&](auto i_) {
                 constexpr int k = i_;
                 keep_here(X2[k]);
-                ZP[k] = fmaf(X2[k], 2.0f / 3.0f, X0[k]) + X1[k];
+                ZP[k] = k ? X0[k] + fmaf(X2[k], 2.0f / 3.0f, X1[k]) : fmaf(X2[k], 2.0f / 3.0f, X0[k]) + X1[k];
             });
             if constexpr (VD)
                 ZR = rpc;
