@@ -96,13 +96,6 @@ int refresh_completed(tslb_group *g) {
     return TSLB_OK;
 }
 
-// z chunk length of a lattice of nz planes under the bound L: ceil(nz / L)
-// chunks of near-equal length.
-int chunk_under_bound(int nz, int L) {
-    const int k = (nz + L - 1) / L;
-    return (nz + k - 1) / k;
-}
-
 // End time, in half planes, of one launch whose work items take cost[i] half
 // planes each: the items are split into eight contiguous ranges, one per XCD
 // (xcd_work_item), and the compute units of an XCD take their range's items
@@ -159,10 +152,10 @@ int plan_chunk_bound(tslb_group *g, int cl) {
         cost.clear();
         for (const tslb_ctx *c : now) {
             const int nz = c->geo.nz, lz = chunk_under_bound(nz, L);
-            const int chunks = (nz + lz - 1) / lz;
+            const int chunks = (int)chunk_count(nz, lz);
             const int tiles = fused_work_items(c, nz);  // one chunk of nz planes: the tile count
             for (int j = 0; j < chunks; ++j) {
-                const int walk = fused_walk2(c, std::min(lz, nz - j * lz));
+                const int walk = (int)fused_walk2(c, std::min(lz, nz - j * lz));
                 for (int t = 0; t < tiles; ++t) cost.push_back(walk);
             }
         }

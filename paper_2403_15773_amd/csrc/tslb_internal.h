@@ -8,6 +8,7 @@
 
 #include "../../include/tslb.h"
 #include "tslb_device.h"
+#include "tslb_plan.h"
 
 namespace tslb {
 
@@ -115,17 +116,13 @@ hipError_t launch_boundary(const tslb_ctx *c, StateView st, int64_t step, hipStr
 hipError_t launch_step(const tslb_ctx *c, StateView in, StateView out, int64_t step_next, hipStream_t s);
 hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int lz, int64_t step_next,
                              hipStream_t s);
-// Tile height (16 or 20 rows) and z chunk of the fused step of ctx c.
-struct FusedPlan {
-    int rows = 16;
-    int lz = 1;
-};
+// Tile height and z chunk of the fused step of ctx c.
 FusedPlan fused_plan(const tslb_ctx *c);
 int fused_chunk(const tslb_ctx *c);
 int fused_rows(const tslb_ctx *c);
 // Cost of a chunk of lz planes for its workgroup, in half planes (the chunk and
 // the fill of the pipeline).
-int fused_walk2(const tslb_ctx *c, int lz);
+long long fused_walk2(const tslb_ctx *c, int lz);
 // Whether the 20-row tile serves ctx c (two components, equal densities).
 bool fused_wide_allowed(const tslb_ctx *c);
 // Describe one step of ctx c (in -> out) as a domain of a multi-domain launch

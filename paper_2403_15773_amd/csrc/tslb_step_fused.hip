@@ -1409,122 +1409,29 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(co
 
 }  // namespace fused
 
-// Tile height and z planes per workgroup.  A workgroup on a chunk of lz planes
-// walks lz planes and the fill of its pipeline, and the W work items of a launch
-// give each CU ceil(W / CUs) of them, so the cost of a plan is
-// ceil(W / CUs) (lz + fill) c, with c the time of one pipeline plane of a
-// workgroup: 1 for 16 rows and kWideCost for 20 rows.
-// fill: one round of workgroups takes 1.97 (lz + 6.4) us with two components and
-// 1.55 (lz + 4.5) with one (32^3 to 64^3 lattices, lz 1 to 8, launch included), of
-// which 3 are planes of the loop and, with two, the geometry's prologue.  So the
-// shortest chunks pay as long as they fill idle CUs: 32^3 droplet 20.4 us a step at 4
-// planes, 14.6 at 1; 48^3 21.2 at 4, 17.0 at 2; 40^3 vortex 13.2 at 4, 8.6 at 1.
-// kWideCost: 400 x 400 x 800 jet 2.83 us a plane on 16 rows, 3.47 on 20 (1.22);
-// 512 x 512 x 2048 jet 2.87 and 3.59 (1.25); 100 x 100 x 200 1.24.
-// Long chunks recompute less halo, short ones keep every unit busy; ties go to the
-// shorter chunk, then to 16 rows.  Chunks are capped at kMaxChunk planes:
-// workgroups that share halo columns run side by side, but over a long chunk
-// they drift apart in z and their shared halo planes leave L2 before the
-// neighbour reads them (HBM reads 1.48x the state at 2048 planes on a
-// 512 x 512 x 2048 lattice, against 1.06x at 64 on 128 x 128 x 512).  On that
-// lattice 16 rows take 12.38 and 12.36 ms at 64 and 128 planes, 20 rows 12.50,
-// 12.54 and 12.79 at 64, 128 and 256.
-// 16-bit moments: 20 rows cost 1.31 (512 x 512 x 2048) to 1.48 (200 x 200 x 400), since
-// their geometry, four waves' work there, is the longest chain of phase A.
-// 20 rows serve the two-component step with equal densities; the one-component
-// and the variable-density step take 16.  A height or chunk length fixed with
-// tslb_set_tile / tslb_set_kernel is taken as given.
-constexpr int kMaxChunk = 128;
-constexpr double kWideCost = 1.22, kWideCostHalf = 1.35;
-
-// Planes a workgroup on a chunk of lz planes walks, doubled.
-int fused_walk2(const tslb_ctx *c, int lz) { return 2 * lz + (c->phase ? 13 : 9); }
-
-// Whether the step's stores carry the non-temporal hint, where a launch writes
-// launch_bytes in all (a launch over several lattices takes what most of its bytes
-// call for).  A line stored with it goes out at once; without it the line
-// stays in L2 until it is complete and then in the 256 MB cache behind.
-//  - A lattice up to kTinyState bytes: hint.  Its launch is a few planes long and
-//    would end with the lines still to be written back (61 x 45 x 83 box 18.6 us a step
-//    with, 19.5 without; 64^3 vortex 10.6, 11.0; 66^3 droplet, 12.7 MB, 22.6 both).
-//  - Rows that do not begin at 128-byte lines: none.  The two tiles that share a
-//    line write it at different times, and the halves go to memory as partial writes
-//    (250 x 256 x 400 jet: 26.4 M write requests against 18.0 M at 256 wide; 250 x 250 x
-//    400 jet 832 us with, 618 without; 300 x 300 x 600 jet 1919 and 1418; 200 x 200 x 400
-//    FP16Q 506 and 487; 16-bit rows of a tile are half a line).
-//  - Whole lines, state and new state within the cache: none, the next step reads from
-//    it (128^3 droplet 55.4 and 48.6, 128^3 vortex 42.1 and 34.4).
-//  - Whole lines, larger: hint, since lines written without it take L2 from the halo
-//    lines that neighbouring workgroups read again (512 x 512 x 2048 jet 12.3 ms and
-//    12.6, 256^3 vortex 262 us and 271, 160^3 droplet 101.5 and 102).
-constexpr size_t kTinyState = 13u << 20, kFarCache = 256u << 20;
-bool fused_stream_stores(const tslb_ctx *c, size_t launch_bytes) {
-    if (launch_bytes <= kTinyState) return true;
-    if (c->geo.nx % (c->storage == ST_FP32 ? 32 : 64)) return false;  // words of a 128-byte line
-    return 2 * launch_bytes > kFarCache;
-}
-
 bool fused_wide_allowed(const tslb_ctx *c) { return c->phase && !c->vd; }
 
 namespace {
 
-int tiles_of(const tslb_ctx *c, int rows) {
-    return ((c->geo.nx + fused::Tile<16>::TX - 1) / fused::Tile<16>::TX) * ((c->geo.ny + rows - 1) / rows);
-}
-
-// Cheapest chunk length for `rows` and its cost (in 16-row plane times).
-double best_chunk(const tslb_ctx *c, int rows, int *lz_out) {
-    const long long tiles = tiles_of(c, rows);
-    const long long cus = std::max(1, c->cu_count);
-    const int nz = c->geo.nz;
-    const double f = rows == 16 ? 1.0 : c->storage == ST_FP32 ? kWideCost : kWideCostHalf;
-    auto cost_of = [&](int lz) {
-        const long long w = tiles * ((nz + lz - 1) / lz);
-        return (double)((w + cus - 1) / cus) * (0.5 * fused_walk2(c, lz)) * f;
-    };
-    if (c->chunk_z > 0) {
-        *lz_out = c->chunk_z;
-        return cost_of(c->chunk_z);
-    }
-    int best_lz = 1;
-    double best = -1.0;
-    for (int k = 1; k <= nz; ++k) {  // k chunks of ceil(nz / k) planes
-        const int lz = (nz + k - 1) / k;
-        if (k > 1 && lz == (nz + k - 2) / (k - 1)) continue;  // same length as k - 1 chunks
-        if (lz > kMaxChunk) continue;
-        const double cost = cost_of(lz);
-        if (best < 0 || cost <= best) {
-            best = cost;
-            best_lz = lz;
-        }
-    }
-    *lz_out = best_lz;
-    return best < 0 ? cost_of(best_lz) : best;
+PlanShape shape_of(const tslb_ctx *c) {
+    static_assert(fused::Tile<16>::TX == kTileX && fused::Tile<20>::TX == kTileX, "tiles of the plan");
+    return {c->geo.nx, c->geo.ny, c->geo.nz, c->phase, fused_wide_allowed(c), c->storage != ST_FP32, c->cu_count};
 }
 
 }  // namespace
 
-FusedPlan fused_plan(const tslb_ctx *c) {
-    FusedPlan pl;
-    int lz16 = 0, lz20 = 0;
-    const double c16 = best_chunk(c, 16, &lz16);
-    pl.rows = 16;
-    pl.lz = lz16;
-    if (!fused_wide_allowed(c) || c->tile_rows == 16) return pl;
-    const double c20 = best_chunk(c, 20, &lz20);
-    if (c->tile_rows == 20 || c20 < c16) {
-        pl.rows = 20;
-        pl.lz = lz20;
-    }
-    return pl;
-}
+FusedPlan fused_plan(const tslb_ctx *c) { return plan_fused(shape_of(c), c->chunk_z, c->tile_rows); }
+
+long long fused_walk2(const tslb_ctx *c, int lz) { return fused_walk2(shape_of(c), lz); }
+
+bool fused_stream_stores(const tslb_ctx *c, size_t launch_bytes) { return stream_stores(shape_of(c), launch_bytes); }
 
 int fused_chunk(const tslb_ctx *c) { return c->plan_lz; }
 
 int fused_rows(const tslb_ctx *c) { return c->plan_rows; }
 
 int fused_work_items(const tslb_ctx *c, int lz) {
-    return tiles_of(c, fused_rows(c)) * ((c->geo.nz + lz - 1) / lz);
+    return (int)(fused_tiles(shape_of(c), fused_rows(c)) * chunk_count(c->geo.nz, lz));
 }
 
 FusedDomain fused_domain(const tslb_ctx *c, StateView in, StateView out, int64_t step_next, int work_begin,
@@ -1540,7 +1447,7 @@ FusedDomain fused_domain(const tslb_ctx *c, StateView in, StateView out, int64_t
     d.tiles_x = (c->geo.nx + fused::Tile<16>::TX - 1) / fused::Tile<16>::TX;
     d.tiles_y = (c->geo.ny + c->plan_rows - 1) / c->plan_rows;
     d.work_begin = work_begin;
-    d.work_count = d.tiles_x * d.tiles_y * ((c->geo.nz + d.lz - 1) / d.lz);
+    d.work_count = fused_work_items(c, d.lz);
     return d;
 }
 
@@ -1570,8 +1477,7 @@ hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int
     const int rows = fused_rows(c);
     const int tiles_x = (c->geo.nx + fused::Tile<16>::TX - 1) / fused::Tile<16>::TX;
     const int tiles_y = (c->geo.ny + rows - 1) / rows;
-    const int chunks = (c->geo.nz + lz - 1) / lz;
-    const unsigned blocks = (unsigned)tiles_x * tiles_y * chunks;
+    const unsigned blocks = (unsigned)fused_work_items(c, lz);
     const unsigned long long sn = (unsigned long long)step_next;
     if (c->vd) {  // variable density: two components, 16 rows (validated at creation)
         if (!c->phase || rows != 16) return hipErrorInvalidValue;
