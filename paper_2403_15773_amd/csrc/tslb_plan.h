@@ -133,4 +133,10 @@ inline bool stream_stores(const PlanShape &s, size_t launch_bytes) {
     return 2 * launch_bytes > kFarCache;
 }
 
+// Workgroups of one launch when `items` are left: a launch takes at most 2^32 - 1
+// threads, 4194303 workgroups of 1024.  Chunks of 128 planes stay far below that on
+// every lattice that is wide enough to fill its tiles; a lattice of one column and more
+// than 5e8 planes, or one whose chunk the caller sets to a plane, does not.
+inline long long launch_blocks(long long items, int threads) { return std::min(items, 0xFFFFFFFFll / threads); }
+
 }  // namespace tslb

@@ -1356,21 +1356,21 @@ static_assert(sizeof(Geo) % alignof(Phys) == 0 && alignof(Geo) == alignof(Phys),
 template <int ST, bool PH, bool VD, int ROWS, bool NT>
 __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
                                                                int lz, int tiles_x, int tiles_y,
-                                                               unsigned long long step_next) {
+                                                               unsigned long long step_next, int first) {
     __shared__ Smem<PH, VD, ROWS> sm;
     // ph sits behind g in the kernel's argument segment
     const PhysMem walls = (PhysMem)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
                                     sizeof(Geo));
     step_fused<ST, PH, false, VD, ROWS, NT>(sm, g, ph, walls, sc, in, out, lz, tiles_x, tiles_y, step_next,
-                                               xcd_work_item(blockIdx.x, gridDim.x));
+                                               first + xcd_work_item(blockIdx.x, gridDim.x));
 }
 
 // Several lattices in one launch: the work items of domain k are
 // [work_begin, work_begin + tiles * chunks); domains are sorted by work_begin.
 template <int ST, bool PH, bool VD, int ROWS, bool NT>
-__global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(const FusedDomain *__restrict__ doms, int ndom) {
+__global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(const FusedDomain *__restrict__ doms, int ndom, int first) {
     __shared__ Smem<PH, VD, ROWS> sm;
-    const int w = xcd_work_item(blockIdx.x, gridDim.x);
+    const int w = first + xcd_work_item(blockIdx.x, gridDim.x);
     int lo = 0, hi = ndom - 1;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -1451,23 +1451,33 @@ FusedDomain fused_domain(const tslb_ctx *c, StateView in, StateView out, int64_t
     return d;
 }
 
-// Launch the fused step over the whole lattice.
+// Launch the fused step over the whole lattice, in as many launches as its work items
+// need (launch_blocks).
 namespace {
 
 template <int ST, bool PH, bool VD, int ROWS>
-void launch_one(unsigned blocks, hipStream_t s, const tslb_ctx *c, StateView in, StateView out, int lz, int tiles_x,
+void launch_one(long long items, hipStream_t s, const tslb_ctx *c, StateView in, StateView out, int lz, int tiles_x,
                 int tiles_y, unsigned long long sn) {
     using namespace fused;
+    constexpr int threads = Tile<ROWS>::threads(PH);
     const bool nt = fused_stream_stores(c, c->buffer_bytes);
-    hipLaunchKernelGGL((nt ? k_step_fused<ST, PH, VD, ROWS, true> : k_step_fused<ST, PH, VD, ROWS, false>), dim3(blocks),
-                       dim3(Tile<ROWS>::threads(PH)), 0, s, c->geo, c->phys, c->scales, in, out, lz, tiles_x, tiles_y, sn);
+    for (long long first = 0, n; first < items; first += n) {
+        n = launch_blocks(items - first, threads);
+        hipLaunchKernelGGL((nt ? k_step_fused<ST, PH, VD, ROWS, true> : k_step_fused<ST, PH, VD, ROWS, false>),
+                           dim3((unsigned)n), dim3(threads), 0, s, c->geo, c->phys, c->scales, in, out, lz, tiles_x,
+                           tiles_y, sn, (int)first);
+    }
 }
 
 template <int ST, bool PH, bool VD, int ROWS>
-void launch_multi(unsigned blocks, hipStream_t s, const FusedDomain *doms, int ndom, bool nt) {
+void launch_multi(long long items, hipStream_t s, const FusedDomain *doms, int ndom, bool nt) {
     using namespace fused;
-    hipLaunchKernelGGL((nt ? k_step_fused_multi<ST, PH, VD, ROWS, true> : k_step_fused_multi<ST, PH, VD, ROWS, false>),
-                       dim3(blocks), dim3(Tile<ROWS>::threads(PH)), 0, s, doms, ndom);
+    constexpr int threads = Tile<ROWS>::threads(PH);
+    for (long long first = 0, n; first < items; first += n) {
+        n = launch_blocks(items - first, threads);
+        hipLaunchKernelGGL((nt ? k_step_fused_multi<ST, PH, VD, ROWS, true> : k_step_fused_multi<ST, PH, VD, ROWS, false>),
+                           dim3((unsigned)n), dim3(threads), 0, s, doms, ndom, (int)first);
+    }
 }
 
 }  // namespace
@@ -1477,21 +1487,21 @@ hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int
     const int rows = fused_rows(c);
     const int tiles_x = (c->geo.nx + fused::Tile<16>::TX - 1) / fused::Tile<16>::TX;
     const int tiles_y = (c->geo.ny + rows - 1) / rows;
-    const unsigned blocks = (unsigned)fused_work_items(c, lz);
+    const long long items = fused_work_items(c, lz);
     const unsigned long long sn = (unsigned long long)step_next;
     if (c->vd) {  // variable density: two components, 16 rows (validated at creation)
         if (!c->phase || rows != 16) return hipErrorInvalidValue;
-        launch_one<ST_FP32, true, true, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);
+        launch_one<ST_FP32, true, true, 16>(items, s, c, in, out, lz, tiles_x, tiles_y, sn);
         return hipGetLastError();
     }
 #define TSLB_FUSED_CASE(ST)                                                                            \
     case ST:                                                                                           \
         if (!c->phase)                                                                                 \
-            launch_one<ST, false, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);         \
+            launch_one<ST, false, false, 16>(items, s, c, in, out, lz, tiles_x, tiles_y, sn);         \
         else if (rows == 20)                                                                           \
-            launch_one<ST, true, false, 20>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
+            launch_one<ST, true, false, 20>(items, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
         else                                                                                           \
-            launch_one<ST, true, false, 16>(blocks, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
+            launch_one<ST, true, false, 16>(items, s, c, in, out, lz, tiles_x, tiles_y, sn);          \
         break;
     switch (c->storage) {
         TSLB_FUSED_CASE(ST_FP32)
@@ -1508,21 +1518,20 @@ hipError_t launch_step_fused(const tslb_ctx *c, StateView in, StateView out, int
 hipError_t launch_step_fused_multi(const FusedDomain *doms, int ndom, int total_work, int storage, bool phase,
                                    bool vd, int rows, bool nt, hipStream_t s) {
     if (ndom <= 0 || total_work <= 0) return hipSuccess;
-    const unsigned blocks = (unsigned)total_work;
     if (vd) {
         if (!phase || rows != 16 || storage != ST_FP32) return hipErrorInvalidValue;
-        launch_multi<ST_FP32, true, true, 16>(blocks, s, doms, ndom, nt);
+        launch_multi<ST_FP32, true, true, 16>(total_work, s, doms, ndom, nt);
         return hipGetLastError();
     }
     if (rows != 16 && (rows != 20 || !phase)) return hipErrorInvalidValue;
 #define TSLB_MULTI_CASE(ST)                                                                            \
     case ST:                                                                                           \
         if (!phase)                                                                                    \
-            launch_multi<ST, false, false, 16>(blocks, s, doms, ndom, nt);                                 \
+            launch_multi<ST, false, false, 16>(total_work, s, doms, ndom, nt);                                 \
         else if (rows == 20)                                                                           \
-            launch_multi<ST, true, false, 20>(blocks, s, doms, ndom, nt);                                  \
+            launch_multi<ST, true, false, 20>(total_work, s, doms, ndom, nt);                                  \
         else                                                                                           \
-            launch_multi<ST, true, false, 16>(blocks, s, doms, ndom, nt);                                  \
+            launch_multi<ST, true, false, 16>(total_work, s, doms, ndom, nt);                                  \
         break;
     switch (storage) {
         TSLB_MULTI_CASE(ST_FP32)

@@ -84,8 +84,9 @@ def test_longest_lattices_are_planned_without_overflow(planner, nx, ny, nz):
     t = time.perf_counter()
     _, got = planner(cases)
     assert time.perf_counter() - t < 10.0
-    for c, (rows, lz, items, _) in zip(cases, got):
+    for c, (rows, lz, items, _, launches) in zip(cases, got):
         assert 1 <= lz <= nz and items == -(-nx // 32) * -(-ny // rows) * -(-nz // lz)
+        assert launches == -(-items // 4194303)  # each within 2^32 - 1 threads
         if c[7]:
             assert lz == min(c[7], nz)
         elif nz > 1000000:  # workgroups are plenty: the longest chunks cost least
