@@ -637,7 +637,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 constexpr float kS = kPhiUlp / 72.0f;
 #pragma unroll
                 for (int k = 0; k < NG; ++k) {
-                    if (k && l + k * NGT >= NGP) break;  // whole waves have no further pair
+                    if (k && l + k * NGT >= NGP) break;  // 20 rows: the last waves have no second pair, one has some
                     int32_t q[12], q0[12], qm[12];
                     read_phi(k, it + 1, q);
                     if constexpr (H) {
