@@ -285,10 +285,11 @@ int tslb_set_kernel(tslb_ctx *ctx, int kernel, int chunk_z);
 /* Height of the fused step's tiles (workgroups of 32 x rows destination
  * columns): rows = 16 or 20 fixes it, 0 (the default) lets the library choose
  * per lattice together with the z chunk, by the same cost model (a 20-row
- * workgroup walks a plane in 1.22 times the time of a 16-row one, 1.35 times
- * with 16-bit moments, and updates 1.25 times the columns; the height that gives each compute unit the least
- * time wins).  20 rows serve the two-component step with equal densities only
- * (TSLB_E_INVAL otherwise); the result is bitwise the same at either height.
+ * workgroup is taken to walk a plane in 1.22 times the time of a 16-row one,
+ * 1.26 times with 16-bit moments, and updates 1.25 times the columns; the height
+ * that gives each compute unit the least time wins).  20 rows serve the
+ * two-component step with equal densities only (TSLB_E_INVAL otherwise); the
+ * result is bitwise the same at either height.
  * Not while the ctx is in a serving group (TSLB_E_STATE). */
 int tslb_set_tile(tslb_ctx *ctx, int rows);
 

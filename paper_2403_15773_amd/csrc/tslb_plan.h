@@ -41,28 +41,33 @@ inline int chunk_under_bound(int nz, int L) {
 // give each CU ceil(W / CUs) of them, so the cost of a plan is
 // ceil(W / CUs) (lz + fill) c, with c the time of one pipeline plane of a
 // workgroup: 1 for 16 rows and kWideCost for 20 rows.
-// fill: one round of workgroups takes 1.97 (lz + 6.4) us with two components and
-// 1.55 (lz + 4.5) with one (32^3 to 64^3 lattices, lz 1 to 8, launch included), of
-// which 3 are planes of the loop and, with two, the geometry's prologue.  So the
-// shortest chunks pay as long as they fill idle CUs: 32^3 droplet 20.4 us a step at 4
-// planes, 14.6 at 1; 48^3 21.2 at 4, 17.0 at 2; 40^3 vortex 13.2 at 4, 8.6 at 1.
-// kWideCost: 400 x 400 x 800 jet 2.83 us a plane on 16 rows, 3.47 on 20 (1.22);
-// 512 x 512 x 2048 jet 2.87 and 3.59 (1.25); 100 x 100 x 200 1.24.
+// fill: one round of workgroups takes 1.97 (lz + 6.2 to 6.6) us with two components
+// and 1.57 (lz + 4.4 to 4.9) with one (32^3 to 64^3 lattices, lz 1 to 12, launch
+// included), of which 3 are planes of the loop and, with two, the geometry's prologue;
+// 6.5 and 4.5 are taken.  So the shortest chunks pay as long as they fill idle CUs: 32^3
+// droplet 20.2 us a step at 4 planes, 14.4 at 1; 48^3 20.9 at 4, 16.8 at 2; 40^3 vortex
+// 13.7 at 4, 9.0 at 1.
+// Cost of 20 rows, from jets timed at both heights: about 1.25 in one round of
+// workgroups, 1.15 to 1.30 in several, where the last round is not full and neighbours
+// share less.  Of 32 jets in binary32 1.22 takes the faster height or one within 4.7 %
+// (512 x 512 x 2048: 20 rows between 1.5 % faster and 1.5 % slower on two devices;
+// 320 x 240 x 640 16 rows, 1116 and 1081 us; 157 x 229 x 103 20 rows, 110 and 115), 0.45 %
+// on average.  With 16-bit moments their geometry, four waves' work there, is the
+// longer chain of phase A: 1.23 to 1.32, of 31 jets in each type 1.26 takes the faster or
+// one within 3.5 %, 0.06 % on average (at 1.35 0.7 %, up to 6.9 %: 200 x 200 x 400 FP16Q
+// 465 us on 16 rows, 438 on 20; 103 x 97 x 514 175 and 164; at 1.18 1.8 %).
 // Long chunks recompute less halo, short ones keep every unit busy; ties go to the
 // shorter chunk, then to 16 rows.  Chunks are capped at kMaxChunk planes:
 // workgroups that share halo columns run side by side, but over a long chunk
 // they drift apart in z and their shared halo planes leave L2 before the
 // neighbour reads them (HBM reads 1.48x the state at 2048 planes on a
 // 512 x 512 x 2048 lattice, against 1.06x at 64 on 128 x 128 x 512).  On that
-// lattice 16 rows take 12.38 and 12.36 ms at 64 and 128 planes, 20 rows 12.50,
-// 12.54 and 12.79 at 64, 128 and 256.
-// 16-bit moments: 20 rows cost 1.31 (512 x 512 x 2048) to 1.48 (200 x 200 x 400), since
-// their geometry, four waves' work there, is the longest chain of phase A.
+// lattice 16 rows take 11.65 and 11.38 ms at 64 and 128 planes, 20 rows 11.80 and 11.58.
 // 20 rows serve the two-component step with equal densities; the one-component
 // and the variable-density step take 16.  A height or chunk length fixed with
 // tslb_set_tile / tslb_set_kernel is taken as given.
 constexpr int kMaxChunk = 128;
-constexpr double kWideCost = 1.22, kWideCostHalf = 1.35;
+constexpr double kWideCost = 1.22, kWideCostHalf = 1.26;
 
 // Planes a workgroup on a chunk of lz planes walks, doubled.
 inline long long fused_walk2(const PlanShape &s, int lz) { return 2ll * lz + (s.phase ? 13 : 9); }

@@ -89,7 +89,8 @@ namespace fused {
 // Tile shapes.  A workgroup owns TX x TY destination columns; its sources, the
 // geometry and the staged phase field cover the tile plus a halo of 1, 2 and 3
 // columns.  Two heights: 16 rows (10 waves with a source, 6 of geometry) and 20
-// rows (12 and 4: 1.23 times the time a plane for 1.25 times the columns), chosen
+// rows (12 and 4: about 1.25 times the time a plane for 1.25 times the columns, but fewer
+// workgroups where that saves a round), chosen
 // per lattice by the host (fused_plan); the one-component and variable-density
 // steps take 16 rows, the former without geometry waves.
 template <int ROWS> struct Tile {

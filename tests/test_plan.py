@@ -100,3 +100,24 @@ def test_store_hint(planner):
               (96, 1, 900 * mb), (128, 1, 900 * mb), (128, 1, 100 * mb), (250, 0, 900 * mb)]]
     _, got = planner(cases)
     assert [g[3] for g in got] == [1, 0, 0, 0, 1, 1, 0, 1, 0, 0]
+
+
+@pytest.mark.parametrize("half,shape,rows", [
+    # two components on 256 compute units: the height that is at least 3.5 % faster in each of the
+    # 16-bit types (us a step on 16 and 20 rows, FP16 and FP16Q)
+    (1, (103, 97, 514), 20),   # 171 162, 175 164
+    (1, (119, 161, 196), 20),  # 116 111, 118 111
+    (1, (66, 38, 415), 20),    # 52.1 50.0, 52.6 50.4
+    (1, (128, 128, 512), 16),  # 192 214, 198 218
+    (1, (237, 41, 113), 16),   # 44.2 56.2, 44.9 56.2
+    (1, (398, 396, 510), 16),  # 1859 1987, 1986 2097
+    (1, (171, 102, 105), 16),  # 59.6 66.3, 60.3 66.2
+    # binary32
+    (0, (119, 161, 196), 20),  # 116 111
+    (0, (128, 128, 512), 16),  # 185 202
+    (0, (398, 396, 510), 16),  # 2134 2250
+    (0, (52, 203, 69), 16),    # 30.7 35.7
+])
+def test_faster_tile_height_is_taken(planner, half, shape, rows):
+    _, got = planner([shape + (1, 1, half, 256, 0, 0, 1 << 30)])
+    assert got[0][0] == rows
