@@ -724,8 +724,9 @@ int tslb_stats_get(tslb_ctx *c, float *mean_phi, float *mean_u, float *rms_uz, i
     const size_t N = (size_t)c->geo.N, ld = (size_t)c->geo.ld;
     const double inv = 1.0 / (double)c->stats.samples;
     if (c->scratch.geo) {
-        // while sampling goes on the geometry planes are there, and every sample writes
-        // them anew: the means are formed in them and copied out
+        // The geometry planes are there (release_planes keeps them while samples are
+        // taken or the gather step is selected), and whatever reads them writes them
+        // first: the means are formed in them and copied out.
         float *out = c->scratch.geo;
         hipError_t e = launch_stats_means(c, inv, c->stats.sum, out, c->stream);
         if (e == hipSuccess && mean_phi) e = hipMemcpyAsync(mean_phi, out, N * 4, hipMemcpyDeviceToHost, c->stream);
@@ -737,8 +738,8 @@ int tslb_stats_get(tslb_ctx *c, float *mean_phi, float *mean_u, float *rms_uz, i
         if (e != hipSuccess) return fail(c, TSLB_E_DEVICE, std::string("statistics: ") + hipGetErrorString(e));
         return TSLB_OK;
     }
-    // After tslb_stats_stop they are gone, and nothing is allocated here: the five sum
-    // planes come over in blocks of nodes through a bounded host buffer.
+    // Without them nothing is allocated on the device: the five sum planes come over in
+    // blocks of nodes through a bounded host buffer.
     const size_t blk = std::min(N, (size_t)1 << 22);
     std::vector<double> h;
     try {

@@ -125,12 +125,18 @@ inline FusedPlan plan_fused(const PlanShape &s, int chunk_z, int tile_rows) {
 //    line write it at different times, and the halves go to memory as partial writes
 //    (250 x 256 x 400 jet: 26.4 M write requests against 18.0 M at 256 wide; 250 x 250 x
 //    400 jet 832 us with, 618 without; 300 x 300 x 600 jet 1919 and 1418; 200 x 200 x 400
-//    FP16Q 506 and 487; 16-bit rows of a tile are half a line).
+//    FP16Q 506 and 487).
 //  - Whole lines, state and new state within the cache: none, the next step reads from
 //    it (128^3 droplet 55.4 and 48.6, 128^3 vortex 42.1 and 34.4).
 //  - Whole lines, larger: hint, since lines written without it take L2 from the halo
 //    lines that neighbouring workgroups read again (512 x 512 x 2048 jet 12.3 ms and
-//    12.6, 256^3 vortex 262 us and 271, 160^3 droplet 101.5 and 102).
+//    12.6, 512 x 512 x 1024 5.46 and 5.79, 256^3 vortex 263 us and 274, 160^3 droplet
+//    101.5 and 102).
+//  - 16-bit rows of a tile are half a line, so that two tiles share it at any width; on
+//    widths of whole lines the hint makes little difference: 512 x 512 x 2048 jet FP16
+//    11.03 ms with, 11.12 without, BF16 11.43 and 11.42, FP16Q 11.72 and 11.78; 256 x 256 x
+//    512 674 us and 666, 697 and 694, 678 and 679; one component 256^3 FP16 265 and 263,
+//    384^3 FP16Q 1037 and 1009.  They follow the rule of binary32.
 constexpr size_t kTinyState = 13u << 20, kFarCache = 256u << 20;
 inline bool stream_stores(const PlanShape &s, size_t launch_bytes) {
     if (launch_bytes <= kTinyState) return true;

@@ -56,9 +56,9 @@
 //   destination: moments sum_i w_i H(c_i) t_i(x - c_i) as a tensor product of
 //            1-D three-point transforms written relative to the middle value, so
 //            the large isotropic part cancels before rounding.
-// 16-bit stored moments (FP16, BF16, FP16Q) keep another order of this arithmetic, the
-// one above the k-space exchange grew from: populations instead of the T are
-// exchanged, G comes from 13 pairs of neighbours, and sums carry their factors.  A
+// 16-bit stored moments (FP16, BF16, FP16Q) keep an earlier order of this arithmetic:
+// populations instead of the T are exchanged, G comes from 13 pairs of neighbours, and
+// sums carry their factors.  A
 // change of rounding in binary32 turns into other roundings of stored moments, and
 // those travel: ten steps of a jet with BF16 moments then differ by 5e-3 in the
 // stress, as much as from the exact result.  Waves, tiles and the LDS records are the
@@ -811,10 +811,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
         });
         // (the first source plane is z0 - 1, loaded at the first iteration; lanes without
         // a source load a column of the lattice and drop it)
-        if (it == IT0 || it >= 4) {
-            if (it >= 4) kmom = plane_after(r + 1, kmom);
-            load_plane<ST>(in.mom, g.ld, plane * kmom, off_src, mom);
-        }
+        if (it > IT0) kmom = plane_after(r + 1, kmom);
+        load_plane<ST>(in.mom, g.ld, plane * kmom, off_src, mom);
         // ================= phase A =================
         // what the source's own column takes of its populations (used in phase B)
         float T0c, T1c, T2c, rpc;
