@@ -175,6 +175,64 @@ __device__ __forceinline__ void quad3(float A, float B, float C, float &vm, floa
     vp = m + B;
 }
 
+// The T of t(c) = T0 + c_z T1 + (c_z^2 - 1/3) T2 from the Hermite coefficients, without
+// the density (tau = t - rho'): put(ix, iy, T0, T1, T2) for each of the nine (c_x, c_y) =
+// (ix - 1, iy - 1).  H: the roundings that 16-bit stored moments keep (9 a2_yz unrounded).
+template <bool H, class Put>
+__device__ __forceinline__ void expand_c(float Jx, float Jy, float Jz, float a2xx, float a2yy, float a2zz, float a2xy,
+                                         float a2xz, float a2yz, float a3xxy, float a3xxz, float a3yyx, float a3yyz,
+                                         float a3zzx, float a3zzy, float a3xyz, Put &&put) {
+#pragma clang fp contract(off)
+    // The scale factors of the coefficients (3 J, 4.5 a2_aa, 9 a2_ab, 13.5 a3_aab,
+    // 27 a3_xyz) are folded into the constants of the multiply-adds that take
+    // a coefficient as a slope or curvature term; only the five that enter as
+    // an addend are scaled explicitly.
+    const float K1y = 3.0f * Jy, K1z = 3.0f * Jz;
+    const float K2yy = 4.5f * a2yy, K2zz = 4.5f * a2zz, K2yz = 9.0f * a2yz;
+    // t = T0 + cz T1 + h(cz) T2; T0 = U0 + cy U1 + h(cy) U2 (per cx), etc.
+    float U0[3], U1[3], V0[3], W0[3];
+    {   // U0 = quad3(0, 3 Jx, 4.5 a2xx): tau = t - rho'
+        const float m = 3.0f * a2xx;
+        U0[1] = -1.5f * a2xx;
+        U0[0] = fmaf(-3.0f, Jx, m);
+        U0[2] = fmaf(3.0f, Jx, m);
+    }
+    {   // U1 = quad3(3 Jy, 9 a2xy, 13.5 a3xxy)
+        const float m = fmaf(9.0f, a3xxy, K1y);
+        U1[1] = fmaf(-4.5f, a3xxy, K1y);
+        U1[0] = fmaf(-9.0f, a2xy, m);
+        U1[2] = fmaf(9.0f, a2xy, m);
+    }
+    {   // V0 = quad3(3 Jz, 9 a2xz, 13.5 a3xxz)
+        const float m = fmaf(9.0f, a3xxz, K1z);
+        V0[1] = fmaf(-4.5f, a3xxz, K1z);
+        V0[0] = fmaf(-9.0f, a2xz, m);
+        V0[2] = fmaf(9.0f, a2xz, m);
+    }
+    W0[0] = fmaf(-13.5f, a3zzx, K2zz);
+    W0[1] = K2zz;
+    W0[2] = fmaf(13.5f, a3zzx, K2zz);
+#pragma unroll
+    for (int ix = 0; ix < 3; ++ix) {
+        const float cx = (float)(ix - 1);
+        const float U2 = ix == 1 ? K2yy : fmaf(13.5f * cx, a3yyx, K2yy);  // linear in cx
+        const float V1 = ix == 1 ? K2yz : fmaf(27.0f * cx, a3xyz, K2yz);
+        float T0[3], T1[3], T2[3];
+        quad3(U0[ix], U1[ix], U2, T0[0], T0[1], T0[2]);
+        {   // T1 = quad3(V0, V1, 13.5 a3yyz)
+            const float m = fmaf(9.0f, a3yyz, V0[ix]);
+            T1[1] = fmaf(-4.5f, a3yyz, V0[ix]);
+            T1[0] = H && ix == 1 ? fmaf(-9.0f, a2yz, m) : m - V1;
+            T1[2] = H && ix == 1 ? fmaf(9.0f, a2yz, m) : m + V1;
+        }
+        T2[0] = fmaf(-13.5f, a3zzy, W0[ix]);
+        T2[1] = W0[ix];
+        T2[2] = fmaf(13.5f, a3zzy, W0[ix]);
+#pragma unroll
+        for (int iy = 0; iy < 3; ++iy) put(ix, iy, T0[iy], T1[iy], T2[iy]);
+    }
+}
+
 // Slot of direction (cx, cy) != (0, 0) in the exchange buffer of one z group.
 __device__ __forceinline__ constexpr int xy_slot(int cx, int cy) {
     return ((cx + 1) + 3 * (cy + 1)) < 4 ? ((cx + 1) + 3 * (cy + 1)) : ((cx + 1) + 3 * (cy + 1)) - 1;
@@ -905,60 +963,14 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 const float a3zzx = fmaf(u2, fmaf(ru2, u0, 2.0f * mxz), u0 * mzz);
                 const float a3zzy = fmaf(u2, fmaf(ru2, u1, 2.0f * myz), u1 * mzz);
                 const float a3xyz = fmaf(ru0 * u1, u2, fmaf(u0, myz, fmaf(u1, mxz, u2 * mxy)));
-                // The scale factors of the coefficients (3 J, 4.5 a2_aa, 9 a2_ab, 13.5 a3_aab,
-                // 27 a3_xyz) are folded into the constants of the multiply-adds that take
-                // a coefficient as a slope or curvature term; only the five that enter as
-                // an addend are scaled explicitly.
-                const float K1y = 3.0f * Jy, K1z = 3.0f * Jz;
-                const float K2yy = 4.5f * a2yy, K2zz = 4.5f * a2zz, K2yz = 9.0f * a2yz;
-                // t = T0 + cz T1 + h(cz) T2; T0 = U0 + cy U1 + h(cy) U2 (per cx), etc.
-                float U0[3], U1[3], V0[3], W0[3];
-                {   // U0 = quad3(0, 3 Jx, 4.5 a2xx): tau = t - rho'
-                    const float m = 3.0f * a2xx;
-                    U0[1] = -1.5f * a2xx;
-                    U0[0] = fmaf(-3.0f, Jx, m);
-                    U0[2] = fmaf(3.0f, Jx, m);
-                }
-                {   // U1 = quad3(3 Jy, 9 a2xy, 13.5 a3xxy)
-                    const float m = fmaf(9.0f, a3xxy, K1y);
-                    U1[1] = fmaf(-4.5f, a3xxy, K1y);
-                    U1[0] = fmaf(-9.0f, a2xy, m);
-                    U1[2] = fmaf(9.0f, a2xy, m);
-                }
-                {   // V0 = quad3(3 Jz, 9 a2xz, 13.5 a3xxz)
-                    const float m = fmaf(9.0f, a3xxz, K1z);
-                    V0[1] = fmaf(-4.5f, a3xxz, K1z);
-                    V0[0] = fmaf(-9.0f, a2xz, m);
-                    V0[2] = fmaf(9.0f, a2xz, m);
-                }
-                W0[0] = fmaf(-13.5f, a3zzx, K2zz);
-                W0[1] = K2zz;
-                W0[2] = fmaf(13.5f, a3zzx, K2zz);
-#pragma unroll
-                for (int ix = 0; ix < 3; ++ix) {
-                    const float cx = (float)(ix - 1);
-                    const float U2 = ix == 1 ? K2yy : fmaf(13.5f * cx, a3yyx, K2yy);  // linear in cx
-                    const float V1 = ix == 1 ? K2yz : fmaf(27.0f * cx, a3xyz, K2yz);
-                    float T0[3], T1[3], T2[3];
-                    quad3(U0[ix], U1[ix], U2, T0[0], T0[1], T0[2]);
-                    {   // T1 = quad3(V0, V1, 13.5 a3yyz)
-                        const float m = fmaf(9.0f, a3yyz, V0[ix]);
-                        T1[1] = fmaf(-4.5f, a3yyz, V0[ix]);
-                        T1[0] = m - V1;
-                        T1[2] = m + V1;
-                    }
-                    T2[0] = fmaf(-13.5f, a3zzy, W0[ix]);
-                    T2[1] = W0[ix];
-                    T2[2] = fmaf(13.5f, a3zzy, W0[ix]);
-#pragma unroll
-                    for (int iy = 0; iy < 3; ++iy) {
-                        const int k = ix + 3 * iy;
-                        const float mid = fmaf(T2[iy], 2.0f / 3.0f, T0[iy]);
-                        t0[k] = fmaf(T2[iy], -1.0f / 3.0f, T0[iy]);
-                        tm[k] = mid - T1[iy];
-                        tp[k] = mid + T1[iy];
-                    }
-                }
+                expand_c<true>(Jx, Jy, Jz, a2xx, a2yy, a2zz, a2xy, a2xz, a2yz, a3xxy, a3xxz, a3yyx, a3yyz, a3zzx, a3zzy,
+                               a3xyz, [&](int ix, int iy, float T0, float T1, float T2) {
+                                   const int k = ix + 3 * iy;
+                                   const float mid = fmaf(T2, 2.0f / 3.0f, T0);
+                                   t0[k] = fmaf(T2, -1.0f / 3.0f, T0);
+                                   tm[k] = mid - T1;
+                                   tp[k] = mid + T1;
+                               });
                 T0c = tm[4];
                 T1c = t0[4];
                 T2c = tp[4];
@@ -1016,63 +1028,17 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             const float a3yyx = fmaf(u1, sxy, u0 * myy), a3yyz = fmaf(u1, syz, u2 * myy);
             const float a3zzx = fmaf(u2, sxz, u0 * mzz), a3zzy = fmaf(u2, syz, u1 * mzz);
             const float a3xyz = fmaf(rxy, u2, fmaf(u0, myz, fmaf(u1, mxz, u2 * mxy)));
-            // The scale factors of the coefficients (3 J, 4.5 a2_aa, 9 a2_ab, 13.5 a3_aab,
-            // 27 a3_xyz) are folded into the constants of the multiply-adds that take
-            // a coefficient as a slope or curvature term; only the five that enter as
-            // an addend are scaled explicitly.
-            const float K1y = 3.0f * Jy, K1z = 3.0f * Jz;
-            const float K2yy = 4.5f * a2yy, K2zz = 4.5f * a2zz, K2yz = 9.0f * a2yz;
-            // t = T0 + cz T1 + h(cz) T2; T0 = U0 + cy U1 + h(cy) U2 (per cx), etc.
-            float U0[3], U1[3], V0[3], W0[3];
-            {   // U0 = quad3(0, 3 Jx, 4.5 a2xx): tau = t - rho'
-                const float m = 3.0f * a2xx;
-                U0[1] = -1.5f * a2xx;
-                U0[0] = fmaf(-3.0f, Jx, m);
-                U0[2] = fmaf(3.0f, Jx, m);
-            }
-            {   // U1 = quad3(3 Jy, 9 a2xy, 13.5 a3xxy)
-                const float m = fmaf(9.0f, a3xxy, K1y);
-                U1[1] = fmaf(-4.5f, a3xxy, K1y);
-                U1[0] = fmaf(-9.0f, a2xy, m);
-                U1[2] = fmaf(9.0f, a2xy, m);
-            }
-            {   // V0 = quad3(3 Jz, 9 a2xz, 13.5 a3xxz)
-                const float m = fmaf(9.0f, a3xxz, K1z);
-                V0[1] = fmaf(-4.5f, a3xxz, K1z);
-                V0[0] = fmaf(-9.0f, a2xz, m);
-                V0[2] = fmaf(9.0f, a2xz, m);
-            }
-            W0[0] = fmaf(-13.5f, a3zzx, K2zz);
-            W0[1] = K2zz;
-            W0[2] = fmaf(13.5f, a3zzx, K2zz);
-#pragma unroll
-            for (int ix = 0; ix < 3; ++ix) {
-                const float cx = (float)(ix - 1);
-                const float U2 = ix == 1 ? K2yy : fmaf(13.5f * cx, a3yyx, K2yy);  // linear in cx
-                const float V1 = ix == 1 ? K2yz : fmaf(27.0f * cx, a3xyz, K2yz);
-                float T0[3], T1[3], T2[3];
-                quad3(U0[ix], U1[ix], U2, T0[0], T0[1], T0[2]);
-                {   // T1 = quad3(V0, V1, 13.5 a3yyz)
-                    const float m = fmaf(9.0f, a3yyz, V0[ix]);
-                    T1[1] = fmaf(-4.5f, a3yyz, V0[ix]);
-                    T1[0] = m - V1;
-                    T1[2] = m + V1;
-                }
-                T2[0] = fmaf(-13.5f, a3zzy, W0[ix]);
-                T2[1] = W0[ix];
-                T2[2] = fmaf(13.5f, a3zzy, W0[ix]);
-                // ---- S5a: publish what crosses columns ----
-#pragma unroll
-                for (int iy = 0; iy < 3; ++iy) {
-                    if (ix == 1 && iy == 1) {
-                        T0c = T0[1];
-                        T1c = T1[1];
-                        T2c = T2[1];
-                    } else {
-                        rec[xy_slot(ix - 1, iy - 1)] = vec4{T0[iy], T1[iy], T2[iy], rp};
-                    }
-                }
-            }
+            // ---- S5a: publish what crosses columns ----
+            expand_c<false>(Jx, Jy, Jz, a2xx, a2yy, a2zz, a2xy, a2xz, a2yz, a3xxy, a3xxz, a3yyx, a3yyz, a3zzx, a3zzy, a3xyz,
+                            [&](int ix, int iy, float T0, float T1, float T2) {
+                                if (ix == 1 && iy == 1) {
+                                    T0c = T0;
+                                    T1c = T1;
+                                    T2c = T2;
+                                } else {
+                                    rec[xy_slot(ix - 1, iy - 1)] = vec4{T0, T1, T2, rp};
+                                }
+                            });
             }
             if constexpr (PH) {
                 // phase: base to every axis neighbour, +-a_e along +-e, phi - 6 base stays
