@@ -29,6 +29,7 @@ import ctypes
 import hashlib
 import json
 import os
+import re
 import statistics
 import sys
 import time
@@ -39,8 +40,8 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 BYTES_PER_NODE = {"fp32": 88, "fp16": 48, "bf16": 48, "fp16q": 64}
 BYTES_PER_NODE_1C = {"fp32": 80, "fp16": 40, "bf16": 40, "fp16q": 56}  # one component: no phase plane
-# HBM traffic of the fused step from rocprofv3 counters, valid while the kernel
-# sources hash to the value recorded next to the figures
+# HBM traffic of the fused step from rocprofv3 counters, valid while the code of the
+# kernel and of its launch plan hashes to the value recorded next to the figures
 TRAFFIC_FILES = {"jet128": os.path.join(ROOT, "profiles", "fused_step_jet128_traffic.txt"),
                  "tgv256": os.path.join(ROOT, "profiles", "fused_step_tgv256_1c_traffic.txt"),
                  "jet512": os.path.join(ROOT, "profiles", "fused_step_jet512_traffic.txt")}
@@ -109,11 +110,19 @@ def describe(name, p):
             "nodes": p["nx"] * p["ny"] * p["nz"]}
 
 
+def code_of(text):
+    """C++ source without its comments and blank space at line ends: what a measurement of
+    the compiled program depends on."""
+    text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
+    lines = (re.sub(r"//.*", "", ln).rstrip() for ln in text.splitlines())
+    return "\n".join(ln for ln in lines if ln) + "\n"
+
+
 def sources_hash():
     h = hashlib.sha256()
     for rel in KERNEL_SOURCES:
-        with open(os.path.join(ROOT, rel), "rb") as f:
-            h.update(f.read())
+        with open(os.path.join(ROOT, rel), encoding="utf-8") as f:
+            h.update(code_of(f.read()).encode())
     return h.hexdigest()[:16]
 
 
