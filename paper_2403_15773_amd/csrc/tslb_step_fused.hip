@@ -21,10 +21,12 @@
 // Each destination node is written by exactly one thread and every read is of
 // step t, so the update is race-free (the thread-safe property of the method).
 //
-// What bounds it.  Vector instructions and the latency of two dependent phases per
-// plane, not HBM; on large lattices with every node moving the chip also lowers its
-// clock, so instructions and LDS words cost time twice.  What the choices below
-// bought, each step timed on a 128 x 128 x 512 jet in motion (us a step):
+// What bounds it.  Vector instructions (74 % of the SIMDs' cycles on a 128 x 128 x 512
+// jet, 70 % at 512 x 512 x 2048, 54 % with one component) and the latency of two
+// dependent phases per plane, not HBM; on large lattices with every node moving the
+// chip also lowers its clock, so instructions and LDS words cost time twice.  What the
+// choices below bought, each step timed on a 128 x 128 x 512 jet in motion (us a step, in turn with the
+// one before; devices differ in clock, the last takes 184 to 188 on others):
 //   252  populations exchanged per c_z, G from 13 differences per column and plane
 //   226  the T exchanged instead (the c_z expansion and the neighbour density
 //        difference then act on 6 sums and on T0 instead of on 27 populations), 16-byte
@@ -62,8 +64,8 @@
 // change of rounding in binary32 turns into other roundings of stored moments, and
 // those travel: ten steps of a jet with BF16 moments then differ by 5e-3 in the
 // stress, as much as from the exact result.  Waves, tiles and the LDS records are the
-// same.  It takes 30 % more vector instructions (128 x 128 x 512 jet, FP16, 207 us a
-// step; 248 with its geometry spread over the source waves).
+// same.  It takes 25 % more vector instructions (731 a node, 586 in binary32; 128 x 128 x
+// 512 jet, FP16, 188 us a step; 248 with its geometry spread over the source waves).
 // Variable density and viscosity (VD): the velocity-based form of the phase-field
 // scheme for components of different density.  The stored rho' is then the
 // normalised pressure p*, the velocity terms of the rebuild take unit density,
@@ -75,8 +77,9 @@
 // Precision: the source builds tau = t - rho' (no density part) and publishes its
 // rho' beside it; the destination forms t - rho'(own column, same plane) as
 // tau + (rho'(source) - rho'(own column)), exact differences of neighbours, and
-// puts rho'(own column) back into the zeroth moment only.  No sum is rounded at
-// the magnitude of rho' except in z and in the final density itself.
+// puts rho'(own column) back into the zeroth moment only; in binary32 it takes the
+// differences of tau and of rho' apart (xy_moments).  No sum is rounded at the magnitude
+// of rho' except in z and in the final density itself.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -1165,8 +1168,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             // tenth of an ulp a step stays below what the sum resolves).  With variable
             // density p* is larger than the stress by far: there the sums stay without it
             // and the exact differences between planes (dr, from ZR) enter, with which a
-            // droplet at density ratio 1:10 keeps its stress within 7e-6 of the oracle
-            // after 200 steps (1.1e-5 with p* added in).
+            // droplet at density ratio 1:10 keeps its stress within 5.7e-6 of the oracle
+            // after 200 steps (1.1e-5 with p* added in, in an earlier form).
             // Elsewhere the large term comes in last, so that M, P and ZS are rounded once
             // at its magnitude.  With that, the differences of xy_moments and J rounded
             // once, the rms error of the stress against binary64 is, after ten steps of a
