@@ -116,7 +116,13 @@ typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
 // The gradient ring holds G itself for the variable-density step (its forces
 // take G directly), else only |G| + eps: the force is rebuilt as n (|G| + eps)
 // from the stored normal, which keeps the 20-row tile within 160 KB of LDS.
-template <bool PH, bool VD, int ROWS> struct alignas(16) Smem {
+// One component has no phase field to publish.  Its exchange buffer is laid out by
+// direction (DIR) where that was the faster, 10 KB less: two workgroups share a compute
+// unit where a launch has more of them than units, as before the records (186 x 6 x 853
+// BF16 46.4 us a step, 47.3 with records; 256^3 vortex 265.6 and 267.9, FP16 249 and 257,
+// BF16 255 and 267).  FP16Q keeps the records of two components (267 us, 275 by direction).
+template <int ST, bool PH> constexpr bool by_direction = !PH && ST != ST_FP16Q;
+template <bool PH, bool VD, int ROWS, bool DIR> struct alignas(16) Smem {
     using T = Tile<ROWS>;
     float xch[T::NSRC][T::REC];        // populations crossing columns
     int32_t phi[4][T::NPHI];           // fixed-point phase field, ring of 4 planes
@@ -124,11 +130,17 @@ template <bool PH, bool VD, int ROWS> struct alignas(16) Smem {
     float G[2][VD ? 3 : 1][T::NSRC];   // gradient (VD) or |G| + eps on the source region, ring of 2 planes
     float kap[T::NSRC];                // 72 kappa of the next source plane
 };
-template <bool VD, int ROWS> struct alignas(16) Smem<false, VD, ROWS> {
+template <bool VD, int ROWS> struct alignas(16) Smem<false, VD, ROWS, false> {
     float xch[Tile<ROWS>::NSRC][Tile<ROWS>::REC];  // populations crossing columns
 };
-static_assert(sizeof(Smem<true, false, 20>) <= 160 * 1024 && sizeof(Smem<true, true, 16>) <= 160 * 1024,
+template <bool VD, int ROWS> struct alignas(16) Smem<false, VD, ROWS, true> {
+    vec4 xch[8][Tile<ROWS>::NSRC];  // populations crossing columns
+};
+static_assert(sizeof(Smem<true, false, 20, false>) <= 160 * 1024 && sizeof(Smem<true, true, 16, false>) <= 160 * 1024,
               "LDS of one workgroup");
+static_assert(2 * sizeof(Smem<false, false, 16, true>) <= 160 * 1024, "LDS of two workgroups");
+// Waves a SIMD holds: of one workgroup of 16 waves, or of two of ten.
+template <int ST, bool PH> constexpr int waves_per_simd = by_direction<ST, PH> ? 5 : PH ? 4 : 3;
 
 // f(0), ..., f(N - 1) with compile-time indices.  An unrolled loop over an array that
 // lives across branches or iterations is too late: the compiler has made the array one
@@ -450,7 +462,7 @@ using PhysMem = const __attribute__((address_space(4))) Phys *;
 // copy of the step apart from the single-lattice kernel's, whose code is
 // otherwise changed (and slowed) by the second user of the same instantiation.
 template <int ST, bool PH, bool MULTI, bool VD, int ROWS, bool NT>
-__device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g, const Phys &ph, PhysMem walls,
+__device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, PH>> &sm, const Geo &g, const Phys &ph, PhysMem walls,
                                            const Scales &sc, const StateView &in, const StateView &out, int lz,
                                            int tiles_x, int tiles_y, unsigned long long step_next, int w) {
 // multiply-adds are written out: every instantiation rounds alike
@@ -933,7 +945,12 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             }
             const float rho = VD ? 1.0f : ST == ST_FP16 ? rho_cur : 1.0f + rp;  // density of the velocity terms
             float u0 = mom_cur[1], u1 = mom_cur[2], u2 = mom_cur[3];
-            vec4 *rec = (vec4 *)&sm.xch[sidx][0];
+            auto rec = [&](int slot) -> vec4 & {  // where this source publishes `slot`
+                if constexpr (by_direction<ST, PH>)
+                    return sm.xch[slot][sidx];
+                else
+                    return ((vec4 *)&sm.xch[sidx][0])[slot];
+            };
             rpc = rp;
             if constexpr (H) {
                 // populations of c_z = -1, 0, +1 in place of the three T
@@ -979,7 +996,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 T2c = tp[4];
 #pragma unroll
                 for (int k = 0; k < 9; ++k)
-                    if (k != 4) rec[xy_slot(k % 3 - 1, k / 3 - 1)] = vec4{tm[k], t0[k], tp[k], rp};
+                    if (k != 4) rec(xy_slot(k % 3 - 1, k / 3 - 1)) = vec4{tm[k], t0[k], tp[k], rp};
             } else {
             // m = (1 - omega) P and a2 of the header, with g = F/rho, v = ubar + g, J = rho v
             // (formed from ubar and F: one rounding):
@@ -1039,7 +1056,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                                     T1c = T1;
                                     T2c = T2;
                                 } else {
-                                    rec[xy_slot(ix - 1, iy - 1)] = vec4{T0, T1, T2, rp};
+                                    rec(xy_slot(ix - 1, iy - 1)) = vec4{T0, T1, T2, rp};
                                 }
                             });
             }
@@ -1053,7 +1070,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
                 const int32_t ax = __float2int_rn(h8 * fmaf(4.0f, u0, gph * n0));
                 const int32_t ay = __float2int_rn(h8 * fmaf(4.0f, u1, gph * n1));
                 const int32_t az = __float2int_rn(h8 * fmaf(4.0f, u2, gph * n2));
-                *(ivec4 *)&rec[8] = ivec4{base + ax, base - ax, base + ay, base - ay};  // +x, -x, +y, -y
+                *(ivec4 *)&rec(8) = ivec4{base + ax, base - ax, base + ay, base - ay};  // +x, -x, +y, -y
                 // phi - 6 base, kept from becoming a 64-bit multiply-add (whose unused upper
                 // addend may be a register that a prefetch is still loading: its wait)
                 int32_t base2 = 2 * base, base4 = 4 * base;
@@ -1090,14 +1107,19 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             t0[4] = T0c;
             t1[4] = T1c;
             t2[4] = T2c;
-            const float(*xc)[T::REC] = &sm.xch[sidx - SX - 1];  // record of the source at (x - 1, y - 1)
+            auto arrived = [&](int dx, int dy, int slot) -> const vec4 & {  // from the source at (x + dx, y + dy)
+                if constexpr (by_direction<ST, PH>)
+                    return sm.xch[slot][sidx + dy * SX + dx];
+                else
+                    return ((const vec4 *)&sm.xch[sidx - SX - 1][0] + ((1 + dy) * SX + 1 + dx) * (T::REC / 4))[slot];
+            };
 #pragma unroll
             for (int cy = -1; cy <= 1; ++cy)
 #pragma unroll
                 for (int cx = -1; cx <= 1; ++cx) {
                     if (!cx && !cy) continue;
                     const int k = (cx + 1) + 3 * (cy + 1);
-                    const vec4 v = ((const vec4 *)&xc[(1 - cy) * SX + (1 - cx)][0])[xy_slot(cx, cy)];
+                    const vec4 v = arrived(-cx, -cy, xy_slot(cx, cy));
                     if constexpr (H) {
                         const float drp = v.w - rpc;
                         t0[k] = v.x + drp;
@@ -1122,7 +1144,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
             }
             int32_t pin = 0;
             if constexpr (PH) {
-                const int32_t(*xi)[T::REC] = (const int32_t(*)[T::REC])xc;
+                const int32_t(*xi)[T::REC] = (const int32_t(*)[T::REC])&sm.xch[sidx - SX - 1];
                 pin = xi[SX][32] + xi[SX + 2][33] + xi[1][34] + xi[2 * SX + 1][35];
             }
             float dr = 0.f;
@@ -1322,10 +1344,10 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS> &sm, const Geo &g,
 
 static_assert(sizeof(Geo) % alignof(Phys) == 0 && alignof(Geo) == alignof(Phys), "ph follows g directly");
 template <int ST, bool PH, bool VD, int ROWS, bool NT>
-__global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
+__global__ __launch_bounds__(Tile<ROWS>::threads(PH), (waves_per_simd<ST, PH>)) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
                                                                int lz, int tiles_x, int tiles_y,
                                                                unsigned long long step_next, int first) {
-    __shared__ Smem<PH, VD, ROWS> sm;
+    __shared__ Smem<PH, VD, ROWS, by_direction<ST, PH>> sm;
     // ph sits behind g in the kernel's argument segment
     const PhysMem walls = (PhysMem)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
                                     sizeof(Geo));
@@ -1336,8 +1358,8 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused(Geo g, P
 // Several lattices in one launch: the work items of domain k are
 // [work_begin, work_begin + tiles * chunks); domains are sorted by work_begin.
 template <int ST, bool PH, bool VD, int ROWS, bool NT>
-__global__ __launch_bounds__(Tile<ROWS>::threads(PH)) void k_step_fused_multi(const FusedDomain *__restrict__ doms, int ndom, int first) {
-    __shared__ Smem<PH, VD, ROWS> sm;
+__global__ __launch_bounds__(Tile<ROWS>::threads(PH), (waves_per_simd<ST, PH>)) void k_step_fused_multi(const FusedDomain *__restrict__ doms, int ndom, int first) {
+    __shared__ Smem<PH, VD, ROWS, by_direction<ST, PH>> sm;
     const int w = first + xcd_work_item(blockIdx.x, gridDim.x);
     int lo = 0, hi = ndom - 1;
     while (lo < hi) {
