@@ -50,7 +50,7 @@ inline int chunk_under_bound(int nz, int L) {
 // Cost of 20 rows, from jets timed at both heights: about 1.25 in one round of
 // workgroups, 1.15 to 1.30 in several, where the last round is not full and neighbours
 // share less.  Of 32 jets in binary32 1.22 takes the faster height or one within 4.7 %
-// (512 x 512 x 2048: 20 rows between 1.5 % faster and 1.5 % slower on two devices;
+// (512 x 512 x 2048: 20 rows 1.5 % faster in one process and 1.5 % slower in another;
 // 320 x 240 x 640 16 rows, 1116 and 1081 us; 157 x 229 x 103 20 rows, 110 and 115), 0.45 %
 // on average.  With 16-bit moments their geometry, four waves' work there, is the
 // longer chain of phase A: 1.23 to 1.32, of 31 jets in each type 1.26 takes the faster or

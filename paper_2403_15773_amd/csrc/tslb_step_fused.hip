@@ -25,8 +25,8 @@
 // jet, 70 % at 512 x 512 x 2048, 54 % with one component) and the latency of two
 // dependent phases per plane, not HBM; on large lattices with every node moving the
 // chip also lowers its clock, so instructions and LDS words cost time twice.  What the
-// choices below bought, each step timed on a 128 x 128 x 512 jet in motion (us a step, in turn with the
-// one before; devices differ in clock, the last takes 184 to 188 on others):
+// choices below bought, each timed on a 128 x 128 x 512 jet in motion in turn with the
+// one before (us a step; from process to process the last varies from 180 to 189):
 //   252  populations exchanged per c_z, G from 13 differences per column and plane
 //   226  the T exchanged instead (the c_z expansion and the neighbour density
 //        difference then act on 6 sums and on T0 instead of on 27 populations), 16-byte
