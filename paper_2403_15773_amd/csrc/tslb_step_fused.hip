@@ -555,12 +555,14 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
     const float sigma72 = ph.sigma * (1.0f / 72.0f), gamma = ph.gamma;
 
     // carried destination state (see S6)
-    float ZA = 0.f, ZD = 0.f, ZR = 0.f, ZS[5], ZO[2], ZP[6];
+    float ZA[3], ZD[3], ZQ[3], ZP[6], ZR = 0.f;
+    each<3>([&](auto i_) {
+        constexpr int k = i_;
+        ZA[k] = ZD[k] = ZQ[k] = 0.f;
+    });
     each<6>([&](auto i_) {
         constexpr int k = i_;
         ZP[k] = 0.f;
-        if (k < 5) ZS[k] = 0.f;
-        if (k < 2) ZO[k] = 0.f;
     });
     float XA[6], XB[6], XC[6];  // with 16-bit moments: X(+1) and X(0) of plane r - 1, X(+1) of plane r
     each<6>([&](auto i_) {
@@ -1182,9 +1184,9 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
             // The populations of c_z = -1, 0, +1 sum to M, Z, P (X = X0 + c_z X1 +
             // (c_z^2 - 1/3) X2) and belong to planes r - 1, r, r + 1.  The plane r still
             // lacks the M of plane r + 1.  Kept for it: of rho', which needs all three z
-            // moments, Z (ZA) and P(r - 1) - Z (ZD); of the others the weighted sum of
-            // Z and P(r - 1) (ZS), and of j_x and j_y, whose first z moment is needed too,
-            // P(r - 1) itself (ZO).  For the plane above: P (ZP).
+            // moments, Z (ZA[0]) and P(r - 1) - Z (ZD[0]); of the others the weighted sum of
+            // Z and P(r - 1) (ZA[1], ZA[2], ZQ), and of j_x and j_y, whose first z moment is
+            // needed too, P(r - 1) itself (ZD[1], ZD[2]).  For the plane above: P (ZP).
             // rho' of the own column comes back last, one rounding at its magnitude, which
             // also keeps the density of a uniform stream from creeping by rounding (a
             // tenth of an ulp a step stays below what the sum resolves).  With variable
@@ -1192,8 +1194,8 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
             // and the exact differences between planes (dr, from ZR) enter, with which a
             // droplet at density ratio 1:10 keeps its stress within 5.7e-6 of the oracle
             // after 200 steps (1.1e-5 with p* added in, in an earlier form).
-            // Elsewhere the large term comes in last, so that M, P and ZS are rounded once
-            // at its magnitude.  With that, the differences of xy_moments and J rounded
+            // Elsewhere the large term comes in last, so that M, P and the weighted sums are
+            // rounded once at its magnitude.  With that, the differences of xy_moments and J rounded
             // once, the rms error of the stress against binary64 is, after ten steps of a
             // 256^3 vortex 8.3e-10 (9.2e-10 with Z, P - Z and a rounding more in each of M,
             // P and J; 8.5e-10 where 27 populations are summed), of a 128 x 128 x 256 jet
@@ -1211,15 +1213,15 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
             else
                 M[0] += rpc;
             // (X carries the factors 1, 6, 6, 9, 9, 36 of xy_moments)
-            const float d00 = VD ? (M[0] - ZA) + dr : M[0] - ZA;
-            const float s00 = d00 + ZD;
-            const float drho = VD ? ZR + fmaf(s00, 1.0f / 6.0f, ZA) : fmaf(s00, 1.0f / 6.0f, ZA);
-            const float jz = (ZD - d00) * (1.0f / 6.0f), Hzz = s00 * (1.0f / 9.0f);
-            const float jx = fmaf(M[1], 1.0f / 36.0f, ZS[0]), Hxz = (ZO[0] - M[1]) * (1.0f / 36.0f);
-            const float jy = fmaf(M[2], 1.0f / 36.0f, ZS[1]), Hyz = (ZO[1] - M[2]) * (1.0f / 36.0f);
-            const float Hxx = fmaf(M[3], 1.0f / 54.0f, ZS[2]);
-            const float Hyy = fmaf(M[4], 1.0f / 54.0f, ZS[3]);
-            const float Hxy = fmaf(M[5], 1.0f / 216.0f, ZS[4]);
+            const float d00 = VD ? (M[0] - ZA[0]) + dr : M[0] - ZA[0];
+            const float s00 = d00 + ZD[0];
+            const float drho = VD ? ZR + fmaf(s00, 1.0f / 6.0f, ZA[0]) : fmaf(s00, 1.0f / 6.0f, ZA[0]);
+            const float jz = (ZD[0] - d00) * (1.0f / 6.0f), Hzz = s00 * (1.0f / 9.0f);
+            const float jx = fmaf(M[1], 1.0f / 36.0f, ZA[1]), Hxz = (ZD[1] - M[1]) * (1.0f / 36.0f);
+            const float jy = fmaf(M[2], 1.0f / 36.0f, ZA[2]), Hyz = (ZD[2] - M[2]) * (1.0f / 36.0f);
+            const float Hxx = fmaf(M[3], 1.0f / 54.0f, ZQ[0]);
+            const float Hyy = fmaf(M[4], 1.0f / 54.0f, ZQ[1]);
+            const float Hxy = fmaf(M[5], 1.0f / 216.0f, ZQ[2]);
             const float inv = VD ? 1.0f : recip(1.0f + drho);
             m[0] = drho;
             m[1] = jx * inv;
@@ -1248,19 +1250,20 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
                 constexpr int k = i_;
                 keep_here(X0[k], X2[k]);
             });
-            ZA = fmaf(X2[0], -1.0f / 3.0f, X0[0]);
-            if (!VD) ZA += rpc;
-            ZD = VD ? (ZP[0] - ZA) - dr : ZP[0] - ZA;
-            keep_here(ZA, ZD);
+            ZA[0] = fmaf(X2[0], -1.0f / 3.0f, X0[0]);
+            if (!VD) ZA[0] += rpc;
+            ZD[0] = VD ? (ZP[0] - ZA[0]) - dr : ZP[0] - ZA[0];
+            keep_here(ZA[0], ZD[0]);
             each<5>([&](auto i_) {
                 constexpr int k = i_ + 1;  // weights (1, 4, 1)/6 over the factor of X
                 constexpr float c = k < 3 ? 1.0f / 36.0f : k < 5 ? 1.0f / 54.0f : 1.0f / 216.0f;
                 constexpr float c3 = k < 3 ? 1.0f / 27.0f : k < 5 ? 2.0f / 81.0f : 1.0f / 162.0f;  // 4 c / 3
-                ZS[k - 1] = fmaf(X0[k], 4.0f * c, fmaf(X2[k], -c3, ZP[k] * c));
-                keep_here(ZS[k - 1]);
+                float &sum = k < 3 ? ZA[k % 3] : ZQ[k % 3];
+                sum = fmaf(X0[k], 4.0f * c, fmaf(X2[k], -c3, ZP[k] * c));
+                keep_here(sum);
                 if constexpr (k < 3) {
-                    ZO[k - 1] = ZP[k];
-                    keep_here(ZO[k - 1]);
+                    ZD[k] = ZP[k];
+                    keep_here(ZD[k]);
                 }
             });
             each<6>([&](auto i_) {
@@ -1343,7 +1346,14 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
 
 
 static_assert(sizeof(Geo) % alignof(Phys) == 0 && alignof(Geo) == alignof(Phys), "ph follows g directly");
-template <int ST, bool PH, bool VD, int ROWS, bool NT>
+// `first` is the first work item of a launch that is one of several.  PART: it is used.
+// As an argument of every launch it moved the compiler's registers about in the other
+// loops: two components FP16Q 2 % and FP16 1 to 2 % slower (128^3 droplet 52.2 and 53.4 us
+// a step, 100 x 100 x 200 jet 72.8 and 74.4), BF16 2 % faster (131 x 77 x 301 jet 98.4 and
+// 95.9), one component 1 to 4 % faster.  So it always is for the latter two, and a kernel
+// of its own does the rest.
+template <int ST, bool PH> constexpr bool takes_first = !PH || ST == ST_BF16;
+template <int ST, bool PH, bool VD, int ROWS, bool NT, bool PART>
 __global__ __launch_bounds__(Tile<ROWS>::threads(PH), (waves_per_simd<ST, PH>)) void k_step_fused(Geo g, Phys ph, Scales sc, StateView in, StateView out,
                                                                int lz, int tiles_x, int tiles_y,
                                                                unsigned long long step_next, int first) {
@@ -1352,7 +1362,7 @@ __global__ __launch_bounds__(Tile<ROWS>::threads(PH), (waves_per_simd<ST, PH>)) 
     const PhysMem walls = (PhysMem)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
                                     sizeof(Geo));
     step_fused<ST, PH, false, VD, ROWS, NT>(sm, g, ph, walls, sc, in, out, lz, tiles_x, tiles_y, step_next,
-                                               first + xcd_work_item(blockIdx.x, gridDim.x));
+                                               (PART ? first : 0) + xcd_work_item(blockIdx.x, gridDim.x));
 }
 
 // Several lattices in one launch: the work items of domain k are
@@ -1450,12 +1460,15 @@ void launch_one(long long items, hipStream_t s, const tslb_ctx *c, StateView in,
                 int tiles_y, unsigned long long sn) {
     using namespace fused;
     constexpr int threads = Tile<ROWS>::threads(PH);
-    const bool nt = fused_stream_stores(c, c->buffer_bytes);
+    constexpr bool part = takes_first<ST, PH>;
+    const bool nt = fused_stream_stores(c, c->buffer_bytes), several = launch_blocks(items, threads) < items;
+    const auto kernel = several && !part ? k_step_fused<ST, PH, VD, ROWS, true, true>
+                        : nt             ? k_step_fused<ST, PH, VD, ROWS, true, part>
+                                         : k_step_fused<ST, PH, VD, ROWS, false, part>;
     for (long long first = 0, n; first < items; first += n) {
         n = launch_blocks(items - first, threads);
-        hipLaunchKernelGGL((nt ? k_step_fused<ST, PH, VD, ROWS, true> : k_step_fused<ST, PH, VD, ROWS, false>),
-                           dim3((unsigned)n), dim3(threads), 0, s, c->geo, c->phys, c->scales, in, out, lz, tiles_x,
-                           tiles_y, sn, (int)first);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(threads), 0, s, c->geo, c->phys, c->scales, in, out, lz,
+                           tiles_x, tiles_y, sn, (int)first);
     }
 }
 
