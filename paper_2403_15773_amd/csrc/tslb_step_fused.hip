@@ -21,7 +21,7 @@
 // Each destination node is written by exactly one thread and every read is of
 // step t, so the update is race-free (the thread-safe property of the method).
 //
-// What bounds it.  Vector instructions (74 % of the SIMDs' cycles on a 128 x 128 x 512
+// What bounds it.  Vector instructions (75 % of the SIMDs' cycles on a 128 x 128 x 512
 // jet, 70 % at 512 x 512 x 2048, 54 % with one component) and the latency of two
 // dependent phases per plane, not HBM; on large lattices with every node moving the
 // chip also lowers its clock, so instructions and LDS words cost time twice.  What the
@@ -64,7 +64,7 @@
 // change of rounding in binary32 turns into other roundings of stored moments, and
 // those travel: ten steps of a jet with BF16 moments then differ by 5e-3 in the
 // stress, as much as from the exact result.  Waves, tiles and the LDS records are the
-// same.  It takes 25 % more vector instructions (731 a node, 586 in binary32; 128 x 128 x
+// same.  It takes 25 % more vector instructions (735 a node, 589 in binary32; 128 x 128 x
 // 512 jet, FP16, 188 us a step; 248 with its geometry spread over the source waves).
 // Variable density and viscosity (VD): the velocity-based form of the phase-field
 // scheme for components of different density.  The stored rho' is then the
@@ -119,8 +119,8 @@ typedef int32_t ivec4 __attribute__((ext_vector_type(4)));
 // One component has no phase field to publish.  Its exchange buffer is laid out by
 // direction (DIR) where that was the faster, 10 KB less: two workgroups share a compute
 // unit where a launch has more of them than units, as before the records (186 x 6 x 853
-// BF16 46.4 us a step, 47.3 with records; 256^3 vortex 265.6 and 267.9, FP16 249 and 257,
-// BF16 255 and 267).  FP16Q keeps the records of two components (267 us, 275 by direction).
+// BF16 46.1 us a step, 47.3 with records; 256^3 vortex 265.6 and 267.9, FP16 249 and 257,
+// BF16 258 and 261).  FP16Q keeps the records of two components (267 us, 275 by direction).
 template <int ST, bool PH> constexpr bool by_direction = !PH && ST != ST_FP16Q;
 template <bool PH, bool VD, int ROWS, bool DIR> struct alignas(16) Smem {
     using T = Tile<ROWS>;
@@ -879,7 +879,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
         }
         each<10>([&](auto i_) {
             constexpr int k = i_;
-            mom_cur[k] = decode_moment<ST>(mom[k], k, sc);
+            mom_cur[k] = ST == ST_BF16 && k == 0 ? __uint_as_float(mom[0] << 16) : decode_moment<ST>(mom[k], k, sc);
             if (!VD && !H && k >= 4) mom_cur[k] *= omega1;  // (1 - omega) Q
             // formed before the loads below, which then reuse the words' registers
             keep_here(mom_cur[k]);
@@ -922,7 +922,12 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
             }
 
             // ---- S4: post-collision populations of the source ----
-            const float rp = mom_cur[0];
+            float rp = mom_cur[0];
+            if constexpr (ST == ST_BF16) {  // scaled here, from the word: one register less over the loads, 5 % (256^3 vortex)
+                rho_cur = fmaf(rp, sc.s2, 1.0f);
+                rp *= sc.s2;
+                keep_here(rp);
+            }
             float om1 = omega1;
             if constexpr (VD) {
                 // rho(phi), omega(phi) and the acceleration that replaces F
@@ -945,7 +950,7 @@ __device__ __forceinline__ void step_fused(Smem<PH, VD, ROWS, by_direction<ST, P
 #pragma unroll
                 for (int k = 4; k < 10; ++k) mom_cur[k] *= om1;
             }
-            const float rho = VD ? 1.0f : ST == ST_FP16 ? rho_cur : 1.0f + rp;  // density of the velocity terms
+            const float rho = VD ? 1.0f : ST == ST_FP16 || ST == ST_BF16 ? rho_cur : 1.0f + rp;  // density of the velocity terms
             float u0 = mom_cur[1], u1 = mom_cur[2], u2 = mom_cur[3];
             auto rec = [&](int slot) -> vec4 & {  // where this source publishes `slot`
                 if constexpr (by_direction<ST, PH>)
@@ -1349,8 +1354,8 @@ static_assert(sizeof(Geo) % alignof(Phys) == 0 && alignof(Geo) == alignof(Phys),
 // `first` is the first work item of a launch that is one of several.  PART: it is used.
 // As an argument of every launch it moved the compiler's registers about in the other
 // loops: two components FP16Q 2 % and FP16 1 to 2 % slower (128^3 droplet 52.2 and 53.4 us
-// a step, 100 x 100 x 200 jet 72.8 and 74.4), BF16 2 % faster (131 x 77 x 301 jet 98.4 and
-// 95.9), one component 1 to 4 % faster.  So it always is for the latter two, and a kernel
+// a step, 100 x 100 x 200 jet 72.8 and 74.4), BF16 2 % faster (131 x 77 x 301 jet 98.1 and
+// 100.1), one component up to 4 % faster.  So it always is for the latter two, and a kernel
 // of its own does the rest.
 template <int ST, bool PH> constexpr bool takes_first = !PH || ST == ST_BF16;
 template <int ST, bool PH, bool VD, int ROWS, bool NT, bool PART>
